@@ -61,7 +61,13 @@ typedef enum dd_status {
   DD_ERR_TIMEOUT = 9         /* serving wait timed out */
 } dd_status;
 
-/* Projection algorithms (dd_project_opts.mode). */
+/* Projection algorithms (dd_project_opts.mode).
+ *
+ * The FP64, FP32, BF16 and FP16 scans of larger problems (dd_project, dd_solve
+ * and the server; from 2^18 to 2^19 data points, fewer for large batches) leave
+ * out tiles of the data set that cannot hold the nearest point: those whose
+ * bounding box lies farther from every query of a group than a data point
+ * already found for it.  The results are those of the scan over all tiles. */
 typedef enum dd_mode {
   /* FP64 MFMA scan of the whole data set in whitened coordinates (expanded
    * form), candidates inside a proven FP64 error margin reranked in the direct
@@ -131,9 +137,11 @@ typedef struct dd_dataset_opts {
 typedef struct dd_project_stats {
   int64_t candidates;       /* candidates reranked in FP64 (mixed modes) */
   int64_t overflowed;       /* queries rescanned by the FP64 fallback */
-  int64_t visited;          /* data points visited (DD_ANN, DD_KMEANS) */
-  double scan_ms;           /* device time of the main scan kernel, the one pass over every
-                               (query, data point) pair (HIP events on the call's stream) */
+  int64_t visited;          /* data points visited (DD_ANN, DD_KMEANS); scans: (query, data
+                               point) pairs the main scan evaluated */
+  double scan_ms;           /* device time of the main scan kernel (where tiles are left out, of
+                               everything from the grouping of the queries to the candidate
+                               extraction; HIP events on the call's stream) */
   double total_ms;          /* device time from the first to the last kernel of the call */
   int64_t slow_tiles;       /* 16-bit scans: (32-query group, tile) items recomputed for candidates */
   int64_t boxes;            /* DD_ANN: tree boxes tested; DD_KMEANS: child balls tested */
@@ -147,12 +155,14 @@ typedef struct dd_project_stats {
 
 typedef struct dd_project_opts {
   int32_t mode;             /* dd_mode; default DD_EXACT_FP64 */
-  int32_t splits;           /* data splits per query block; 0 = automatic */
+  int32_t splits;           /* data splits per query block; 0 = automatic (no effect on a scan
+                               that leaves out tiles) */
   int32_t ann_budget;       /* DD_ANN, DD_KMEANS: max leaves visited per query;
                                0 = unlimited (exact) */
   int32_t passes;           /* 16-bit modes: 1 = marking pass only, 2 = a bound-seeding pass over
                                every 64th tile first; 0 = automatic (2 without a warm start);
-                               any other value is DD_ERR_ARG */
+                               any other value is DD_ERR_ARG (no effect on a scan that leaves
+                               out tiles, whose bounds come from one near tile per query) */
   dd_project_stats* stats;  /* optional host pointer; filling it synchronises the stream */
   double ann_radius_discount;  /* DD_KMEANS: 1 - f_d in [0, 1], the part of a child's radius
                                   the ball test |q - c| - f_d r leaves out (Section 4.2):

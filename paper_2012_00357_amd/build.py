@@ -41,7 +41,7 @@ FINITE_FLAGS = ["-fno-honor-nans", "-mno-amdgpu-ieee"]
 MFMA_FLAGS = FINITE_FLAGS + ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 # The tree walks: the same for their box and ball bounds (queries with
 # non-finite coordinates leave the walk before any arithmetic).
-FINITE_SOURCES = ("ann.hip",)
+FINITE_SOURCES = ("ann.hip", "cull.hip")
 
 
 def _compile(src: str) -> str:

@@ -67,7 +67,7 @@ struct AnnArgs {
   const uint32_t* perm;
   const uint32_t* iperm;
   int64_t N;
-  const float* yq;         // [m][12] queries on the principal axes (rotate_queries_kernel)
+  const float* yq;         // [m][12] queries on the principal axes (prep_kernel)
   float xmax;
   int budget;
   QueryList L;
@@ -663,20 +663,6 @@ __global__ __launch_bounds__(256, 6) void ann_walk_kernel(AnnArgs A) {
   }
 }
 
-// Queries on the principal axes of the trees: yq[q][a] = sum_k V[k][a] q[k]
-// (FP64, rounded to FP32), one thread per (query, axis).
-__global__ void rotate_queries_kernel(const double* __restrict__ qw, int64_t m,
-                                      const double* __restrict__ V, float* __restrict__ yq) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 12 * m) return;
-  const int64_t q = i / 12;
-  const int a = (int)(i - 12 * q);
-  double y = 0.0;
-#pragma unroll
-  for (int k = 0; k < 12; ++k) y = fma(V[12 * k + a], qw[12 * q + k], y);
-  yq[i] = (float)y;
-}
-
 }  // namespace
 
 dd_status launch_ann_walk(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t len_max,
@@ -714,13 +700,7 @@ dd_status launch_ann_walk(const Dataset& D, const QueryPrep& Q, QueryList L, int
   A.perm = D.perm.as<uint32_t>();
   A.iperm = D.iperm.as<uint32_t>();
   A.N = D.N;
-  // the walk runs over all states of the call (the identity list), whose
-  // rotated coordinates are formed first
-  if (L.list || !Q.yq || !D.vrot.p)
-    return set_error(DD_ERR_ARG, "walk: identity query list and room for the rotated queries");
-  hipLaunchKernelGGL(rotate_queries_kernel, dim3((unsigned)((12 * L.m + 255) / 256)), dim3(256), 0,
-                     st, Q.qw, L.m, D.vrot.as<double>(), Q.yq);
-  DD_HIP(hipGetLastError());
+  if (!Q.yq) return set_error(DD_ERR_ARG, "walk: the queries' coordinates on the principal axes");
   A.yq = Q.yq;
   A.xmax = __builtin_nextafterf((float)D.xmax, INFINITY);
   A.budget = budget;

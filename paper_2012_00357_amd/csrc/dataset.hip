@@ -608,9 +608,10 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
       D.hi[a] = hi;
     }
     std::memcpy(D.mean, P.mean, sizeof(D.mean));
+    choose_group_cells(D);
   }
   // cell resolution: 2^bits cells per axis, 6 axes -> 6*bits key bits
-  const int bits = 5;
+  const int bits = kKeyBits;
   P.bits = bits;
   for (int a = 0; a < kKeyAxes; ++a) P.scale[a] *= (double)(1 << bits);
   dsamp.release();
@@ -630,6 +631,7 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     }
     DD_TRY(iota_u32(D.perm.as<uint32_t>(), N, st));
     DD_TRY(radix_sort_pairs(keys.as<uint32_t>(), D.perm.as<uint32_t>(), N, kKeyAxes * bits, st));
+    DD_TRY(build_tile_keys(keys.as<uint32_t>(), N, kTile64, D.tkey, st));
   }
   DD_TRY(D.iperm.alloc(sizeof(uint32_t) * (size_t)N));
   hipLaunchKernelGGL(invert_perm_kernel, dim3(grid_for(N)), dim3(256), 0, st,
@@ -668,9 +670,13 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     DD_HIP(hipGetLastError());
   }
 
+  // boxes of the scans' tiles
+  DD_TRY(build_tile_boxes(D, kTile64, nullptr, D.boxes, st));
+
   // 5. tile-centred 16-bit packs, from the sorted FP64 pack
   if (packs & (DD_PACK_BF16 | DD_PACK_FP16)) {
     D.n_tiles = (N + tile - 1) / tile;
+    DD_TRY(build_tile_boxes(D, tile, &D.boxes, D.boxes16, st));
     int64_t rows = D.n_tiles * tile;
     DD_TRY(D.centre.alloc(sizeof(float) * 12 * (size_t)D.n_tiles));
     DD_TRY(D.radius.alloc(sizeof(float) * (size_t)D.n_tiles));

@@ -70,6 +70,7 @@ void sym_eigen(int n, const double* A, double* evals, double* V);
 // ---------------------------------------------------------------------------
 constexpr int kDim = 12;           // phase-space dimension 2M (M = 6 Voigt components)
 constexpr int kKeyAxes = 6;        // principal axes used for the spatial order
+constexpr int kKeyBits = 5;        // bits per axis of its sort keys
 constexpr int kAnnLeaf = 64;       // points per ANN leaf (one wavefront)
 constexpr int kAnnFan = 64;        // children per ANN tree node (one wavefront)
 constexpr int kCounterSlots = 32;  // ANN walk statistics: slots, each on its own 128-byte line
@@ -113,6 +114,26 @@ constexpr size_t kArenaKeepBytes = (size_t)1 << 30;  // largest block an arena k
 constexpr int kArenaKeep = 8;                         // idle arenas kept per dataset
 constexpr int kArenaPinnedWords = 64;
 
+// Boxes of the scans' tiles (csrc/cull.hip): per tile of `rows` consecutive rows
+// of the sorted packs and per chunk of 64 tiles, float lo[12], hi[12] in
+// principal-axis coordinates y = V^T x, rounded outward.
+struct TileBoxes {
+  DevBuf tile, chunk, root;   // root: the box of all points
+  int64_t n_tiles = 0;
+  int rows = 0;
+  size_t bytes() const { return tile.bytes + chunk.bytes + root.bytes; }
+};
+
+// Cells by which a batch's queries are grouped: bit b of the cell index on axis
+// a goes to bit (target[a] >> 4 b) & 15 of the key.
+constexpr int kGroupKeyBits = 15;
+struct GroupCells {
+  float lo[kKeyAxes];
+  float scale[kKeyAxes];    // cells per unit length
+  int bits[kKeyAxes];
+  uint64_t target[kKeyAxes];
+};
+
 struct Dataset {
   int device = 0;
   int64_t N = 0;
@@ -148,6 +169,10 @@ struct Dataset {
   DevBuf vrot;     // double [144]: V on the device (the walks rotate their queries with it)
   double mean[kDim];
   double lo[kKeyAxes], hi[kKeyAxes];
+  GroupCells cells{};
+  TileBoxes boxes;     // tiles of the FP64 and FP32 scans (kTile64 rows)
+  TileBoxes boxes16;   // tiles of the 16-bit scans (tile rows)
+  DevBuf tkey;         // uint32 [boxes.n_tiles]: sort key of each tile's first row
   // ANN box tree over the sorted order: level 0 boxes bound leaves of kAnnLeaf
   // consecutive points, level k+1 boxes bound kAnnFan boxes of level k; boxes
   // are float lo[12], hi[12] in principal-axis coordinates y = V^T x, rounded
@@ -191,6 +216,16 @@ struct Dataset {
 
   int64_t device_bytes() const;
 };
+
+// Boxes of tiles of `rows` rows, as unions of the boxes of `from` where its rows
+// divide them, else from the FP64 pack.
+dd_status build_tile_boxes(const Dataset& D, int rows, const TileBoxes* from, TileBoxes& B,
+                           hipStream_t st);
+// Sort key of the first row of every tile of `rows` rows.
+dd_status build_tile_keys(const uint32_t* sorted_keys, int64_t N, int rows, DevBuf& tkey,
+                          hipStream_t st);
+// D.cells from the extent of the data on the principal axes.
+void choose_group_cells(Dataset& D);
 
 // Builds the k-means tree of DD_PACK_KMEANS over D's sorted FP64 pack.
 dd_status build_kmeans_tree(Dataset& D, hipStream_t st);

@@ -152,6 +152,8 @@ extern "C" dd_status dd_project_noalloc(const dd_dataset* ds, const double* stat
       !c.get(Q.u32, (size_t)m) || !c.get(Q.invalid, (size_t)m) || !c.get(counters, kNumCounters) ||
       !c.get(fb1, (size_t)m) || !c.get(fb2, (size_t)m))
     return set_error(DD_ERR_TOO_LARGE, "dd_project_noalloc: scratch too small");
+  if (mode != DD_EXACT_FP64 && !c.get(Q.yq, (size_t)m * 12))
+    return set_error(DD_ERR_TOO_LARGE, "dd_project_noalloc: scratch too small");
   hipLaunchKernelGGL(zero_words_kernel, dim3((kNumCounters + 255) / 256), dim3(256), 0, st, counters,
                      kNumCounters);
   DD_HIP(hipGetLastError());
@@ -160,8 +162,6 @@ extern "C" dd_status dd_project_noalloc(const dd_dataset* ds, const double* stat
   const QueryList all{nullptr, nullptr, m};
   if (mode == DD_EXACT_FP64)
     return exact_from_scratch(D, Q, all, m, out, c, fb2, counters + 1, st);
-  if (!c.get(Q.yq, (size_t)m * 12))
-    return set_error(DD_ERR_TOO_LARGE, "dd_project_noalloc: scratch too small");
   unsigned long long* walk_stats = reinterpret_cast<unsigned long long*>(counters + 32);
   DD_TRY(launch_ann_walk(D, Q, all, m, warm_start_idx_dev, budget, out, fb1, counters, walk_stats,
                          nullptr, st, mode == DD_KMEANS, 1.0 - discount));

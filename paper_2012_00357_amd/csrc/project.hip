@@ -196,6 +196,62 @@ dd_status direct_from(const Dataset& D, const QueryPrep& Q, QueryList L2, int64_
   return run_direct(D, Q, L2, h, S, out, st, pd, po);
 }
 
+// Largest mask array of a culled scan; a batch that needs more is scanned in
+// runs of queries.
+constexpr size_t kMaskBytes = (size_t)256 << 20;
+
+// Queries of one run (whole mask words) whose masks fit in `room` bytes.
+int64_t mask_run(int64_t n_tiles, int64_t m, int sub, size_t room) {
+  const size_t word = (size_t)n_tiles * 8;   // of mask and left
+  const int64_t words = (int64_t)(std::min(room, kMaskBytes) / word);
+  return std::min<int64_t>(std::min<int64_t>(m, kMaskQueries),
+                           std::max<int64_t>(words, 1) * 32 * sub);
+}
+size_t mask_bytes(int64_t n_tiles, int64_t run, int sub) {
+  return aligned((size_t)n_tiles * 8 * mask_words(run, sub) + 16) +
+         aligned((size_t)n_tiles * kMaskParts * sizeof(uint2));
+}
+dd_status alloc_masks(Scratch& sc, int64_t n_tiles, int64_t run, int sub, TileMasks& M) {
+  const size_t masks = 2 * (size_t)n_tiles * mask_words(run, sub);
+  uint32_t* z = nullptr;
+  DD_TRY(sc.get(z, masks + 4));
+  M.zero = z;
+  M.zero_bytes = ((masks + 4) * 4 + 15) & ~(size_t)15;   // pieces are 256-byte multiples
+  M.n_entry = z;
+  M.mask = z + 4;
+  M.left = M.mask + masks / 2;
+  DD_TRY(sc.get(M.entry, (size_t)n_tiles * kMaskParts));
+  M.sub = sub;
+  return DD_OK;
+}
+
+// The queries [p0, ...) of Q.
+QueryPrep query_run(const QueryPrep& Q, int64_t p0) {
+  QueryPrep R = Q;
+  R.qw = Q.qw + 12 * p0;
+  R.yq = Q.yq + 12 * p0;
+  R.qn2 = Q.qn2 + p0;
+  R.u64 = Q.u64 + p0;
+  R.u32 = Q.u32 + p0;
+  R.invalid = Q.invalid + p0;
+  if (Q.q16) R.q16 = Q.q16 + 16 * p0;
+  return R;
+}
+
+// Sorted copies of the queries (see launch_order).
+dd_status alloc_sorted(Scratch& sc, int64_t m, QueryPrep& R, int*& order) {
+  DD_TRY(sc.get(R.qw, (size_t)m * 12));
+  DD_TRY(sc.get(R.yq, (size_t)m * 12));
+  DD_TRY(sc.get(R.qn2, (size_t)m));
+  DD_TRY(sc.get(R.u64, (size_t)m));
+  DD_TRY(sc.get(R.u32, (size_t)m));
+  DD_TRY(sc.get(R.invalid, (size_t)m));
+  DD_TRY(sc.get(order, (size_t)m));
+  return DD_OK;
+}
+
+constexpr int kCulledK = 64;   // candidate list entries per query of the culled scans
+
 // FP64 MFMA scan over list L, merge, and the direct fallback for its overflow.
 dd_status exact64(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t len_max, int splits,
                   Outputs out, Scratch& sc, int* d_counters, hipStream_t st, int64_t* n_fallback,
@@ -234,6 +290,125 @@ dd_status exact64(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t len
   return DD_OK;
 }
 
+// Cells of the grouping order for a batch: about one query per cell.
+int group_key_bits(int64_t m) {
+  int b = 8;
+  while (b < kGroupKeyBits && ((int64_t)1 << b) < m) ++b;
+  return b;
+}
+// Scratch of a culled FP64 scan beside the prepared queries, with masks for one
+// word of queries at a time (the least it needs).
+size_t culled_bytes(const Dataset& D, int64_t m) {
+  const size_t n = (size_t)m;
+  return 2 * aligned(n * 12 * 4) + aligned(n * 2) + ((size_t)4 << group_key_bits(m)) +
+         aligned(n * 12 * 8) + 2 * aligned(n * 8) + 3 * aligned(n * 4) + aligned(n * 64) +   // sorted
+         2 * aligned(n * kCulledK * 4) + 2 * aligned(n * 4) + aligned(n * 8) + aligned(n * 4) +
+         mask_bytes(D.boxes.n_tiles, 1, 16) + exact64_bytes(m, 1) + 2 * kAlignSlack;
+}
+// Scratch of the prepared queries and the counters.
+size_t prepared_bytes(int64_t m) {
+  const size_t n = (size_t)m;
+  return aligned(n * 12 * 8) + 2 * aligned(n * 8) + 2 * aligned(n * 4) + (64 << 10) + kAlignSlack;
+}
+// Whether a scan of m queries is culled.  Culling costs about nine small launches
+// (50 us) and leaves few of the pairs of a large data set: at 2^23 points it
+// takes 0.11 to 0.83 ms for 8 to 4096 queries in FP64 against 1.2 to 24 ms for
+// the scan of every tile, and 0.11 to 0.43 against 0.32 to 1.5 ms in BF16.  The
+// line lies where both take the same time: at 2^18 points without a warm start
+// (BF16, 8 to 4096 queries: 101 to 166 against 110 to 205 us) and 2^19 with one,
+// which makes the full scan faster (10^6 points: 101 to 187 against 108 to 211
+// us; 2^18: 103 to 165 against 87 to 136 us).  Below that it is a large batch's
+// work that pays: FP64 from 2^27 pairs (2^16 points, 4096 queries: 178 against
+// 426 us; 512 queries: 112 against 111 us), 16 bits from 2^32.
+bool cull_pays(const Dataset& D, int mode, int64_t m, bool warm) {
+  if (D.boxes.n_tiles < 1 || mode == DD_DIRECT_FP64 || walk_mode(mode)) return false;
+  if (D.N >= (1 << 19) || (!warm && D.N >= (1 << 18))) return true;
+  const bool scan16 = mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16;
+  return scan16 ? D.N >= (1 << 18) && m * D.N >= ((int64_t)1 << 32)
+                : D.N >= (1 << 16) && m * D.N > ((int64_t)1 << 27);
+}
+
+// A culled scan in `mode` of m prepared queries (with their coordinates on the
+// principal axes): all of them, sorted by their cells, or those of list L in
+// its order; merge and FP64 rerank.  n_left: the queries the scan leaves (their
+// list overflowed, or the mode's scan does not take them), in fb / fb_count.
+dd_status culled_scan(const Dataset& D, int mode, const QueryPrep& Q, QueryList L, int64_t m,
+                      float u32_scale, Outputs out, Scratch& sc, int* d_counters, int* fb_count,
+                      hipStream_t st, int*& fb, int64_t& n_left, Timing* tm) {
+  QueryPrep R;
+  int* order = nullptr;
+  DD_TRY(alloc_sorted(sc, m, R, order));
+  CandBuf cb;
+  cb.S = cb.P = 1;
+  cb.K = kCulledK;
+  DD_TRY(sc.get(cb.lb, (size_t)m * cb.K));
+  DD_TRY(sc.get(cb.j, (size_t)m * cb.K));
+  DD_TRY(sc.get(cb.count, (size_t)m));
+  DD_TRY(sc.get(fb, (size_t)m));
+  DD_HIP(hipMemsetAsync(cb.count, 0, sizeof(int) * (size_t)m, st));
+  const bool scan16 = mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16;
+  if (scan16) DD_TRY(sc.get(R.q16, (size_t)m * 16));
+  const TileBoxes& B = scan16 ? D.boxes16 : D.boxes;
+  const int sub = mode == DD_EXACT_FP64 ? 16 : 32;
+  const size_t keep = kAlignSlack + mask_bytes(B.n_tiles, 0, sub) + exact64_bytes(m, 1);
+  const size_t room = sc.room() == SIZE_MAX ? SIZE_MAX : sc.room() > keep ? sc.room() - keep : 0;
+  const int64_t run = mask_run(B.n_tiles, m, sub, room);
+  TileMasks M;
+  DD_TRY(alloc_masks(sc, B.n_tiles, run, sub, M));
+  if (tm && tm->on) {
+    M.pairs = reinterpret_cast<unsigned long long*>(d_counters + 6);
+    M.items = reinterpret_cast<unsigned*>(d_counters + 4);
+  }
+  if (tm) DD_TRY(tm->mark(1, st));
+  const float s = scan16 ? D.sc16.s : 1.0f;
+  if (L.list)
+    DD_TRY(launch_gather(Q, L, m, s / u32_scale, R, order, st));
+  else
+    DD_TRY(launch_order(Q, m, scan16_reach(D, mode == DD_MIXED_FP16), R, order, st));
+  DD_TRY(launch_seed(D, R, m, (double)s, st));
+  for (int64_t p0 = 0; p0 < m; p0 += run) {
+    const int64_t n = std::min(run, m - p0);
+    const QueryPrep Rp = query_run(R, p0);
+    CandBuf cp = cb;
+    cp.lb = cb.lb + p0 * cb.K;
+    cp.j = cb.j + p0 * cb.K;
+    cp.count = cb.count + p0;
+    M.words = mask_words(n, sub);
+    DD_TRY(launch_cull(D, B, Rp, n, 1.0f / s, M, st));
+    if (mode == DD_EXACT_FP64)
+      DD_TRY(launch_scan64_culled(D, Rp, n, M, cp, st));
+    else if (mode == DD_MIXED_FP32)
+      DD_TRY(launch_scan32_culled(D, Rp, n, M, cp, st));
+    else
+      DD_TRY(launch_scan16_culled(D, mode == DD_MIXED_FP16, Rp, n, M, cp, st));
+  }
+  if (tm) DD_TRY(tm->mark(2, st));
+  unsigned long long* n_cand =
+      (tm && tm->on) ? reinterpret_cast<unsigned long long*>(d_counters + 2) : nullptr;
+  DD_TRY(launch_merge_rerank(D, Q, QueryList{order, nullptr, m}, m, cb, nullptr, out, fb, fb_count,
+                             n_cand, st));
+  uint32_t* hw = sc.host_word(1);
+  DD_HIP(hipMemcpyAsync(hw, fb_count, sizeof(int), hipMemcpyDeviceToHost, st));
+  DD_HIP(hipStreamSynchronize(st));
+  n_left = (int64_t)*hw;
+  return DD_OK;
+}
+
+// FP64 scan of list L (h queries, its length on the host): culled where the
+// queries' coordinates are at hand and it pays, else over all tiles; then the
+// direct scan of what it leaves.  u32_scale: the scale Q.u32 is in.
+dd_status fallback64(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t h, float u32_scale,
+                     Outputs out, Scratch& sc, int* d_counters, hipStream_t st) {
+  if (!Q.yq || sc.room() != SIZE_MAX || !cull_pays(D, DD_EXACT_FP64, h, false))
+    return exact64(D, Q, L, h, 0, out, sc, d_counters, st, nullptr, nullptr);
+  int* fb = nullptr;
+  int64_t left = 0;
+  DD_TRY(culled_scan(D, DD_EXACT_FP64, Q, L, h, u32_scale, out, sc, d_counters, d_counters + 1, st,
+                     fb, left, nullptr));
+  if (left == 0) return DD_OK;
+  return direct_from(D, Q, QueryList{fb, d_counters + 1, left}, left, 0, out, sc, st);
+}
+
 // FP32 MFMA scan over list L, merge and FP64 rerank; the queries whose lists
 // overflowed (or that the scan leaves out) go to the FP64 MFMA scan.
 dd_status mixed32(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t len_max, int splits,
@@ -266,7 +441,7 @@ dd_status mixed32(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t len
   if (n_fallback) *n_fallback += h;
   if (h > 0) {
     QueryList L1{fb, d_counters, h};
-    DD_TRY(exact64(D, Q, L1, h, 0, out, sc, d_counters, st, nullptr, nullptr));
+    DD_TRY(fallback64(D, Q, L1, h, 1.0f, out, sc, d_counters, st));
   }
   return DD_OK;
 }
@@ -393,8 +568,11 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
   DD_HIP(hipGetDevice(&cur_dev));
   if (cur_dev != D.device) return set_error(DD_ERR_ARG, "dataset lives on another device");
 
+  const bool scan = !walk_mode(mode) && mode != DD_DIRECT_FP64;
   Scratch sc(D, st, fixed);
   DD_TRY(sc.open());
+  const bool cull = cull_pays(D, mode, m, warm_start_idx_dev != nullptr) &&
+                    (!fixed || sc.room() > prepared_bytes(m) + culled_bytes(D, m));
   Timing timing;
   if (opts && opts->stats) DD_TRY(timing.init(st));
   QueryPrep Q;
@@ -403,13 +581,23 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
   DD_TRY(sc.get(Q.u64, (size_t)m));
   DD_TRY(sc.get(Q.u32, (size_t)m));
   DD_TRY(sc.get(Q.invalid, (size_t)m));
+  if (cull) {
+    DD_TRY(sc.get(Q.yq, (size_t)m * 12));
+    DD_TRY(sc.get(Q.key, (size_t)m));
+    Q.key_bits = group_key_bits(m);
+  } else if (walk_mode(mode)) {
+    DD_TRY(sc.get(Q.yq, (size_t)m * 12));
+  }
   // [0] fb1, [1] fb2, [2..3] candidates (u64), [4..5] slow tiles (u64),
+  // [6..7] (query, point) pairs of a culled scan (u64),
   // [32..) ANN walk statistics (kCounterSlots slots of kCounterStride u64, each
   // slot on its own 128-byte line)
   constexpr int kNumCounters = 32 + 2 * kCounterStride * kCounterSlots;
+  const int n_zero = kNumCounters + (cull ? 1 << Q.key_bits : 0);   // counters, then the key histogram
   int* counters = nullptr;
-  DD_TRY(sc.get(counters, kNumCounters));
-  DD_HIP(hipMemsetAsync(counters, 0, kNumCounters * sizeof(int), st));
+  DD_TRY(sc.get(counters, n_zero));
+  DD_HIP(hipMemsetAsync(counters, 0, n_zero * sizeof(int), st));
+  if (cull) Q.hist = reinterpret_cast<unsigned*>(counters + kNumCounters);
   const bool scan16 = (mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16);
   DD_TRY(prepare_queries(D, states_dev, whitened, m, warm_start_idx_dev,
                          scan16 ? (double)D.sc16.s : 1.0, Q, st));
@@ -423,6 +611,21 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
     DD_TRY(timing.mark(1, st));
     DD_TRY(direct_from(D, Q, all, m, splits, out, sc, st));
     DD_TRY(timing.mark(2, st));
+  } else if (cull) {
+    int* fb = nullptr;
+    int64_t left = 0;
+    const float s = scan16 ? D.sc16.s : 1.0f;
+    int* fb_count = counters + (mode == DD_EXACT_FP64 ? 1 : 0);
+    DD_TRY(culled_scan(D, mode, Q, all, m, s, out, sc, counters, fb_count, st, fb, left, &timing));
+    n_fallback += left;
+    if (scan16) n_items_host = -1;   // read with the statistics
+    if (left > 0) {
+      const QueryList L1{fb, fb_count, left};
+      if (mode == DD_EXACT_FP64)
+        DD_TRY(direct_from(D, Q, L1, left, 0, out, sc, st));
+      else
+        DD_TRY(fallback64(D, Q, L1, left, s, out, sc, counters, st));
+    }
   } else if (mode == DD_EXACT_FP64) {
     DD_TRY(exact64(D, Q, all, m, splits, out, sc, counters, st, &n_fallback, &timing));
   } else if (mode == DD_MIXED_FP32) {
@@ -430,7 +633,6 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
   } else if (walk_mode(mode)) {
     int* fb = nullptr;
     DD_TRY(sc.get(fb, (size_t)m));
-    DD_TRY(sc.get(Q.yq, (size_t)m * 12));
     ann = reinterpret_cast<unsigned long long*>(counters + 32);
     DD_TRY(timing.mark(1, st));
     if (dist2_out_dev && (budget != 0 || fd < 1.0))
@@ -445,7 +647,7 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
     n_fallback += h;
     if (h > 0) {
       QueryList L1{fb, counters, h};
-      DD_TRY(exact64(D, Q, L1, h, 0, out, sc, counters, st, nullptr, nullptr));
+      DD_TRY(fallback64(D, Q, L1, h, 1.0f, out, sc, counters, st));
     }
   } else {
     const bool fp16 = (mode == DD_MIXED_FP16);
@@ -526,7 +728,7 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
     n_fallback += h;
     if (h > 0) {
       QueryList L1{fb, counters, h};
-      DD_TRY(exact64(D, Q, L1, h, 0, out, sc, counters, st, nullptr, nullptr));
+      DD_TRY(fallback64(D, Q, L1, h, D.sc16.s, out, sc, counters, st));
     }
   }
   if (opts && opts->stats) {
@@ -534,6 +736,8 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
     unsigned long long slots[kCounterStride * kCounterSlots] = {};
     unsigned long long a[6] = {0, 0, 0, 0, 0, 0};
     unsigned items = 0;
+    unsigned long long pairs = 0;
+    if (cull) DD_HIP(hipMemcpyAsync(&pairs, counters + 6, sizeof(pairs), hipMemcpyDeviceToHost, st));
     DD_HIP(hipMemcpyAsync(&nc, counters + 2, sizeof(nc), hipMemcpyDeviceToHost, st));
     if (n_items_host < 0)
       DD_HIP(hipMemcpyAsync(&items, counters + 4, sizeof(items), hipMemcpyDeviceToHost, st));
@@ -548,7 +752,7 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
     DD_HIP(hipEventElapsedTime(&total_ms, timing.ev[0], timing.ev[3]));
     opts->stats->candidates = (int64_t)nc;
     opts->stats->overflowed = n_fallback;
-    opts->stats->visited = (int64_t)a[0];
+    opts->stats->visited = scan ? (cull ? (int64_t)pairs : m * D.N) : (int64_t)a[0];
     opts->stats->boxes = (int64_t)a[1];
     opts->stats->leaves = (int64_t)a[2];
     opts->stats->leaf_boxes = (int64_t)a[4];

@@ -57,15 +57,33 @@ struct Mats {
   double G[36];
 };
 
-__global__ void prep_kernel(const double* __restrict__ states, int64_t m, Mats M,
+// Cell of a query of the grouping order (top key_bits bits).
+__device__ inline int group_key(const GroupCells& g, const float (&y)[12], int key_bits) {
+  unsigned key = 0;
+#pragma unroll
+  for (int a = 0; a < kKeyAxes; ++a) {
+    const int top = (1 << g.bits[a]) - 1;
+    const float c = floorf((y[a] - g.lo[a]) * g.scale[a]);
+    const int cell = c >= (float)top ? top : (c > 0.0f ? (int)c : 0);   // NaN: 0
+    for (int b = 0; b < g.bits[a]; ++b)
+      key |= ((unsigned)(cell >> b) & 1u) << ((g.target[a] >> (4 * b)) & 15u);
+  }
+  return (int)(key >> (kGroupKeyBits - key_bits));
+}
+
+__global__ __launch_bounds__(256) void prep_kernel(
+                            const double* __restrict__ states, int64_t m, Mats M,
                             const int64_t* __restrict__ warm, int64_t N,
                             const uint32_t* __restrict__ iperm, const double* __restrict__ w64,
                             const float* __restrict__ w32, double u32_scale,
                             double* __restrict__ qw, double* __restrict__ qn2,
                             double* __restrict__ u64, float* __restrict__ u32,
-                            int* __restrict__ invalid) {
+                            int* __restrict__ invalid, const double* __restrict__ V,
+                            float* __restrict__ yq, GroupCells cells, int key_bits,
+                            uint16_t* __restrict__ key, unsigned* __restrict__ hist) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
+  const bool in = i < m;
+  if (!in) i = m - 1;   // the last block's spare threads repeat the last query
   double y[12];
   bool ok = true;
   for (int k = 0; k < 12; ++k) {
@@ -108,6 +126,21 @@ __global__ void prep_kernel(const double* __restrict__ states, int64_t m, Mats M
   }
   u64[i] = ub;
   u32[i] = ub32;
+  if (!yq) return;
+  // the query on the principal axes of the boxes and trees (FP64, rounded to FP32)
+  float ya[12];
+#pragma unroll
+  for (int a = 0; a < 12; ++a) {
+    double r = 0.0;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) r = fma(V[12 * k + a], q[k], r);
+    ya[a] = (float)r;
+    yq[12 * i + a] = ya[a];
+  }
+  if (!key) return;
+  const int gk = group_key(cells, ya, key_bits);
+  key[i] = (uint16_t)gk;
+  (void)cell_add(hist, in ? gk : -1);
 }
 
 dd_status prepare_queries(const Dataset& D, const double* states, bool whitened, int64_t m,
@@ -118,9 +151,12 @@ dd_status prepare_queries(const Dataset& D, const double* states, bool whitened,
     M.F[i] = whitened ? id : D.F[i];
     M.G[i] = whitened ? id : D.G[i];
   }
-  hipLaunchKernelGGL(prep_kernel, dim3(grid1(m)), dim3(256), 0, st, states, m, M, warm, D.N,
+  // small blocks: a query is a long chain of FP64 work, spread over the CUs
+  const int block = m < 65536 ? 64 : 256;
+  hipLaunchKernelGGL(prep_kernel, dim3(grid1(m, block)), dim3(block), 0, st, states, m, M, warm, D.N,
                      D.iperm.as<uint32_t>(), D.w64.as<double>(), D.w32.as<float>(), u32_scale,
-                     Q.qw, Q.qn2, Q.u64, Q.u32, Q.invalid);
+                     Q.qw, Q.qn2, Q.u64, Q.u32, Q.invalid, D.vrot.as<double>(), Q.yq, D.cells,
+                     Q.key_bits, Q.key, Q.hist);
   DD_HIP(hipGetLastError());
   return DD_OK;
 }
@@ -174,7 +210,7 @@ __global__ __launch_bounds__(256) void merge_rerank_thread_kernel(
     float Uf = INFINITY;
     if (Uq) {
       Uf = Uq[q];
-    } else {
+    } else if (cb.U) {
       for (int s = 0; s < S; ++s) Uf = fminf(Uf, cb.U[p * S + s]);
     }
     double qv[12];
@@ -243,7 +279,7 @@ __global__ __launch_bounds__(256) void merge_rerank_wave_kernel(
   float Uf = INFINITY;
   if (Uq) {
     Uf = Uq[q];
-  } else {
+  } else if (cb.U) {
     for (int s = lane; s < S; s += 64) Uf = fminf(Uf, cb.U[p * S + s]);
     for (int off = 32; off > 0; off >>= 1) Uf = fminf(Uf, __shfl_xor(Uf, off));
   }

@@ -228,6 +228,164 @@ dd_status launch_scan64(const Dataset& D, const QueryPrep& Q, QueryList L, int64
 }
 
 // ---------------------------------------------------------------------------
+// Culled scans (csrc/cull.hip): the listed tiles, each for the query groups of
+// its mask.  A workgroup takes one tile at a time through LDS and its
+// wavefronts take the groups in turn, so a tile is read once (blocks of 256
+// queries that walk the tiles they need read the data 7 times as often and took
+// 8.0 ms where this takes 3.5: FP64, N = 2^24, m = 32768, where a tile is wanted
+// by 20 groups of 16 queries; rows read straight to the operand registers took
+// 14.7 ms, bound by the cache accesses of their 96-byte strides).
+// Bound: the matrix core, as the full scans, on the pairs that are left.
+// Measured whole calls, full scan -> culled: FP64 N = 2^24, m = 32768 264 -> 5.2
+// ms (1.0 % of the pairs left); FP32 N = 10^7, m = 30011 98 -> 3.5 ms (2.4 %);
+// BF16 N = 2^27, m = 65536 243 -> 9.0 ms (1.3 %).
+// ---------------------------------------------------------------------------
+// Groups of a mask row to items[] (ids ascending); the entry's part of them is
+// [first, end).  THREADS >= words.
+template <int THREADS>
+__device__ inline void mask_items(const uint32_t* row, int words, uint32_t part, uint16_t* items,
+                                  int* wsum, int& first, int& end) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t w = t < words ? row[t] : 0u;
+  const int n = __popc(w);
+  int incl = n;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(incl, off);
+    if (lane >= off) incl += o;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  int at = incl - n, total = 0;
+#pragma unroll
+  for (int v = 0; v < THREADS / 64; ++v) {
+    if (v < wave) at += wsum[v];
+    total += wsum[v];
+  }
+  for (; w; w &= w - 1) items[at++] = (uint16_t)(32 * t + __builtin_ctz(w));
+  __syncthreads();
+  const int k = (int)(part & 0xFFFFu), parts = (int)(part >> 16);
+  first = total * k / parts;
+  end = total * (k + 1) / parts;
+}
+
+constexpr int kMaskGroups64 = (int)(kMaskQueries / 16);
+
+// FP64, groups of 16 queries.  !EXTRACT: the tile's minimum lowers the queries'
+// bounds (an atomic minimum on the bits of non-negative doubles), and `left`
+// gets the groups with a query whose tile minimum is within its bound as it
+// stands.  EXTRACT: these under the final bounds; every point whose lower bound is within the bound is
+// appended to its query's list.  Two passes, as a bound that still falls would
+// fill the lists with points that are not candidates in the end.
+template <bool EXTRACT>
+__global__ __launch_bounds__(256, 4) void scan64_culled_kernel(
+    const double* __restrict__ w64, const double* __restrict__ n64, int64_t N, int64_t m,
+    const double* __restrict__ qw, const double* __restrict__ qn2, double* u64,
+    const int* __restrict__ invalid, double xmax, TileMasks M, CandBuf cb) {
+  __shared__ __align__(16) double xs[kTile64 * 12];
+  __shared__ __align__(16) double ns[kTile64];
+  __shared__ uint16_t items[kMaskGroups64];
+  __shared__ int wsum[4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, kq = lane >> 4;
+  const unsigned n_entries = M.n_entry[EXTRACT ? 1 : 0];
+  unsigned visits = 0;
+  for (unsigned k = blockIdx.x; k < n_entries; k += gridDim.x) {
+    const uint2 e = M.entry[k];
+    const int64_t t = e.x;
+    tile_to_lds64(w64, n64, t, xs, ns, wave, lane);
+    int first, n;
+    mask_items<256>((EXTRACT ? M.left : M.mask) + t * M.words, M.words, e.y, items, wsum, first, n);
+    wait_copies();
+    __syncthreads();
+    // the group's operands are loaded ahead, while the group before is scored
+    double b[3], qn, U;
+    bool valid;
+    auto load = [&](int i) __attribute__((always_inline)) {
+      const int64_t p = 16 * (int64_t)items[i] + col;
+      valid = p < m && !invalid[p < m ? p : 0];
+      const int64_t q = valid ? p : 0;
+#pragma unroll
+      for (int s = 0; s < 3; ++s) b[s] = qw[12 * q + 4 * s + kq];
+      qn = qn2[q];
+      U = __hip_atomic_load(&u64[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (first + wave < n) load(first + wave);
+    for (int i = first + wave; i < n; i += 4) {
+      const int group = items[i];
+      const int64_t p = 16 * (int64_t)group + col;
+      const bool v = valid;
+      const double b0 = v ? -2.0 * b[0] : 0.0, b1 = v ? -2.0 * b[1] : 0.0, b2 = v ? -2.0 * b[2] : 0.0;
+      const double qq = v ? qn : 0.0, Uq = v ? U : (EXTRACT ? -INFINITY : INFINITY);
+      const double qa = sqrt(qq) + xmax;
+      const double alpha = 0x1p-48 * qa * qa + 1e-300;
+      if (i + 4 < n) load(i + 4);
+      double tm = INFINITY;
+#pragma unroll 4
+      for (int rb = 0; rb < kTile64 / 16; ++rb) {
+        const int r0 = rb * 16 + col;
+        f64x4_t acc;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = ns[rb * 16 + kq + 4 * j];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xs[12 * r0 + kq], b0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xs[12 * r0 + 4 + kq], b1, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xs[12 * r0 + 8 + kq], b2, acc, 0, 0, 0);
+        const double mn = fmin(fmin(acc[0], acc[1]), fmin(acc[2], acc[3]));
+        if (!EXTRACT) {
+          tm = fmin(tm, mn);
+        } else if (__any((mn + qq) - alpha <= Uq)) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int64_t x = t * kTile64 + rb * 16 + kq + 4 * j;
+            const double lb = (acc[j] + qq) - alpha;
+            if (v && x < N && lb <= Uq) {
+              const int at = atomicAdd(&cb.count[p], 1);
+              if (at < cb.K) {
+                cb.lb[p * cb.K + at] = f32_down(lb);
+                cb.j[p * cb.K + at] = (uint32_t)x;
+              }
+            }
+          }
+        }
+      }
+      if (!EXTRACT) {
+        tm = fmin(tm, __shfl_xor(tm, 16));
+        tm = fmin(tm, __shfl_xor(tm, 32));
+        const double dmin = tm + qq;
+        const double Un = fmax(fmin(Uq, dmin + alpha), 0.0);   // an upper bound of a square
+        if (v && kq == 0 && Un < Uq)
+          atomicMin(reinterpret_cast<unsigned long long*>(&u64[p]),
+                    (unsigned long long)__double_as_longlong(Un));
+        if (__any(v && dmin - alpha <= Un) && lane == 0)
+          atomicOr(&M.left[t * M.words + (group >> 5)], 1u << (group & 31));
+      }
+      ++visits;
+    }
+    __syncthreads();   // the tile and the items are replaced next
+  }
+  if (lane == 0 && visits) {
+    if (!EXTRACT && M.pairs) atomicAdd(M.pairs, (unsigned long long)visits * (16u * kTile64));
+    if (EXTRACT && M.items) atomicAdd(M.items, visits);
+  }
+}
+
+dd_status launch_scan64_culled(const Dataset& D, const QueryPrep& Q, int64_t m, const TileMasks& M,
+                               const CandBuf& cb, hipStream_t st) {
+  if (m <= 0) return DD_OK;
+  if (m > kMaskQueries || M.sub != 16 || M.words != mask_words(m, 16) || cb.S != 1 || cb.P != 1)
+    return set_error(DD_ERR_ARG, "culled FP64 scan: mask or list shape");
+  const unsigned blocks = (unsigned)std::min<int64_t>(D.boxes.n_tiles * kMaskParts, 256 * 4);
+  DD_TRY(launch_plan(M, D.boxes.n_tiles, false, st));
+  hipLaunchKernelGGL(scan64_culled_kernel<false>, dim3(blocks), dim3(256), 0, st, D.w64.as<double>(),
+                     D.n64.as<double>(), D.N, m, Q.qw, Q.qn2, Q.u64, Q.invalid, D.xmax, M, cb);
+  DD_TRY(launch_plan(M, D.boxes.n_tiles, true, st));
+  hipLaunchKernelGGL(scan64_culled_kernel<true>, dim3(blocks), dim3(256), 0, st, D.w64.as<double>(),
+                     D.n64.as<double>(), D.N, m, Q.qw, Q.qn2, Q.u64, Q.invalid, D.xmax, M, cb);
+  DD_HIP(hipGetLastError());
+  return DD_OK;
+}
+
+// ---------------------------------------------------------------------------
 // FP32 MFMA scan.  v_mfma_f32_32x32x2_f32: A (32 data rows x 2 k): lane supplies
 // row lane%32, k = lane/32; B (2 k x 32 queries): lane supplies query lane%32,
 // k = lane/32; C and D: lane holds rows 8*(i/4) + 4*(lane/32) + i%4 (i < 16) of
@@ -405,6 +563,144 @@ __global__ __launch_bounds__(256, 3) void scan32_kernel(
   }
 }
 
+// The culled FP32 scan: as scan64_culled_kernel with groups of 32 queries; the
+// bounds are shared through u64 (FP32 values).
+constexpr int kMaskGroups32 = (int)(kMaskQueries / 32);
+
+template <bool EXTRACT>
+__global__ __launch_bounds__(256, 4) void scan32_culled_kernel(
+    const float* __restrict__ w32, const float* __restrict__ n32, int64_t N, int64_t m,
+    const double* __restrict__ qw, const double* __restrict__ qn2, double* u64,
+    const int* __restrict__ invalid, float xmax, TileMasks M, CandBuf cb) {
+  __shared__ float xs[6][2][kTile32];   // xs[s][h][row] = x^[row][2 s + h]
+  __shared__ __align__(16) float ns[kTile32];
+  __shared__ uint16_t items[kMaskGroups32];
+  __shared__ int wsum[4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, h = lane >> 5;
+  const unsigned n_entries = M.n_entry[EXTRACT ? 1 : 0];
+  unsigned visits = 0;
+  for (unsigned k = blockIdx.x; k < n_entries; k += gridDim.x) {
+    const uint2 e = M.entry[k];
+    const int64_t t = e.x;
+    {
+      const float4* src = reinterpret_cast<const float4*>(w32 + t * kTile32 * 12);
+      float4 reg[3];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) reg[v] = src[tid + 256 * v];
+      const float nreg = n32[t * kTile32 + tid];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        const int el = 4 * (tid + 256 * v), row = el / 12, c = el % 12;   // c in {0, 4, 8}
+        xs[c / 2][0][row] = reg[v].x;
+        xs[c / 2][1][row] = reg[v].y;
+        xs[c / 2 + 1][0][row] = reg[v].z;
+        xs[c / 2 + 1][1][row] = reg[v].w;
+      }
+      ns[tid] = nreg;
+    }
+    int first, n;
+    mask_items<256>((EXTRACT ? M.left : M.mask) + t * M.words, M.words, e.y, items, wsum, first, n);
+    // (mask_items ends with a barrier after the tile's stores)
+    double qv[6], qn, Ud;
+    bool valid;
+    auto load = [&](int i) __attribute__((always_inline)) {
+      const int64_t p = 32 * (int64_t)items[i] + col;
+      valid = p < m && !invalid[p < m ? p : 0];
+      const int64_t q = valid ? p : 0;
+#pragma unroll
+      for (int s = 0; s < 6; ++s) qv[s] = qw[12 * q + 2 * s + h];
+      qn = qn2[q];
+      Ud = __hip_atomic_load(&u64[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (first + wave < n) load(first + wave);
+    for (int i = first + wave; i < n; i += 4) {
+      const int group = items[i];
+      const int64_t p = 32 * (int64_t)group + col;
+      const float qa = valid ? (float)sqrt(qn) + xmax : 0.0f;
+      const bool v = valid && qa < 0x1p60f;
+      float b[6];
+      double part = 0.0;
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const double qk = v ? (double)(float)qv[s] : 0.0;   // q^ = fl32(q)
+        b[s] = (float)(-2.0 * qk);
+        part = fma(qk, qk, part);
+      }
+      const float o = (float)(part + __shfl_xor(part, 32));
+      const float a = 0x1p-18f * qa * qa + 1e-30f;
+      const float Uq = v ? f32_up(Ud) : (EXTRACT ? -INFINITY : INFINITY);
+      if (i + 4 < n) load(i + 4);
+      float tm = INFINITY;
+#pragma unroll 2
+      for (int rb = 0; rb < kTile32 / 32; ++rb) {
+        f32x16_t acc;
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const float4 v4 = *reinterpret_cast<const float4*>(&ns[rb * 32 + 8 * g4 + 4 * h]);
+          acc[4 * g4 + 0] = v4.x;
+          acc[4 * g4 + 1] = v4.y;
+          acc[4 * g4 + 2] = v4.z;
+          acc[4 * g4 + 3] = v4.w;
+        }
+#pragma unroll
+        for (int s = 0; s < 6; ++s) acc = mfma_f32(xs[s][h][rb * 32 + col], b[s], acc);
+        const float mn = min16(EXTRACT ? INFINITY : tm, acc);
+        if (!EXTRACT) {
+          tm = mn;
+        } else if (__any((mn + o) - a <= Uq)) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int64_t x = t * kTile32 + rb * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
+            const float lb = (acc[j] + o) - a;
+            if (v && x < N && lb <= Uq) {
+              const int at = atomicAdd(&cb.count[p], 1);
+              if (at < cb.K) {
+                cb.lb[p * cb.K + at] = lb;
+                cb.j[p * cb.K + at] = (uint32_t)x;
+              }
+            }
+          }
+        }
+      }
+      if (!EXTRACT) {
+        tm = fminf(tm, __shfl_xor(tm, 32));
+        const float dmin = tm + o;
+        const float Un = fmaxf(fminf(Uq, dmin + a), 0.0f);   // an upper bound of a square
+        if (v && h == 0 && Un < Uq)
+          atomicMin(reinterpret_cast<unsigned long long*>(&u64[p]),
+                    (unsigned long long)__double_as_longlong((double)Un));
+        if (__any(v && dmin - a <= Un) && lane == 0)
+          atomicOr(&M.left[t * M.words + (group >> 5)], 1u << (group & 31));
+      }
+      ++visits;
+    }
+    __syncthreads();   // the tile and the items are replaced next
+  }
+  if (lane == 0 && visits) {
+    if (!EXTRACT && M.pairs) atomicAdd(M.pairs, (unsigned long long)visits * (32u * kTile32));
+    if (EXTRACT && M.items) atomicAdd(M.items, visits);
+  }
+}
+
+dd_status launch_scan32_culled(const Dataset& D, const QueryPrep& Q, int64_t m, const TileMasks& M,
+                               const CandBuf& cb, hipStream_t st) {
+  if (m <= 0) return DD_OK;
+  static_assert(kTile32 == kTile64, "one set of tile boxes for both scans");
+  if (m > kMaskQueries || M.sub != 32 || M.words != mask_words(m, 32) || cb.S != 1 || cb.P != 1)
+    return set_error(DD_ERR_ARG, "culled FP32 scan: mask or list shape");
+  const unsigned blocks = (unsigned)std::min<int64_t>(D.boxes.n_tiles * kMaskParts, 256 * 4);
+  DD_TRY(launch_plan(M, D.boxes.n_tiles, false, st));
+  hipLaunchKernelGGL(scan32_culled_kernel<false>, dim3(blocks), dim3(256), 0, st, D.w32.as<float>(),
+                     D.n32.as<float>(), D.N, m, Q.qw, Q.qn2, Q.u64, Q.invalid, (float)D.xmax32, M, cb);
+  DD_TRY(launch_plan(M, D.boxes.n_tiles, true, st));
+  hipLaunchKernelGGL(scan32_culled_kernel<true>, dim3(blocks), dim3(256), 0, st, D.w32.as<float>(),
+                     D.n32.as<float>(), D.N, m, Q.qw, Q.qn2, Q.u64, Q.invalid, (float)D.xmax32, M, cb);
+  DD_HIP(hipGetLastError());
+  return DD_OK;
+}
+
 dd_status launch_scan32(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t list_len_max,
                         const CandBuf& cb, hipStream_t st) {
   if (list_len_max <= 0) return DD_OK;
@@ -518,6 +814,13 @@ __device__ inline bool near16(const double* __restrict__ qw, int64_t q, const Sc
     a = fmaf(t, t, a);
   }
   return sc.far > 0.0f && a < sc.far * sc.far;
+}
+
+Scale16 scan16_reach(const Dataset& D, bool fp16) {
+  Scale16 sc = D.sc16;
+  const double limit = fp16 ? kFarLimitFp16 : kFarLimitBf16;
+  sc.far = (float)std::max(0.0, limit - D.span16);
+  return sc;
 }
 
 __device__ inline void centre_select(const float* __restrict__ cp, int h, float (&cs)[8]) {
@@ -746,13 +1049,182 @@ __global__ __launch_bounds__(256) void scan16_extract_kernel(
   }
 }
 
+// The culled 16-bit scan (see scan64_culled_kernel): eight wavefronts per tile,
+// each taking two groups of 32 queries at a time against the tile's rows (the
+// row operands are read once for both), scores and bounds as in
+// scan16_pass_kernel.  The running bounds are shared through u32 (an atomic
+// minimum on the bits of non-negative floats).
+constexpr int kW16c = 8;
+
+template <class T16, int TILE, bool EXTRACT>
+__global__ __launch_bounds__(64 * kW16c, 4) void scan16_culled_kernel(
+    const uint4* __restrict__ wp, const float* __restrict__ centre, const float* __restrict__ radius,
+    int64_t N, int64_t m, const float* __restrict__ q16, float* u32, TileMasks M, CandBuf cb) {
+  typedef Vec16<T16> VT;
+  typedef typename VT::type vec_t;
+  constexpr int NB = TILE / 32, TH = 64 * kW16c;
+  __shared__ uint4 rows[2 * TILE];      // [half * TILE + row]
+  __shared__ uint16_t items[kMaskGroups32];
+  __shared__ int wsum[kW16c];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5, col = lane & 31;
+  const unsigned n_entries = M.n_entry[EXTRACT ? 1 : 0];
+  unsigned visits = 0;
+  for (unsigned k = blockIdx.x; k < n_entries; k += gridDim.x) {
+    const uint2 en = M.entry[k];
+    const int64_t t = en.x;
+    {
+      const uint4* src = wp + t * TILE * 2;
+#pragma unroll
+      for (int e = tid; e < 2 * TILE; e += TH) rows[(e & 1) * TILE + (e >> 1)] = src[e];
+    }
+    int first, n;
+    mask_items<TH>((EXTRACT ? M.left : M.mask) + t * M.words, M.words, en.y, items, wsum, first, n);
+    // (mask_items ends with a barrier after the tile's stores)
+    float cs[8];
+    centre_select(centre + 12 * t, h, cs);
+    const float rad = radius[t];
+    for (int i = first + 2 * wave; i < n; i += 2 * kW16c) {
+      const bool two = i + 1 < n;
+      float o[2], eta[2], alpha[2], Uq[2], T[2];
+      bool v[2];
+      int p[2];
+      vec_t B[2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        p[g] = 32 * (int)items[g && two ? i + 1 : i] + col;
+        const bool in = p[g] < m && (g == 0 || two);
+        const int q = in ? p[g] : 0;
+        // lanes of half h hold k = 8 h .. 8 h + 7: coordinates 0..11, then 1, 1, 1, 0
+        const float4* qc = reinterpret_cast<const float4*>(q16 + 16 * (int64_t)q);
+        const float4 c0 = qc[2 * h], c1 = qc[1 + 2 * h];   // (h: 8..11; |q|, flag)
+        const float2 extra = *reinterpret_cast<const float2*>(q16 + 16 * (int64_t)q + 12);
+        v[g] = in && extra.y != 0.0f;
+        float qf[8] = {c0.x, c0.y, c0.z, c0.w, h ? 1.0f : c1.x, h ? 1.0f : c1.y, h ? 1.0f : c1.z,
+                       h ? 0.0f : c1.w};
+        if (!v[g]) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) qf[c] = h && c >= 4 ? qf[c] : 0.0f;
+        }
+        const float qabs = v[g] ? extra.x : 0.0f;
+        Uq[g] = v[g] ? __hip_atomic_load(&u32[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                     : (EXTRACT ? -INFINITY : INFINITY);
+        tile_operands<T16>(qf, qabs, cs, rad, h, B[g], o[g], eta[g], alpha[g]);
+        // scores that can pass the lower-bound test (see scan16_extract_kernel)
+        const float a = (Uq[g] + eta[g]) * (1.0f + 0x1p-18f);
+        const float sa = a * a + alpha[g];
+        T[g] = v[g] ? (sa - o[g]) + 0x1p-18f * (sa + fabsf(o[g])) + 1e-30f : -INFINITY;
+      }
+      const f32x16_t zero = {};
+      const uint4* base = &rows[h * TILE + col];
+      float tm[2] = {INFINITY, INFINITY};
+      auto extract = [&](int g, int rb, const f32x16_t& acc) __attribute__((always_inline)) {
+        if (min16(INFINITY, acc) <= T[g]) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            if (acc[j] <= T[g]) {
+              const int64_t x = t * TILE + rb * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
+              const float lb = fsqrt(fmaxf(acc[j] + o[g] - alpha[g], 0.0f)) * kRelDn - eta[g];
+              if (x < N && lb <= Uq[g]) {
+                const int at = atomicAdd(&cb.count[p[g]], 1);
+                if (at < cb.K) {
+                  cb.lb[(int64_t)p[g] * cb.K + at] = lb;
+                  cb.j[(int64_t)p[g] * cb.K + at] = (uint32_t)x;
+                }
+              }
+            }
+          }
+        }
+      };
+      if (EXTRACT) {
+        for (int rb = 0; rb < NB; ++rb) {
+          const vec_t A = __builtin_bit_cast(vec_t, base[rb * 32]);
+          const f32x16_t a0 = VT::mfma(A, B[0], zero), a1 = VT::mfma(A, B[1], zero);
+          extract(0, rb, a0);
+          extract(1, rb, a1);
+        }
+      } else {
+        // four row blocks at a time (a rolled loop: unrolled, the row operands of
+        // the whole tile are hoisted out of the loop over the groups and spill);
+        // MFMA x = (row block x / 2, group x % 2), each reduction two MFMAs
+        // behind its producer
+#pragma unroll 1
+        for (int rb0 = 0; rb0 < NB; rb0 += 4) {
+          vec_t A[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) A[u] = __builtin_bit_cast(vec_t, base[(rb0 + u) * 32]);
+          f32x16_t acc[3];
+#pragma unroll
+          for (int x = 0; x < 10; ++x) {
+            if (x < 8) acc[x % 3] = VT::mfma(A[x >> 1], B[x & 1], zero);
+            if (x >= 2) tm[x & 1] = min16(tm[x & 1], acc[(x - 2) % 3]);
+          }
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          const float dmin = fminf(tm[g], __shfl_xor(tm[g], 32)) + o[g];
+          const float Un = fminf(Uq[g], (fsqrt(dmin + alpha[g]) + eta[g]) * kRelUp);
+          if (v[g] && h == 0 && Un < Uq[g])
+            atomicMin(reinterpret_cast<unsigned*>(&u32[p[g]]), __float_as_uint(Un));
+          const float lbmin = fsqrt(fmaxf(dmin - alpha[g], 0.0f)) * kRelDn - eta[g];
+          const int group = p[g] >> 5;   // the same in every lane
+          if (__any(v[g] && lbmin <= Un) && lane == 0)
+            atomicOr(&M.left[t * M.words + (group >> 5)], 1u << (group & 31));
+        }
+      }
+      visits += two ? 2 : 1;
+    }
+    __syncthreads();   // the tile and the items are replaced next
+  }
+  if (lane == 0 && visits) {
+    if (!EXTRACT && M.pairs) atomicAdd(M.pairs, (unsigned long long)visits * (32u * TILE));
+    if (EXTRACT && M.items) atomicAdd(M.items, visits);
+  }
+}
+
+template <class T16, int TILE>
+static dd_status launch16c(const Dataset& D, const uint16_t* pack, const QueryPrep& Q, int64_t m,
+                           const TileMasks& M, const CandBuf& cb, hipStream_t st) {
+  const uint4* wp = reinterpret_cast<const uint4*>(pack);
+  const unsigned blocks = (unsigned)std::min<int64_t>(D.n_tiles * kMaskParts, 256 * 2);
+  DD_TRY(launch_plan(M, D.n_tiles, false, st));
+  hipLaunchKernelGGL((scan16_culled_kernel<T16, TILE, false>), dim3(blocks), dim3(64 * kW16c), 0, st,
+                     wp, D.centre.as<float>(), D.radius.as<float>(), D.N, m, Q.q16, Q.u32, M, cb);
+  DD_TRY(launch_plan(M, D.n_tiles, true, st));
+  hipLaunchKernelGGL((scan16_culled_kernel<T16, TILE, true>), dim3(blocks), dim3(64 * kW16c), 0, st,
+                     wp, D.centre.as<float>(), D.radius.as<float>(), D.N, m, Q.q16, Q.u32, M, cb);
+  DD_HIP(hipGetLastError());
+  return DD_OK;
+}
+
+template <class T16>
+static dd_status launch16c_tile(const Dataset& D, const uint16_t* pack, const QueryPrep& Q, int64_t m,
+                                const TileMasks& M, const CandBuf& cb, hipStream_t st) {
+  switch (D.tile) {
+    case 128: return launch16c<T16, 128>(D, pack, Q, m, M, cb, st);
+    case 256: return launch16c<T16, 256>(D, pack, Q, m, M, cb, st);
+    case 512: return launch16c<T16, 512>(D, pack, Q, m, M, cb, st);
+    case 1024: return launch16c<T16, 1024>(D, pack, Q, m, M, cb, st);
+    default: return launch16c<T16, 2048>(D, pack, Q, m, M, cb, st);
+  }
+}
+
+dd_status launch_scan16_culled(const Dataset& D, bool fp16, const QueryPrep& Q, int64_t m,
+                               const TileMasks& M, const CandBuf& cb, hipStream_t st) {
+  if (m <= 0) return DD_OK;
+  if (m > kMaskQueries || M.sub != 32 || M.words != mask_words(m, 32) || cb.S != 1 || cb.P != 1 ||
+      !Q.q16)
+    return set_error(DD_ERR_ARG, "culled 16-bit scan: mask or list shape");
+  if (fp16) return launch16c_tile<Fp16>(D, D.wfp16.as<uint16_t>(), Q, m, M, cb, st);
+  return launch16c_tile<Bf16>(D, D.wbf16.as<uint16_t>(), Q, m, M, cb, st);
+}
+
 template <class T16, int TILE>
 static dd_status launch16(const Dataset& D, const uint16_t* pack, const Scan16Call& c, hipStream_t st) {
   const uint4* wp = reinterpret_cast<const uint4*>(pack);
   const int64_t qblocks = (c.list_len_max + kQ16 - 1) / kQ16;
-  Scale16 sc = D.sc16;
-  const double limit = T16::kUnit < 0.001f ? kFarLimitFp16 : kFarLimitBf16;
-  sc.far = (float)std::max(0.0, limit - D.span16);
+  const Scale16 sc = scan16_reach(D, T16::kUnit < 0.001f);
   if (c.phase == Scan16Call::kExtract) {
     const unsigned waves = c.item_cap;   // grid sized for the capacity; extra waves exit
     const unsigned blocks = (unsigned)(((uint64_t)waves * 64 + 255) / 256);
