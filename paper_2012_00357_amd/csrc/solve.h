@@ -30,10 +30,11 @@ dd_status project_whitened(const Dataset& D, const double* qw_dev, int64_t m,
                            double fd = 1.0, int passes = 0, const float* fd_q = nullptr,
                            const int* budget_q = nullptr);
 
-// K^-1 for the mesh and Dirichlet pattern, formed on st from the CSR matrix on
-// first use and cached on the dataset.
+// Element stiffness Ke = w sum_g B_g^T C B_g (24 x 24).
+void element_stiffness(const FEMesh& M, const double* C, double* Ke);
+// K^-1 for the mesh and Dirichlet pattern, formed on st on first use and cached
+// on the dataset.
 dd_status dense_inverse_for(const Dataset& ds, const FEMesh& M, const uint8_t* mask,
-                            const int32_t* rowptr, const int32_t* col, const double* val,
                             std::shared_ptr<DenseInverse>& out, hipStream_t st);
 // The cached K^-1 for the mesh and Dirichlet pattern, or null.
 std::shared_ptr<DenseInverse> dense_inverse_cached(const Dataset& ds, const FEMesh& M,

@@ -6,7 +6,8 @@
 // (eqs. "KuE", "KeS") needs C eps* = L w_eps* and sig* = L w_sig*, and returns
 // eps = B u, sig = sig* + C B eta, i.e. w_eps = L^T B u, w_sig = w_sig* + L^T B eta.
 //
-// K = A_e{ w B^T C B } is assembled once (host, CSR over all DOFs with identity
+// K = A_e{ w B^T C B } is assembled once (for conjugate gradients on the host, CSR
+// over all DOFs with identity
 // rows at Dirichlet DOFs) and both systems K u = E, K eta = S are solved
 // together by a Jacobi-preconditioned conjugate-gradient kernel running in one
 // workgroup, warm-started from the previous iterate.  All reductions run in a
@@ -70,7 +71,7 @@ int64_t FEMesh::node(int i, int j, int k) const {
 }
 
 // Element stiffness Ke = w sum_g B_g^T C B_g (24 x 24).
-static void element_stiffness(const FEMesh& M, const double* C, double* Ke) {
+void element_stiffness(const FEMesh& M, const double* C, double* Ke) {
   std::fill(Ke, Ke + 24 * 24, 0.0);
   for (int g = 0; g < 8; ++g) {
     const double* B = M.B[g];
@@ -707,8 +708,7 @@ dd_status DDSolver::setup(const Dataset& D, const dd_mesh& mesh, const uint8_t* 
   const int64_t nd = M.n_dof, nm = M.n_mp;
   const bool want_dense = nd <= kDenseMaxDof && !(opts && (opts->flags & DD_SOLVE_CG));
   if (want_dense) dense = dense_inverse_cached(D, M, mask);
-  // the CSR matrix is needed by CG, or once to form K^-1
-  const bool need_csr = !dense;
+  const bool need_csr = !want_dense;   // the CSR matrix is CG's
   std::vector<int32_t> rowptr, col;
   std::vector<double> val, dinv;
   if (need_csr) assemble_csr(M, D.C, mask, rowptr, col, val, dinv);
@@ -816,8 +816,7 @@ dd_status DDSolver::setup(const Dataset& D, const dd_mesh& mesh, const uint8_t* 
   DD_HIP(hipMemsetAsync(d_cgstat.p, 0, 64, st));
   DD_HIP(hipMemsetAsync(d_scal.p, 0, d_scal.bytes, st));   // the scalars kernel's ticket
   if (want_dense && !dense)
-    DD_TRY(dense_inverse_for(D, M, mask, d_rowptr.as<int32_t>(), d_col.as<int32_t>(),
-                             d_val.as<double>(), dense, st));
+    DD_TRY(dense_inverse_for(D, M, mask, dense, st));
   skip_on = (walk_mode(mode) && ann_budget == 0 && fd_at(1) >= 1.0 && opts &&
              (opts->flags & DD_SOLVE_SKIP));
   local_on = walk_mode(mode) && opts && (opts->flags & DD_SOLVE_LOCAL_ACCURACY) &&
@@ -918,20 +917,8 @@ dd_status DDSolver::prepare_inverse(const Dataset& D, const dd_mesh& m, const ui
   std::unique_ptr<FEMesh> M(new FEMesh());
   M->init(m);
   if (M->n_dof > kDenseMaxDof || dense_inverse_cached(D, *M, mask)) return DD_OK;
-  std::vector<int32_t> rowptr, col;
-  std::vector<double> val, dinv;
-  assemble_csr(*M, D.C, mask, rowptr, col, val, dinv);
-  DevBuf r, c, v;
-  DD_TRY(r.alloc(sizeof(int32_t) * rowptr.size()));
-  DD_TRY(c.alloc(sizeof(int32_t) * std::max<size_t>(col.size(), 1)));
-  DD_TRY(v.alloc(sizeof(double) * std::max<size_t>(val.size(), 1)));
-  DD_HIP(hipMemcpyAsync(r.p, rowptr.data(), sizeof(int32_t) * rowptr.size(), hipMemcpyHostToDevice, st));
-  if (!col.empty()) {
-    DD_HIP(hipMemcpyAsync(c.p, col.data(), sizeof(int32_t) * col.size(), hipMemcpyHostToDevice, st));
-    DD_HIP(hipMemcpyAsync(v.p, val.data(), sizeof(double) * val.size(), hipMemcpyHostToDevice, st));
-  }
   std::shared_ptr<DenseInverse> out;
-  DD_TRY(dense_inverse_for(D, *M, mask, r.as<int32_t>(), c.as<int32_t>(), v.as<double>(), out, st));
+  DD_TRY(dense_inverse_for(D, *M, mask, out, st));
   DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }
