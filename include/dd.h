@@ -307,7 +307,7 @@ typedef struct dd_solve_opts {
   int32_t cg_max_iter;   /* 0 = 20000 */
   int32_t flags;         /* DD_SOLVE_NO_GRAPH: launch the CG kernels one by one; DD_SOLVE_CG,
                             DD_SOLVE_SKIP, DD_SOLVE_LOCAL_ACCURACY (below) */
-  double cg_tol;         /* relative residual of the two P_C solves; 0 = 1e-13 */
+  double cg_tol;         /* relative residual of the two P_C solves by CG; 0 = 1e-13 */
   int32_t ann_budget;    /* DD_ANN, DD_KMEANS: leaves per projection (0 = exact walk) */
   int32_t ann_ramp;      /* DD_ANN, DD_KMEANS: > 0 = accuracy schedule.  With a budget,
                             iteration i <= ann_ramp uses ann_budget * i leaves and later
@@ -325,11 +325,14 @@ typedef struct dd_solve_opts {
                                       DD_ERR_ARG */
 } dd_solve_opts;
 #define DD_SOLVE_NO_GRAPH 0x1
-/* P_C by CG even for meshes of at most 16384 DOFs, where dd_solve otherwise
- * forms K^-1 once (blocked Gauss-Jordan on the GPU, about 0.4 s at 16384),
- * keeps it on the dataset for that mesh and Dirichlet pattern (at most 4 GiB
- * of inverses per dataset, least recently used dropped first) and applies it
- * as one product per P_C. */
+/* P_C by CG always.  Otherwise dd_solve forms an operator once and keeps it on the
+ * dataset for that mesh and Dirichlet pattern (at most 4 GiB of them per dataset,
+ * least recently used dropped first): K^-1 for small meshes, applied as one product
+ * per P_C, or the block elimination of the mesh's node planes, from about 6000
+ * DOFs on and as long as it fits that cache (cubes of up to 27 elements a side; 13 ms
+ * to form at 16^3, 28 at 20^3).  Beyond 16384 DOFs CG stays where cg_tol or
+ * cg_max_iter is given, where the Dirichlet DOFs leave a rigid motion free and where
+ * the device has no room for the operator. */
 #define DD_SOLVE_CG 0x2
 /* Exact DD_ANN and DD_KMEANS solves: skip the projection of material points whose state
  * moved less than half the certified gap between their nearest and second

@@ -88,6 +88,7 @@ struct DenseInverse {
   double hx = 0, hy = 0, hz = 0;
   std::vector<uint8_t> mask;
   int64_t n = 0, n_pad = 0;
+  bool planes = false;   // inv holds the block elimination of node planes instead
   DevBuf inv;
 };
 constexpr int64_t kDenseMaxDof = 16384;               // meshes up to here use K^-1

@@ -1,9 +1,9 @@
-// P_C by an explicit inverse for small meshes.  K is constant over the DD
-// iterations (Section 2: the paper factorises it once); for up to kDenseMaxDof
-// DOFs its inverse is formed once on the GPU and kept per (mesh, Dirichlet
-// pattern) on the dataset, and every P_C is then one product of K^-1 with the
-// two right-hand sides (E and S of eqs. "KuE", "KeS") -- a stream of n^2
-// doubles instead of hundreds of CG iterations.
+// P_C by operators formed once.  K is constant over the DD iterations (Section 2:
+// the paper factorises it once): for small meshes its inverse is formed on the
+// GPU and kept per (mesh, Dirichlet pattern) on the dataset, and every P_C is then
+// one product of K^-1 with the two right-hand sides (E and S of eqs. "KuE",
+// "KeS") -- a stream of n^2 doubles instead of hundreds of CG iterations.  Larger
+// meshes keep the block elimination of their node planes instead (below).
 //
 // Inversion.  The nodes are numbered plane by plane and an element joins two
 // neighbouring planes, so K is block tridiagonal in groups of planes (diagonal
@@ -21,7 +21,7 @@
 // identity.  For each 64-block k of it:
 //   A_kk <- A_kk^-1;  A_ik <- -A_ik A_kk (i != k);  A_ij <- A_ij + A_ik A_kj
 //   (i, j != k);  A_kj <- A_kk A_kj (j != k).
-// Measured, 16^3 elements, whole formation: 27 ms (430 ms by Gauss-Jordan over
+// Measured, 16^3 elements (the largest cube below kDenseMaxDof), whole formation: 27 ms (430 ms by Gauss-Jordan over
 // the whole matrix on the vector FP64 units, the trailing updates 375 of them,
 // and the matrix assembled on the host).  What is left is the chain of 238
 // diagonal 64-blocks, each waiting for the one before.
@@ -46,8 +46,8 @@ struct MeshDims {
 
 // Rows of one block of K (DOFs row0 .. row0 + rows - 1) from the element
 // stiffness Ke: the columns of the same block to W (leading dimension ldw) and
-// those of the block before (DOFs prev0 ..) to B (ldb).  One thread per (row,
-// neighbouring node); W and B start at zero.  An entry sums the elements that
+// those of the block before (DOFs prev0 ..) to B (ldb; null: left out).  One
+// thread per (row, neighbouring node); W and B start at zero.  An entry sums the elements that
 // share both nodes in element order.  Dirichlet rows and columns are those of
 // the identity.
 __global__ __launch_bounds__(256) void assemble_block_kernel(
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void assemble_block_kernel(
     if (mask[col] || col >= row0 + rows) continue;   // the next block's columns are its own
     if (col >= row0)
       W[lr * ldw + (col - row0)] = s[c];
-    else
+    else if (B)
       B[lr * ldb + (col - prev0)] = s[c];
   }
 }
@@ -108,11 +108,27 @@ __global__ void pad_identity_kernel(double* __restrict__ W, int64_t n, int64_t n
 // ---------------------------------------------------------------------------
 constexpr int kGT = 64, kGK = 16, kGLd = kGT + 2;
 
+struct Gemm {
+  int64_t m, n, k;
+  const double* A;
+  int64_t lda;
+  const double* B;
+  int64_t ldb;
+  double* C;
+  int64_t ldc;
+};
+struct GemmPair {
+  Gemm g[2];   // blockIdx.z
+};
+
 template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm64_kernel(int64_t m, int64_t n, int64_t kdim, double alpha,
-                                                     const double* __restrict__ A, int64_t lda,
-                                                     const double* __restrict__ B, int64_t ldb,
-                                                     double beta, double* __restrict__ C, int64_t ldc) {
+__global__ __launch_bounds__(256) void gemm64_kernel(GemmPair G, double alpha, double beta) {
+  const Gemm& g = G.g[blockIdx.z];
+  const int64_t m = g.m, n = g.n, kdim = g.k, lda = g.lda, ldb = g.ldb, ldc = g.ldc;
+  const double* __restrict__ A = g.A;
+  const double* __restrict__ B = g.B;
+  double* __restrict__ C = g.C;
+  if ((int64_t)blockIdx.x * kGT >= m || (int64_t)blockIdx.y * kGT >= n) return;
   __shared__ double as[2][kGK][kGLd], bs[2][kGK][kGLd];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t i0 = (int64_t)blockIdx.x * kGT, j0 = (int64_t)blockIdx.y * kGT;
@@ -183,9 +199,23 @@ template <bool TA, bool TB>
 void gemm64(int64_t m, int64_t n, int64_t k, double alpha, const double* A, int64_t lda,
             const double* B, int64_t ldb, double beta, double* C, int64_t ldc, hipStream_t st) {
   if (m <= 0 || n <= 0) return;
+  const GemmPair G = {{{m, n, k, A, lda, B, ldb, C, ldc}, {}}};
   hipLaunchKernelGGL((gemm64_kernel<TA, TB>),
                      dim3((unsigned)((m + kGT - 1) / kGT), (unsigned)((n + kGT - 1) / kGT)), dim3(256),
-                     0, st, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+                     0, st, G, alpha, beta);
+}
+
+// C_s = beta C_s + alpha A_s B_s for the first `count` of the pair
+void gemm64_pair(const GemmPair& G, int count, double alpha, double beta, hipStream_t st) {
+  int64_t m = 0, n = 0;
+  for (int s = 0; s < count; ++s) {
+    m = std::max(m, G.g[s].m);
+    n = std::max(n, G.g[s].n);
+  }
+  hipLaunchKernelGGL((gemm64_kernel<false, false>),
+                     dim3((unsigned)((m + kGT - 1) / kGT), (unsigned)((n + kGT - 1) / kGT),
+                          (unsigned)count),
+                     dim3(256), 0, st, G, alpha, beta);
 }
 
 // dst[j][i] = src[i][j] for i < rows, j < cols (32 x 32 tiles through LDS).
@@ -202,14 +232,25 @@ __global__ __launch_bounds__(256) void transpose_kernel(const double* __restrict
     if (j0 + r < cols && i0 + tx < rows) dst[(j0 + r) * ldd + i0 + tx] = s[tx][r];
 }
 
+// The matrices (n x n, n a multiple of 64) that one Gauss-Jordan sweep inverts
+// side by side, and the inverse of each one's current diagonal block.
+struct SweepPair {
+  double* A[2];
+  int64_t n[2];
+  double* Akk[2];
+};
+
 // Inverts the diagonal block [k0, k0+64)^2 in place (and copies it to Akk).
 // Four lanes hold a row in registers (16 columns each); at each pivot its row
 // goes to the others through LDS and its column through the lanes of a row, so
 // a pivot is one barrier and 16 fused multiply-adds (all in LDS, with two
 // barriers and 16 read-modify-writes per thread, a block took 152 us; this 28,
 // and the division is not what it waits for).
-__global__ __launch_bounds__(256) void gj_diag_kernel(double* __restrict__ A, int64_t n_pad,
-                                                      int64_t k0, double* __restrict__ Akk) {
+__global__ __launch_bounds__(256) void gj_diag_kernel(SweepPair S, int64_t k0) {
+  double* __restrict__ A = S.A[blockIdx.x];
+  double* __restrict__ Akk = S.Akk[blockIdx.x];
+  const int64_t n_pad = S.n[blockIdx.x];
+  if (k0 >= n_pad) return;
   __shared__ double rowp[2][kB];
   const int t = threadIdx.x, r = t >> 2, q = t & 3;   // row r, columns 16 q .. 16 q + 15
   double s[16];
@@ -245,8 +286,11 @@ __global__ __launch_bounds__(256) void gj_diag_kernel(double* __restrict__ A, in
 }
 
 // Column panel: rows i outside the block, A[i, k] <- -A[i, k] Akk.  4 rows per block.
-__global__ __launch_bounds__(256) void gj_col_kernel(double* __restrict__ A, int64_t n_pad,
-                                                     int64_t k0, const double* __restrict__ Akk) {
+__global__ __launch_bounds__(256) void gj_col_kernel(SweepPair S, int64_t k0) {
+  double* __restrict__ A = S.A[blockIdx.y];
+  const double* __restrict__ Akk = S.Akk[blockIdx.y];
+  const int64_t n_pad = S.n[blockIdx.y];
+  if (k0 >= n_pad) return;
   __shared__ double inv[kB][kB + 1];
   __shared__ double row[4][kB];
   const int t = threadIdx.x;
@@ -266,8 +310,10 @@ __global__ __launch_bounds__(256) void gj_col_kernel(double* __restrict__ A, int
 
 // Trailing update of one 64x64 tile outside block row/column k:
 // A[I, J] += A[I, k] A[k, J], a wavefront 32 x 32 of it in FP64 MFMA.
-__global__ __launch_bounds__(256) void gj_update_kernel(double* __restrict__ A, int64_t n_pad,
-                                                        int64_t k0) {
+__global__ __launch_bounds__(256) void gj_update_kernel(SweepPair S, int64_t k0) {
+  double* __restrict__ A = S.A[blockIdx.y];
+  const int64_t n_pad = S.n[blockIdx.y];
+  if (k0 >= n_pad || blockIdx.x >= (n_pad / kB - 1) * (n_pad / kB - 1)) return;
   __shared__ double a[kB][kB + 2];   // [k][row] of A[I, k]
   __shared__ double b[kB][kB + 2];   // A[k, J]
   const int64_t nb = n_pad / kB;
@@ -315,8 +361,11 @@ __global__ __launch_bounds__(256) void gj_update_kernel(double* __restrict__ A, 
 }
 
 // Row panel: columns j outside the block, A[k, j] <- Akk A[k, j].  4 columns per block.
-__global__ __launch_bounds__(256) void gj_row_kernel(double* __restrict__ A, int64_t n_pad,
-                                                     int64_t k0, const double* __restrict__ Akk) {
+__global__ __launch_bounds__(256) void gj_row_kernel(SweepPair S, int64_t k0) {
+  double* __restrict__ A = S.A[blockIdx.y];
+  const double* __restrict__ Akk = S.Akk[blockIdx.y];
+  const int64_t n_pad = S.n[blockIdx.y];
+  if (k0 >= n_pad) return;
   __shared__ double inv[kB][kB + 1];
   __shared__ double colv[4][kB];
   const int t = threadIdx.x;
@@ -334,48 +383,53 @@ __global__ __launch_bounds__(256) void gj_row_kernel(double* __restrict__ A, int
   A[(k0 + r) * n_pad + j] = acc;
 }
 
-// x_s = K^-1 b_s for the two systems; one wavefront per row, fixed reduction order.
-__global__ __launch_bounds__(256) void dense_apply_kernel(const double* __restrict__ inv,
-                                                          int64_t n_pad, int64_t n,
-                                                          const double* __restrict__ b,
-                                                          double* __restrict__ x) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= n) return;
-  const double* row = inv + r * n_pad;
+// out[r] = (BACK: out[r] -) sum_j row[j] v[j] for both systems (v and out: the
+// second n further on), a wavefront per row, fixed reduction order; unrolled so
+// that several iterations' loads are in flight (the FMA chain keeps its order).
+template <bool BACK>
+__device__ inline void row_product(const double* __restrict__ row, const double* v, int64_t n,
+                                   int64_t len, double* out, int lane) {
   double a0 = 0.0, a1 = 0.0;
-  // unrolled so that several iterations' loads are in flight; the FMA chain
-  // keeps its order
 #pragma unroll 8
-  for (int64_t j = lane; j < n; j += 64) {
+  for (int64_t j = lane; j < len; j += 64) {
     const double k = row[j];
-    a0 = fma(k, b[j], a0);
-    a1 = fma(k, b[n + j], a1);
+    a0 = fma(k, v[j], a0);
+    a1 = fma(k, v[n + j], a1);
   }
   for (int off = 32; off > 0; off >>= 1) {
     a0 += __shfl_xor(a0, off);
     a1 += __shfl_xor(a1, off);
   }
   if (lane == 0) {
-    x[r] = a0;
-    x[n + r] = a1;
+    out[0] = BACK ? out[0] - a0 : a0;
+    out[n] = BACK ? out[n] - a1 : a1;
   }
+}
+
+// x_s = K^-1 b_s for the two systems.
+__global__ __launch_bounds__(256) void dense_apply_kernel(const double* __restrict__ inv,
+                                                          int64_t n_pad, int64_t n,
+                                                          const double* __restrict__ b,
+                                                          double* __restrict__ x) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r < n) row_product<false>(inv + r * n_pad, b, n, n, x + r, threadIdx.x & 63);
 }
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
 
-// In-place inverse of W (n x n, n a multiple of 64).
-static void gauss_jordan(double* W, int64_t n, double* akk, hipStream_t st) {
-  const int64_t nb = n / kB;
+// In-place inverses of the first `count` matrices of the pair.
+static void gauss_jordan(const SweepPair& S, int count, hipStream_t st) {
+  const int64_t n = count > 1 ? std::max(S.n[0], S.n[1]) : S.n[0], nb = n / kB;
   for (int64_t k0 = 0; k0 < n; k0 += kB) {
-    hipLaunchKernelGGL(gj_diag_kernel, dim3(1), dim3(256), 0, st, W, n, k0, akk);
+    hipLaunchKernelGGL(gj_diag_kernel, dim3(count), dim3(256), 0, st, S, k0);
     if (nb == 1) return;
-    hipLaunchKernelGGL(gj_col_kernel, dim3(blocks_for(n - kB, 4)), dim3(256), 0, st, W, n, k0, akk);
-    hipLaunchKernelGGL(gj_update_kernel, dim3((unsigned)((nb - 1) * (nb - 1))), dim3(256), 0, st, W, n,
-                       k0);
-    hipLaunchKernelGGL(gj_row_kernel, dim3(blocks_for(n - kB, 4)), dim3(256), 0, st, W, n, k0, akk);
+    const dim3 panel(blocks_for(n - kB, 4), count);
+    hipLaunchKernelGGL(gj_col_kernel, panel, dim3(256), 0, st, S, k0);
+    hipLaunchKernelGGL(gj_update_kernel, dim3((unsigned)((nb - 1) * (nb - 1)), count), dim3(256), 0,
+                       st, S, k0);
+    hipLaunchKernelGGL(gj_row_kernel, panel, dim3(256), 0, st, S, k0);
   }
 }
 
@@ -424,7 +478,7 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
                        dke.as<double>(), dmask.as<uint8_t>(), (int64_t)0, n, (int64_t)0, X, n_pad,
                        (double*)nullptr, (int64_t)0);
     hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, X, n, n_pad);
-    gauss_jordan(X, n_pad, akk.as<double>(), st);
+    gauss_jordan({{X}, {n_pad}, {akk.as<double>()}}, 1, st);
     DD_HIP(hipGetLastError());
     DD_HIP(hipStreamSynchronize(st));
     return DD_OK;
@@ -444,7 +498,7 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
       gemm64<false, true>(b, b, pb, -1.0, L, n_pad, B, pb, 1.0, W, w, st);
     }
     DD_HIP(hipMemcpyAsync(S, W, sizeof(double) * (size_t)(w * w), hipMemcpyDeviceToDevice, st));
-    gauss_jordan(W, w, akk.as<double>(), st);
+    gauss_jordan({{W}, {w}, {akk.as<double>()}}, 1, st);
     DD_HIP(hipMemcpy2DAsync(X + o * n_pad + o, sizeof(double) * n_pad, W, sizeof(double) * w,
                             sizeof(double) * b, (size_t)b, hipMemcpyDeviceToDevice, st));
     // one Newton step, X += X (I - S X), the residual in B: without it the errors
@@ -467,6 +521,331 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
                        st, X + o * n_pad + no, n_pad, b, n - no, X + no * n_pad + o, n_pad);
     DD_HIP(hipGetLastError());
   }
+  DD_HIP(hipStreamSynchronize(st));
+  return DD_OK;
+}
+
+// ---------------------------------------------------------------------------
+// P_C by block elimination of node planes, for meshes whose inverse would be
+// read for longer than the elimination's chain of small launches takes.
+//
+// With the blocks of planes above, both ends of the chain are eliminated at the
+// same time towards the middle block: block k couples to one next block only,
+//   S_next = A_next - C_k^T H_k,  H_k = S_k^-1 C_k,  C_k = K(k, next),
+// and the middle block takes both sides.  Kept are S_k^-1 and H_k (C_k is zero
+// but for the plane next to the other block: H_k has that plane's columns).
+// Then K x = b is
+//   y_next = b_next - H_k^T y_k      (ends to middle, both sides in a launch),
+//   z_k = S_k^-1 y_k                 (all blocks in one launch),
+//   x_k = z_k - H_k x_next           (middle to ends),
+// about 3 n b entries read instead of the inverse's n^2, in P launches.
+// ---------------------------------------------------------------------------
+struct PlaneBlocks {   // P blocks of whole planes: b DOFs each, the last bl
+  int64_t P = 0, b = 0, bl = 0, face = 0;
+  int64_t mid() const { return P / 2; }
+  int64_t off(int64_t k) const { return k * b; }
+  int64_t size(int64_t k) const { return k == P - 1 ? bl : b; }
+};
+
+static __host__ __device__ inline int64_t ld8(int64_t n) { return (n + 7) / 8 * 8; }   // 64-byte rows
+
+static PlaneBlocks plane_blocks(int64_t nx, int64_t ny, int64_t nz) {
+  PlaneBlocks B;
+  B.face = 3 * (nx + 1) * (ny + 1);
+  const int64_t per = std::max<int64_t>(1, (kMinBlock + B.face - 1) / B.face);
+  B.P = std::max<int64_t>(1, (nz + 1) / per);
+  B.b = per * B.face;
+  B.bl = (nz + 1) * B.face - (B.P - 1) * B.b;   // a short last group joins the one before
+  return B;
+}
+
+// Bytes that K^-1 must be larger by, per block, for the chain's launches to pay.
+// Measured per DD iteration, cubes of n elements a side, FP64 scan of 2000 points,
+// inverse / planes: n = 8 0.128 / 0.146 ms, 11 0.198 / 0.209 (15 MB a block), 12
+// 0.254 / 0.224 (23 MB), 14 0.397 / 0.310, 16 0.693 / 0.392; beyond the inverse's
+// sizes CG / planes: 18 6.2 / 0.51, 20 7.8 / 0.73, 24 12.9 / 1.29, 27 16.9 / 2.06.
+constexpr int64_t kPlaneStepBytes = (int64_t)18 << 20;
+
+// doubles of S_k^-1 of all blocks, and of H_k
+static int64_t plane_inv_len(const PlaneBlocks& B) {
+  return (B.P - 1) * B.b * ld8(B.b) + B.bl * ld8(B.bl);
+}
+static int64_t plane_h_len(const PlaneBlocks& B) {
+  return ((B.P - 1) * B.b + B.bl) * ld8(B.face);
+}
+
+// Up to kDenseMaxDof DOFs K^-1 or the planes, whichever is applied sooner; beyond
+// it the planes as long as the dataset's cache holds them (cubes of up to 27
+// elements a side), else CG.  Formation, first solve of one iteration with it:
+// n = 16 13 ms (K^-1 27), 20 28 (CG 28), 24 64 (CG 55), 27 111 (CG 85).
+PCKind pc_kind(int64_t nx, int64_t ny, int64_t nz) {
+  const PlaneBlocks B = plane_blocks(nx, ny, nz);
+  const int64_t n = (nz + 1) * B.face;
+  const int64_t bytes = 8 * (plane_inv_len(B) + plane_h_len(B));
+  const bool fits = B.P >= 3 && bytes <= kDenseCacheBytes;
+  if (n > kDenseMaxDof) return fits ? PCKind::kPlanes : PCKind::kCG;
+  return fits && 8 * n * n - bytes > B.P * kPlaneStepBytes ? PCKind::kPlanes : PCKind::kInverse;
+}
+
+int64_t pc_bytes(int64_t nx, int64_t ny, int64_t nz) {
+  const PlaneBlocks B = plane_blocks(nx, ny, nz);
+  const int64_t n_pad = ((nz + 1) * B.face + kB - 1) / kB * kB;
+  switch (pc_kind(nx, ny, nz)) {
+    case PCKind::kPlanes: return 8 * (plane_inv_len(B) + plane_h_len(B));
+    case PCKind::kInverse: return 8 * n_pad * n_pad;
+    default: return 0;
+  }
+}
+
+namespace {
+
+struct PlaneArgs {
+  int64_t n, P, b, bl, face, mid;
+  const double* inv;   // S_k^-1 at k b ld8(b), leading dimension ld8 of the block's size
+  const double* h;     // H_k at k b ld8(face)
+};
+
+// Couplings of the DOFs c of one plane (`to`) with the plane beside it (`from`):
+// val[27][face], entry 9 comp + (3 (dj + 1) + di + 1) the coupling with component
+// comp of the neighbour node (i + di, j + dj).
+__global__ __launch_bounds__(256) void plane_coupling_kernel(MeshDims d, const double* __restrict__ Ke,
+                                                             const uint8_t* __restrict__ mask,
+                                                             int64_t face, int64_t from, int64_t to,
+                                                             double* __restrict__ val) {
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (id >= 9 * face) return;
+  const int64_t c = id % face;
+  const int nb = (int)(id / face);
+  const int sx = d.nx + 1, comp = (int)(c % 3), i = (int)((c / 3) % sx), j = (int)(c / 3 / sx);
+  const int ii = i + nb % 3 - 1, jj = j + nb / 3 - 1;
+  double s[3] = {0.0, 0.0, 0.0};
+  if (ii >= 0 && jj >= 0 && ii <= d.nx && jj <= d.ny && !mask[to * face + c]) {
+    const int k = (int)to, kk = (int)from, ez = min(k, kk);
+    for (int ey = max(j, jj) - 1; ey <= min(j, jj); ++ey)
+      for (int ex = max(i, ii) - 1; ex <= min(i, ii); ++ex) {
+        if (ex < 0 || ey < 0 || ex >= d.nx || ey >= d.ny) continue;
+        const int a = (i - ex) + 2 * (j - ey) + 4 * (k - ez);
+        const int b = (ii - ex) + 2 * (jj - ey) + 4 * (kk - ez);
+        for (int q = 0; q < 3; ++q) s[q] += Ke[24 * (3 * a + comp) + 3 * b + q];
+      }
+    const int64_t col0 = from * face + 3 * (ii + (int64_t)sx * jj);
+    for (int q = 0; q < 3; ++q)
+      if (mask[col0 + q]) s[q] = 0.0;
+  }
+  for (int q = 0; q < 3; ++q) val[(9 * q + nb) * face + c] = s[q];
+}
+
+// H[r][c] = sum_j X[r][row0 + j] C[j][c] over the 27 neighbours j of c (X: rows x rows, ldx)
+constexpr int kHRows = 8;
+__global__ __launch_bounds__(256) void plane_h_kernel(int sx, int sy, int64_t rows,
+                                                      const double* __restrict__ X, int64_t ldx,
+                                                      int64_t row0, const double* __restrict__ val,
+                                                      double* __restrict__ H, int64_t ldh) {
+  const int64_t face = 3 * (int64_t)sx * sy, c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (c >= face) return;
+  const int i = (int)((c / 3) % sx), j = (int)(c / 3 / sx);
+  double v[27];
+  int at[9];
+#pragma unroll
+  for (int nb = 0; nb < 9; ++nb) {
+    const int ii = i + nb % 3 - 1, jj = j + nb / 3 - 1;
+    at[nb] = ii >= 0 && jj >= 0 && ii < sx && jj < sy ? 3 * (ii + sx * jj) : 0;   // 0: coefficient 0
+#pragma unroll
+    for (int q = 0; q < 3; ++q) v[9 * q + nb] = val[(9 * q + nb) * face + c];
+  }
+  const int64_t r1 = min(rows, ((int64_t)blockIdx.y + 1) * kHRows);
+  for (int64_t r = (int64_t)blockIdx.y * kHRows; r < r1; ++r) {
+    const double* x = X + r * ldx + row0;
+    double s = 0.0;
+#pragma unroll
+    for (int nb = 0; nb < 9; ++nb)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s = fma(x[at[nb] + q], v[9 * q + nb], s);
+    H[r * ldh + c] = s;
+  }
+}
+
+// S[r][c] -= sum_j C[j][r] H[j][c] over the 27 neighbours j of r: one row r per blockIdx.y
+__global__ __launch_bounds__(256) void plane_schur_kernel(int sx, int sy, const double* __restrict__ val,
+                                                          const double* __restrict__ H, int64_t ldh,
+                                                          double* __restrict__ S, int64_t lds_) {
+  const int64_t face = 3 * (int64_t)sx * sy, c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (c >= face) return;
+  const int64_t r = blockIdx.y;
+  const int i = (int)((r / 3) % sx), j = (int)(r / 3 / sx);
+  double s = 0.0;
+#pragma unroll
+  for (int nb = 0; nb < 9; ++nb) {
+    const int ii = i + nb % 3 - 1, jj = j + nb / 3 - 1;
+    const int64_t at = ii >= 0 && jj >= 0 && ii < sx && jj < sy ? 3 * (ii + (int64_t)sx * jj) : 0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s = fma(val[(9 * q + nb) * face + r], H[(at + q) * ldh + c], s);
+  }
+  S[r * lds_ + c] -= s;
+}
+
+// y_next -= H_k^T y_k for step t of both sides (blockIdx.y; the middle block
+// takes both sides' terms in one workgroup).  A workgroup holds 16 columns, 64
+// groups of its threads every 64th row: a row of 16 doubles is a 128-byte line,
+// and 1024 threads put 64 of them in flight each pass.
+constexpr int kFwdCols = 16, kFwdThreads = 1024, kFwdGroups = kFwdThreads / kFwdCols;
+__global__ __launch_bounds__(kFwdThreads) void plane_forward_kernel(PlaneArgs A, int64_t t, double* y) {
+  __shared__ double part[2][kFwdThreads / 64][kFwdCols];
+  const int side = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t kl = t, kr = A.P - 1 - t;
+  const bool left = kl < A.mid, right = kr > A.mid;
+  const bool both = left && right && kl + 1 == A.mid && kr - 1 == A.mid;
+  if (side == 0 ? !left : (!right || both)) return;
+  const int64_t ldh = ld8(A.face);
+  const int64_t c = (int64_t)blockIdx.x * kFwdCols + (threadIdx.x & (kFwdCols - 1));
+  const int g = threadIdx.x / kFwdCols;
+  for (int s = side; s <= (both ? 1 : side); ++s) {
+    const int64_t k = s == 0 ? kl : kr;
+    const int64_t rows = k == A.P - 1 ? A.bl : A.b, o = k * A.b;
+    const int64_t dst = s == 0 ? o + rows : o - A.face;
+    const double* H = A.h + o * ldh;
+    double a0 = 0.0, a1 = 0.0;
+    if (c < A.face) {
+#pragma unroll 8
+      for (int64_t r = g; r < rows; r += kFwdGroups) {
+        const double h = H[r * ldh + c];
+        a0 = fma(h, y[o + r], a0);
+        a1 = fma(h, y[A.n + o + r], a1);
+      }
+    }
+    a0 += __shfl_xor(a0, 16);
+    a1 += __shfl_xor(a1, 16);
+    a0 += __shfl_xor(a0, 32);
+    a1 += __shfl_xor(a1, 32);
+    if (lane < kFwdCols) {
+      part[0][wave][lane] = a0;
+      part[1][wave][lane] = a1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * kFwdCols) {
+      const int sys = threadIdx.x / kFwdCols;
+      if (c < A.face) {
+        double sum = 0.0;
+        for (int w = 0; w < kFwdThreads / 64; ++w) sum += part[sys][w][threadIdx.x & (kFwdCols - 1)];
+        y[sys * A.n + dst + c] -= sum;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// z = S_k^-1 y_k, every block
+__global__ __launch_bounds__(256) void plane_blocks_kernel(PlaneArgs A, const double* __restrict__ y,
+                                                           double* __restrict__ x) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= A.n) return;
+  const int64_t k = min(r / A.b, A.P - 1), len = k == A.P - 1 ? A.bl : A.b, o = k * A.b;
+  row_product<false>(A.inv + o * ld8(A.b) + (r - o) * ld8(len), y + o, A.n, len, x + r, threadIdx.x & 63);
+}
+
+// x_k -= H_k x_next at step t of both sides (blockIdx.y)
+__global__ __launch_bounds__(256) void plane_backward_kernel(PlaneArgs A, int64_t t, double* x) {
+  const bool left = blockIdx.y == 0;
+  const int64_t k = left ? t : A.P - 1 - t;
+  if (left ? k >= A.mid : k <= A.mid) return;
+  const int64_t rows = k == A.P - 1 ? A.bl : A.b, o = k * A.b;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  row_product<true>(A.h + (o + r) * ld8(A.face), x + (left ? o + rows : o - A.face), A.n, A.face, x + o + r,
+                  threadIdx.x & 63);
+}
+
+PlaneArgs plane_args(const DenseInverse& D) {
+  const PlaneBlocks B = plane_blocks(D.nx, D.ny, D.nz);
+  const double* p = D.inv.as<double>();
+  return {D.n, B.P, B.b, B.bl, B.face, B.mid(), p, p + plane_inv_len(B)};
+}
+
+}  // namespace
+
+// Forms S_k^-1 and H_k on st.
+static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* mask, DenseInverse& D,
+                             hipStream_t st) {
+  const PlaneBlocks B = plane_blocks(M.nx, M.ny, M.nz);
+  const int64_t n = M.n_dof, inv_len = plane_inv_len(B);
+  D.n = n;
+  D.planes = true;
+  DD_TRY(D.inv.alloc(sizeof(double) * (size_t)(inv_len + plane_h_len(B))));
+  const int64_t bmax = std::max(B.b, B.bl), wmax = (bmax + kB - 1) / kB * kB;
+  DevBuf work, val, akk, dke, dmask;
+  DD_TRY(work.alloc(sizeof(double) * (size_t)(6 * wmax * wmax)));
+  DD_TRY(val.alloc(sizeof(double) * (size_t)(2 * 27 * B.face)));
+  DD_TRY(akk.alloc(sizeof(double) * 2 * kB * kB));
+  DD_TRY(dke.alloc(sizeof(double) * 24 * 24));
+  DD_TRY(dmask.alloc((size_t)n));
+  DD_HIP(hipMemcpyAsync(dke.p, Ke, sizeof(double) * 24 * 24, hipMemcpyHostToDevice, st));
+  DD_HIP(hipMemcpyAsync(dmask.p, mask, (size_t)n, hipMemcpyHostToDevice, st));
+  const MeshDims dims{M.nx, M.ny, M.nz};
+  const int sx = M.nx + 1, sy = M.ny + 1;
+  const int64_t mid = B.mid(), ldh = ld8(B.face);
+  double* inv = D.inv.as<double>();
+  double* h = inv + inv_len;
+  auto side_val = [&](int s) { return val.as<double>() + s * 27 * B.face; };
+  // the blocks of a step (one of each side, the middle one alone at the end)
+  for (int64_t t = 0; t <= mid; ++t) {
+    int64_t blk[2];
+    int count = 0;
+    if (t < mid) blk[count++] = t;
+    if (t < mid && B.P - 1 - t > mid) blk[count++] = B.P - 1 - t;
+    if (t == mid) blk[count++] = mid;
+    SweepPair S = {};
+    GemmPair res = {}, add = {};
+    for (int q = 0; q < count; ++q) {
+      const int64_t k = blk[q], b = B.size(k), w = (b + kB - 1) / kB * kB, ld = ld8(b);
+      double* W = work.as<double>() + 3 * q * wmax * wmax;
+      double *S0 = W + wmax * wmax, *R = S0 + wmax * wmax, *X = inv + B.off(k) * ld8(B.b);
+      DD_HIP(hipMemsetAsync(W, 0, sizeof(double) * (size_t)(w * w), st));
+      hipLaunchKernelGGL(assemble_block_kernel, dim3(blocks_for(27 * b, 256)), dim3(256), 0, st, dims,
+                         dke.as<double>(), dmask.as<uint8_t>(), B.off(k), b, (int64_t)0, W, w,
+                         (double*)nullptr, (int64_t)0);
+      if (w > b) hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, W, b, w);
+      for (int s = 0; s < 2; ++s) {   // the Schur terms of the block(s) before
+        const int64_t from = s == 0 ? k - 1 : k + 1;
+        const bool has = s == 0 ? from >= 0 && from < mid : from < B.P && from > mid;
+        if (!has) continue;
+        const double* H = h + (B.off(from) + (s == 0 ? B.size(from) - B.face : 0)) * ldh;
+        double* at = W + (s == 0 ? 0 : (b - B.face) * (w + 1));
+        hipLaunchKernelGGL(plane_schur_kernel, dim3(blocks_for(B.face, 256), (unsigned)B.face), dim3(256),
+                           0, st, sx, sy, side_val(s), H, ldh, at, w);
+      }
+      DD_HIP(hipMemcpyAsync(S0, W, sizeof(double) * (size_t)(w * w), hipMemcpyDeviceToDevice, st));
+      hipLaunchKernelGGL(identity_kernel, dim3(blocks_for(b * b, 256)), dim3(256), 0, st, R, b);
+      S.A[q] = W;
+      S.n[q] = w;
+      S.Akk[q] = akk.as<double>() + q * kB * kB;
+      res.g[q] = {b, b, b, S0, w, W, w, R, b};
+      add.g[q] = {b, b, b, W, w, R, b, X, ld};
+    }
+    gauss_jordan(S, count, st);
+    for (int q = 0; q < count; ++q) {
+      const int64_t k = blk[q], b = B.size(k), w = S.n[q];
+      DD_HIP(hipMemcpy2DAsync(add.g[q].C, sizeof(double) * ld8(b), S.A[q], sizeof(double) * w,
+                              sizeof(double) * b, (size_t)b, hipMemcpyDeviceToDevice, st));
+    }
+    // one Newton step, X += X (I - S X): without it the blocks' errors add up
+    // along the planes
+    gemm64_pair(res, count, -1.0, 1.0, st);
+    gemm64_pair(add, count, 1.0, 1.0, st);
+    if (t == mid) break;
+    for (int q = 0; q < count; ++q) {
+      const int64_t k = blk[q], b = B.size(k), o = B.off(k);
+      const int s = k < mid ? 0 : 1;
+      // planes on both sides of the boundary
+      const int64_t from = s == 0 ? (o + b) / B.face - 1 : o / B.face, to = s == 0 ? from + 1 : from - 1;
+      hipLaunchKernelGGL(plane_coupling_kernel, dim3(blocks_for(9 * B.face, 256)), dim3(256), 0, st, dims,
+                         dke.as<double>(), dmask.as<uint8_t>(), B.face, from, to, side_val(s));
+      hipLaunchKernelGGL(plane_h_kernel, dim3(blocks_for(B.face, 256), blocks_for(b, kHRows)), dim3(256),
+                         0, st, sx, sy, b, add.g[q].C, ld8(b), s == 0 ? b - B.face : (int64_t)0,
+                         side_val(s), h + o * ldh, ldh);
+    }
+    DD_HIP(hipGetLastError());
+  }
+  DD_HIP(hipGetLastError());
   DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }
@@ -504,7 +883,10 @@ dd_status dense_inverse_for(const Dataset& ds, const FEMesh& M, const uint8_t* m
   d->mask.assign(mask, mask + n);
   double Ke[24 * 24];
   element_stiffness(M, ds.C, Ke);
-  DD_TRY(form_inverse(M, Ke, mask, *d, st));
+  if (pc_kind(M.nx, M.ny, M.nz) == PCKind::kPlanes)
+    DD_TRY(form_planes(M, Ke, mask, *d, st));
+  else
+    DD_TRY(form_inverse(M, Ke, mask, *d, st));
   std::lock_guard<std::mutex> lk(ds.cache_mu);
   ds.pc_cache.push_front(d);
   int64_t bytes = 0;
@@ -519,9 +901,20 @@ dd_status dense_inverse_for(const Dataset& ds, const FEMesh& M, const uint8_t* m
   return DD_OK;
 }
 
-dd_status dense_apply(const DenseInverse& D, const double* b, double* x, hipStream_t st) {
-  hipLaunchKernelGGL(dense_apply_kernel, dim3(blocks_for(D.n, 4)), dim3(256), 0, st,
-                     D.inv.as<double>(), D.n_pad, D.n, b, x);
+dd_status dense_apply(const DenseInverse& D, double* b, double* x, hipStream_t st) {
+  if (!D.planes) {
+    hipLaunchKernelGGL(dense_apply_kernel, dim3(blocks_for(D.n, 4)), dim3(256), 0, st,
+                       D.inv.as<double>(), D.n_pad, D.n, b, x);
+    DD_HIP(hipGetLastError());
+    return DD_OK;
+  }
+  const PlaneArgs A = plane_args(D);
+  const dim3 fwd(blocks_for(A.face, kFwdCols), 2), bwd(blocks_for(std::max(A.b, A.bl), 4), 2);
+  for (int64_t t = 0; t < A.mid; ++t)
+    hipLaunchKernelGGL(plane_forward_kernel, fwd, dim3(kFwdThreads), 0, st, A, t, b);
+  hipLaunchKernelGGL(plane_blocks_kernel, dim3(blocks_for(A.n, 4)), dim3(256), 0, st, A, b, x);
+  for (int64_t t = A.mid - 1; t >= 0; --t)
+    hipLaunchKernelGGL(plane_backward_kernel, bwd, dim3(256), 0, st, A, t, x);
   DD_HIP(hipGetLastError());
   return DD_OK;
 }

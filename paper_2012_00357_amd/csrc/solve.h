@@ -39,8 +39,13 @@ dd_status dense_inverse_for(const Dataset& ds, const FEMesh& M, const uint8_t* m
 // The cached K^-1 for the mesh and Dirichlet pattern, or null.
 std::shared_ptr<DenseInverse> dense_inverse_cached(const Dataset& ds, const FEMesh& M,
                                                    const uint8_t* mask);
-// x[0..n) = K^-1 b[0..n), x[n..2n) = K^-1 b[n..2n).
-dd_status dense_apply(const DenseInverse& D, const double* b, double* x, hipStream_t st);
+// How P_C is solved for a mesh unless the caller asks for CG, and the device
+// bytes kept on the dataset for it.
+enum class PCKind { kInverse, kPlanes, kCG };
+PCKind pc_kind(int64_t nx, int64_t ny, int64_t nz);
+int64_t pc_bytes(int64_t nx, int64_t ny, int64_t nz);
+// x[0..n) = K^-1 b[0..n), x[n..2n) = K^-1 b[n..2n); b is overwritten.
+dd_status dense_apply(const DenseInverse& D, double* b, double* x, hipStream_t st);
 
 class DDSolver {
  public:

@@ -6,12 +6,11 @@
 // (eqs. "KuE", "KeS") needs C eps* = L w_eps* and sig* = L w_sig*, and returns
 // eps = B u, sig = sig* + C B eta, i.e. w_eps = L^T B u, w_sig = w_sig* + L^T B eta.
 //
-// K = A_e{ w B^T C B } is assembled once (for conjugate gradients on the host, CSR
-// over all DOFs with identity
-// rows at Dirichlet DOFs) and both systems K u = E, K eta = S are solved
-// together by a Jacobi-preconditioned conjugate-gradient kernel running in one
-// workgroup, warm-started from the previous iterate.  All reductions run in a
-// fixed order, so a solve is bitwise reproducible.
+// K = A_e{ w B^T C B } is constant.  Both systems K u = E, K eta = S are solved
+// together: with an operator kept on the dataset (dense.hip), or by a
+// Jacobi-preconditioned conjugate gradient over the CSR matrix (assembled on the
+// host), warm-started from the previous iterate.  All reductions run in a fixed
+// order, so a solve is bitwise reproducible.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -664,6 +663,50 @@ __global__ void local_accuracy_kernel(int64_t nm, const double* __restrict__ dis
 
 static unsigned g256(int64_t n) { return (unsigned)((n + 255) / 256); }
 
+// Whether the Dirichlet DOFs exclude every rigid motion (then K is positive
+// definite): the Gram matrix of the six rigid motions over them, in coordinates
+// scaled to [-1, 1], by Cholesky with a bound on the pivots.
+static bool rigid_motions_excluded(const FEMesh& M, const uint8_t* mask) {
+  double G[6][6] = {};
+  const double s = 2.0 / std::max({M.nx * M.hx, M.ny * M.hy, M.nz * M.hz});
+  double count = 0.0;
+  for (int k = 0; k <= M.nz; ++k)
+    for (int j = 0; j <= M.ny; ++j)
+      for (int i = 0; i <= M.nx; ++i) {
+        const uint8_t* m = mask + 3 * M.node(i, j, k);
+        if (!(m[0] | m[1] | m[2])) continue;
+        const double x = s * M.hx * (i - 0.5 * M.nx), y = s * M.hy * (j - 0.5 * M.ny),
+                     z = s * M.hz * (k - 0.5 * M.nz);
+        const double R[3][6] = {{1, 0, 0, 0, z, -y}, {0, 1, 0, -z, 0, x}, {0, 0, 1, y, -x, 0}};
+        for (int c = 0; c < 3; ++c) {
+          if (!m[c]) continue;
+          count += 1.0;
+          for (int a = 0; a < 6; ++a)
+            for (int b = 0; b <= a; ++b) G[a][b] += R[c][a] * R[c][b];
+        }
+      }
+  for (int a = 0; a < 6; ++a) {
+    for (int b = 0; b <= a; ++b) {
+      double v = G[a][b];
+      for (int q = 0; q < b; ++q) v -= G[a][q] * G[b][q];
+      if (a == b) {
+        if (!(v > 1e-9 * count)) return false;
+        G[a][a] = std::sqrt(v);
+      } else {
+        G[a][b] = v / G[b][b];
+      }
+    }
+  }
+  return count > 0.0;
+}
+
+// Whether P_C uses an operator kept on the dataset.  Beyond the inverse's sizes
+// CG also takes meshes that are free to move (K singular, consistent forces).
+static bool use_kept_operator(const FEMesh& M, const uint8_t* mask) {
+  if (pc_kind(M.nx, M.ny, M.nz) == PCKind::kCG) return false;
+  return M.n_dof <= kDenseMaxDof || rigid_motions_excluded(M, mask);
+}
+
 // ---------------------------------------------------------------------------
 // Solver object
 // ---------------------------------------------------------------------------
@@ -706,8 +749,16 @@ dd_status DDSolver::setup(const Dataset& D, const dd_mesh& mesh, const uint8_t* 
   std::memcpy(L, Lm, sizeof(L));
   std::memcpy(Lt, LT, sizeof(Lt));
   const int64_t nd = M.n_dof, nm = M.n_mp;
-  const bool want_dense = nd <= kDenseMaxDof && !(opts && (opts->flags & DD_SOLVE_CG));
-  if (want_dense) dense = dense_inverse_cached(D, M, mask);
+  bool want_dense = use_kept_operator(M, mask) && !(opts && (opts->flags & DD_SOLVE_CG));
+  if (nd > kDenseMaxDof && opts && (opts->cg_tol > 0 || opts->cg_max_iter > 0)) want_dense = false;
+  if (want_dense) {
+    dense = dense_inverse_cached(D, M, mask);
+    if (!dense) {
+      const dd_status rc = dense_inverse_for(D, M, mask, dense, st);
+      if (rc == DD_ERR_OOM && nd > kDenseMaxDof) want_dense = false;   // CG needs a fraction of it
+      else DD_TRY(rc);
+    }
+  }
   const bool need_csr = !want_dense;   // the CSR matrix is CG's
   std::vector<int32_t> rowptr, col;
   std::vector<double> val, dinv;
@@ -815,8 +866,6 @@ dd_status DDSolver::setup(const Dataset& D, const dd_mesh& mesh, const uint8_t* 
   DD_HIP(hipMemsetAsync(d_x.p, 0, sizeof(double) * 2 * nd, st));
   DD_HIP(hipMemsetAsync(d_cgstat.p, 0, 64, st));
   DD_HIP(hipMemsetAsync(d_scal.p, 0, d_scal.bytes, st));   // the scalars kernel's ticket
-  if (want_dense && !dense)
-    DD_TRY(dense_inverse_for(D, M, mask, dense, st));
   skip_on = (walk_mode(mode) && ann_budget == 0 && fd_at(1) >= 1.0 && opts &&
              (opts->flags & DD_SOLVE_SKIP));
   local_on = walk_mode(mode) && opts && (opts->flags & DD_SOLVE_LOCAL_ACCURACY) &&
@@ -900,10 +949,7 @@ int64_t DDSolver::footprint_bytes(const dd_mesh& m) {
 }
 
 int64_t DDSolver::inverse_bytes(const dd_mesh& m) {
-  const int64_t nd = 3 * (int64_t)(m.nx + 1) * (m.ny + 1) * (m.nz + 1);
-  if (nd > kDenseMaxDof) return 0;
-  const int64_t n_pad = (nd + 63) / 64 * 64;   // the Gauss-Jordan block size
-  return n_pad * n_pad * (int64_t)sizeof(double);
+  return pc_bytes(m.nx, m.ny, m.nz);
 }
 
 bool DDSolver::inverse_cached(const Dataset& D, const dd_mesh& m, const uint8_t* mask) {
@@ -916,9 +962,11 @@ dd_status DDSolver::prepare_inverse(const Dataset& D, const dd_mesh& m, const ui
                                     hipStream_t st) {
   std::unique_ptr<FEMesh> M(new FEMesh());
   M->init(m);
-  if (M->n_dof > kDenseMaxDof || dense_inverse_cached(D, *M, mask)) return DD_OK;
+  if (!use_kept_operator(*M, mask) || dense_inverse_cached(D, *M, mask)) return DD_OK;
   std::shared_ptr<DenseInverse> out;
-  DD_TRY(dense_inverse_for(D, *M, mask, out, st));
+  const dd_status rc = dense_inverse_for(D, *M, mask, out, st);
+  if (rc == DD_ERR_OOM && M->n_dof > kDenseMaxDof) return DD_OK;   // setup() turns to CG
+  DD_TRY(rc);
   DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }

@@ -181,3 +181,35 @@ def test_inverse_blocks_equal_cg(L, C0, mesh):
     assert np.array_equal(a["idx"], b["idx"])
     assert np.abs(a["u"] - b["u"]).max() <= 1e-10 * np.abs(b["u"]).max()
     ds.close()
+
+
+@pytest.mark.parametrize("mesh", [(12, 12, 12), (9, 9, 40), (5, 5, 160), (15, 15, 23), (20, 17, 16),
+                                  (30, 30, 3), (34, 34, 2)])
+def test_plane_elimination_equals_cg(L, C0, mesh):
+    """P_C by the elimination of node planes (odd and even numbers of blocks, three
+    of them, groups of planes with a longer last one, block sizes around a multiple
+    of 64, below and above the inverse's 16384 DOFs) gives the conjugate gradients'
+    solve: the same associations, u within 1e-10 of its maximum (CG residual 1e-13).
+    A caller's CG options and a body free to move keep to CG beyond those DOFs."""
+    nx, ny, nz = mesh
+    N = 3000
+    e, s = ddsynth.data_points(N, 9100 + nx + 10 * ny + 100 * nz)
+    ds = L.dd_dataset_create(to_dev(e), to_dev(s), C0, packs=0x1)
+    n1 = (nx + 1) * (ny + 1) * (nz + 1)
+    mask = np.zeros((n1, 3), np.uint8)
+    mask[np.arange(n1) % (nx + 1) == 0] = 1
+    rng = np.random.default_rng(9)
+    force = np.where(mask, 0.0, rng.normal(0, 20.0 / (nx * ny * nz + 1), (n1, 3)))
+    init = ddsynth.indices(8 * nx * ny * nz, N, 6)
+    a = L.dd_solve(ds, mesh, mask.ravel(), force.ravel(), init, max_iter=3)
+    b = L.dd_solve(ds, mesh, mask.ravel(), force.ravel(), init, max_iter=3, cg=True)
+    again = L.dd_solve(ds, mesh, mask.ravel(), force.ravel(), init, max_iter=3)
+    assert a["cg_iterations"] == 0 and b["cg_iterations"] > 0
+    assert np.array_equal(a["idx"], b["idx"])
+    assert np.abs(a["u"] - b["u"]).max() <= 1e-10 * np.abs(b["u"]).max()
+    assert np.array_equal(a["u"], again["u"])
+    if 3 * n1 > 16384:
+        c = L.dd_solve(ds, mesh, mask.ravel(), force.ravel(), init, max_iter=1, cg_tol=1e-6)
+        free = L.dd_solve(ds, mesh, np.zeros(3 * n1, np.uint8), np.zeros(3 * n1), init, max_iter=1)
+        assert c["cg_iterations"] > 0 and free["cg_iterations"] > 0
+    ds.close()
