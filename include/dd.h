@@ -88,7 +88,9 @@ typedef enum dd_mode {
    * distances with a proven error margin, FP64 rerank.  With ann_budget = 0 the
    * walk ends only when every box is pruned, and the result is exact; with a
    * budget it stops after that many leaves (64 points each) and is approximate
-   * (never worse than the warm-start point). */
+   * (never worse than the warm-start point).  An exact call that asks for no
+   * statistics finds the same answers by a 16-bit scan where that is sooner (data
+   * sets of 2^13 to 2^24 points; scan_for_walk in project.hip). */
   DD_ANN = 3,
   /* Plain FP64 direct-form scan (VALU), the simplest exact kernel. */
   DD_DIRECT_FP64 = 4,
@@ -107,7 +109,7 @@ typedef enum dd_mode {
    * Section 4.2: a child is entered while |q - c| - f_d r is below the best
    * distance the walk has found itself (the first descent reaches a leaf
    * whatever the warm start); the warm-start point stays a candidate, so the
-   * answer is never farther than it. */
+   * answer is never farther than it.  Exact calls by scan as for DD_ANN. */
   DD_KMEANS = 6
 } dd_mode;
 
@@ -119,6 +121,9 @@ typedef enum dd_mode {
 #define DD_PACK_FP16 0x8u   /* tile-centred FP16 [N][16]: DD_MIXED_FP16 */
 #define DD_PACK_ANN 0x10u   /* box tree over the sorted order, compact leaves (implies FP64): DD_ANN */
 #define DD_PACK_KMEANS 0x20u /* k-means tree, compact leaves (implies FP64): DD_KMEANS */
+/* A data set with a tree, 2^13 to 2^24 points and no 16-bit pack keeps the FP16 one for
+ * its exact searches as well (36 bytes a point), if the device has room for it;
+ * DD_MIXED_FP16 stays unavailable on it. */
 #define DD_PACK_DEFAULT (DD_PACK_FP64 | DD_PACK_BF16)
 
 typedef struct dd_dataset dd_dataset;

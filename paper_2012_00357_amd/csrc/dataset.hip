@@ -516,6 +516,35 @@ static dd_status choose_scale16(Dataset& D, hipStream_t st) {
   return DD_OK;
 }
 
+// The tile-centred 16-bit packs `which` of D, from its sorted FP64 pack.
+static dd_status build_pack16(Dataset& D, uint32_t which, int tile, hipStream_t st) {
+  const int64_t N = D.N;
+  D.n_tiles = (N + tile - 1) / tile;
+  const int64_t rows = D.n_tiles * tile;
+  DD_TRY(build_tile_boxes(D, tile, &D.boxes, D.boxes16, st));
+  DD_TRY(D.centre.alloc(sizeof(float) * 12 * (size_t)D.n_tiles));
+  DD_TRY(D.radius.alloc(sizeof(float) * (size_t)D.n_tiles));
+  hipLaunchKernelGGL(tile_stats_kernel, dim3((unsigned)D.n_tiles), dim3(kStatThreads), 0, st,
+                     D.w64.as<double>(), N, tile, D.centre.as<float>(), D.radius.as<float>());
+  DD_HIP(hipGetLastError());
+  DD_TRY(choose_scale16(D, st));
+  if (which & DD_PACK_BF16) {
+    DD_TRY(D.wbf16.alloc(sizeof(uint16_t) * 16 * (size_t)rows));
+    hipLaunchKernelGGL(pack16_kernel<Bf16>, dim3(grid_for(rows)), dim3(256), 0, st,
+                       D.w64.as<double>(), N, rows, tile, (double)D.sc16.s, D.centre.as<float>(),
+                       D.wbf16.as<uint16_t>());
+    DD_HIP(hipGetLastError());
+  }
+  if (which & DD_PACK_FP16) {
+    DD_TRY(D.wfp16.alloc(sizeof(uint16_t) * 16 * (size_t)rows));
+    hipLaunchKernelGGL(pack16_kernel<Fp16>, dim3(grid_for(rows)), dim3(256), 0, st,
+                       D.w64.as<double>(), N, rows, tile, (double)D.sc16.s, D.centre.as<float>(),
+                       D.wfp16.as<uint16_t>());
+    DD_HIP(hipGetLastError());
+  }
+  return DD_OK;
+}
+
 static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_dataset_opts* opts,
                              hipStream_t st, Dataset& D) {
   uint32_t packs = (opts && opts->packs) ? opts->packs : DD_PACK_DEFAULT;
@@ -686,30 +715,17 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
   // boxes of the scans' tiles
   DD_TRY(build_tile_boxes(D, kTile64, nullptr, D.boxes, st));
 
-  // 5. tile-centred 16-bit packs, from the sorted FP64 pack
+  // 5. tile-centred 16-bit packs, from the sorted FP64 pack; a data set with a
+  // tree holds one for its exact searches too, as long as the device has room
   if (packs & (DD_PACK_BF16 | DD_PACK_FP16)) {
-    D.n_tiles = (N + tile - 1) / tile;
-    DD_TRY(build_tile_boxes(D, tile, &D.boxes, D.boxes16, st));
-    int64_t rows = D.n_tiles * tile;
-    DD_TRY(D.centre.alloc(sizeof(float) * 12 * (size_t)D.n_tiles));
-    DD_TRY(D.radius.alloc(sizeof(float) * (size_t)D.n_tiles));
-    hipLaunchKernelGGL(tile_stats_kernel, dim3((unsigned)D.n_tiles), dim3(kStatThreads), 0, st,
-                       D.w64.as<double>(), N, tile, D.centre.as<float>(), D.radius.as<float>());
-    DD_HIP(hipGetLastError());
-    DD_TRY(choose_scale16(D, st));
-    if (packs & DD_PACK_BF16) {
-      DD_TRY(D.wbf16.alloc(sizeof(uint16_t) * 16 * (size_t)rows));
-      hipLaunchKernelGGL(pack16_kernel<Bf16>, dim3(grid_for(rows)), dim3(256), 0, st,
-                         D.w64.as<double>(), N, rows, tile, (double)D.sc16.s, D.centre.as<float>(),
-                         D.wbf16.as<uint16_t>());
-      DD_HIP(hipGetLastError());
-    }
-    if (packs & DD_PACK_FP16) {
-      DD_TRY(D.wfp16.alloc(sizeof(uint16_t) * 16 * (size_t)rows));
-      hipLaunchKernelGGL(pack16_kernel<Fp16>, dim3(grid_for(rows)), dim3(256), 0, st,
-                         D.w64.as<double>(), N, rows, tile, (double)D.sc16.s, D.centre.as<float>(),
-                         D.wfp16.as<uint16_t>());
-      DD_HIP(hipGetLastError());
+    DD_TRY(build_pack16(D, packs, tile, st));
+  } else if ((packs & (DD_PACK_ANN | DD_PACK_KMEANS)) && N >= kTreeScanMin && N <= kTreeScanMax) {
+    const dd_status rc = build_pack16(D, DD_PACK_FP16, tile, st);
+    if (rc == DD_ERR_OOM) {
+      DD_HIP(hipStreamSynchronize(st));
+      D.wfp16.release();
+    } else {
+      DD_TRY(rc);
     }
   }
 

@@ -20,6 +20,7 @@ dd_status DevBuf::alloc(size_t n) {
   hipError_t e = hipMalloc(&p, n);
   if (e != hipSuccess) {
     p = nullptr;
+    (void)hipGetLastError();   // a caller that goes on without the buffer starts clean
     return set_error(e == hipErrorOutOfMemory ? DD_ERR_OOM : DD_ERR_DEVICE,
                      std::string("hipMalloc(") + std::to_string(n) + "): " + hipGetErrorString(e));
   }

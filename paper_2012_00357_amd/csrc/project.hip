@@ -328,6 +328,24 @@ bool cull_pays(const Dataset& D, int mode, int64_t m, bool warm) {
                 : D.N >= (1 << 16) && m * D.N > ((int64_t)1 << 27);
 }
 
+// The 16-bit scan that finds an exact walk's answers sooner, or 0.  Its tiles are
+// matrix products shared by 32 queries, where a walk's leaf is one query's chain
+// of dependent loads and vector instructions.  P_D per DD iteration, walk / FP16
+// scan: 10^5 points, 512 queries 393-606 / 101-103 us, 64000 queries 3431-4220 /
+// 463-580; 10^6 points, 32768 queries 2368-5209 / 777-1081; 2^24, 32768 queries
+// 3345-17526 / 1329-5021.  With queries near the data and a warm start both take
+// the same time at 2^24 points and 32768 queries (1667-1777 / 1723-1772) and the
+// walk is ahead at 2^26 (2204-2611 / 3586-3631): the pack ends at 2^24.  For few
+// queries on few points the walk's single launch wins: 10^4 points, 64 queries
+// 67-74 / 85-93, 512 queries 75-82 / 91-95, 4096 queries 100-102 / 99-100; 2^15
+// points, 64 queries 80-99 / 86-90, 512 queries 124-144 / 91; 2^16 points, 8
+// queries 83-88 / 83, 64 queries 86-100 / 88-92.
+int scan_for_walk(const Dataset& D, int64_t m) {
+  if (D.N < kTreeScanMin || D.N > kTreeScanMax) return 0;
+  if (!(D.N > (1 << 16) || m >= 4096 || (m >= 512 && D.N >= (1 << 15)))) return 0;
+  return D.wfp16.p ? DD_MIXED_FP16 : D.wbf16.p ? DD_MIXED_BF16 : 0;
+}
+
 // A culled scan in `mode` of m prepared queries (with their coordinates on the
 // principal axes): all of them, sorted by their cells, or those of list L in
 // its order; merge and FP64 rerank.  n_left: the queries the scan leaves (their
@@ -511,63 +529,12 @@ dd_status project_reserved(const Dataset& D, const double* states_dev, bool whit
                          dist_out_dev, nullptr, st, nullptr, nullptr, arena);
 }
 
-// As project_impl; dist2_out_dev (exact DD_ANN only) receives the distance to
-// the second nearest point, -1 where it is not certified; fd_q / budget_q
-// (walk modes, device arrays over the m states) give each state its own
-// radius factor and leaf budget; `fixed` (optional) is a caller's reserve that
-// the call carves every temporary buffer from.
-dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool whitened, int64_t m,
-                          const int64_t* warm_start_idx_dev, const dd_project_opts* opts,
-                          int64_t* idx_out_dev, double* dist_out_dev, double* dist2_out_dev,
-                          hipStream_t st, const float* fd_q, const int* budget_q,
-                          ScratchArena* fixed) {
-  if (m < 0 || m > 0x7FFFFFFFll) return set_error(DD_ERR_ARG, "m must be in [0, 2^31-1]");
-  if (m == 0) return DD_OK;
-  if (!states_dev || !idx_out_dev) return set_error(DD_ERR_ARG, "NULL states or idx_out");
-  const int mode = opts ? opts->mode : DD_EXACT_FP64;
-  const int splits = opts ? opts->splits : 0;
-  if (splits < 0) return set_error(DD_ERR_ARG, "splits must be >= 0");
-  const int budget = opts ? opts->ann_budget : 0;
-  if (budget < 0) return set_error(DD_ERR_ARG, "ann_budget must be >= 0");
-  if (opts && (opts->passes < 0 || opts->passes > 2))
-    return set_error(DD_ERR_ARG, "passes must be 0, 1 or 2");
-  const double discount = opts ? opts->ann_radius_discount : 0.0;
-  if (!(discount >= 0.0 && discount <= 1.0))
-    return set_error(DD_ERR_ARG, "ann_radius_discount must be in [0, 1]");
-  const double fd = 1.0 - discount;
-  if (discount > 0.0 && mode != DD_KMEANS)
-    return set_error(DD_ERR_ARG, "ann_radius_discount applies to the k-means walk only");
-  switch (mode) {
-    case DD_EXACT_FP64:
-    case DD_DIRECT_FP64:
-      if (!(D.packs & DD_PACK_FP64)) return set_error(DD_ERR_UNSUPPORTED, "dataset has no FP64 pack");
-      break;
-    case DD_MIXED_FP32:
-      if (!(D.packs & DD_PACK_FP32) || !(D.packs & DD_PACK_FP64))
-        return set_error(DD_ERR_UNSUPPORTED, "FP32 mode needs the FP32 and FP64 packs");
-      break;
-    case DD_MIXED_BF16:
-      if (!(D.packs & DD_PACK_BF16) || !(D.packs & DD_PACK_FP64))
-        return set_error(DD_ERR_UNSUPPORTED, "BF16 mode needs the BF16 and FP64 packs");
-      break;
-    case DD_MIXED_FP16:
-      if (!(D.packs & DD_PACK_FP16) || !(D.packs & DD_PACK_FP64))
-        return set_error(DD_ERR_UNSUPPORTED, "FP16 mode needs the FP16 and FP64 packs");
-      break;
-    case DD_ANN:
-      if (!(D.packs & DD_PACK_ANN)) return set_error(DD_ERR_UNSUPPORTED, "dataset has no ANN tree");
-      break;
-    case DD_KMEANS:
-      if (!(D.packs & DD_PACK_KMEANS))
-        return set_error(DD_ERR_UNSUPPORTED, "dataset has no k-means tree");
-      break;
-    default:
-      return set_error(DD_ERR_UNSUPPORTED, "projection mode not available");
-  }
-  int cur_dev = -1;
-  DD_HIP(hipGetDevice(&cur_dev));
-  if (cur_dev != D.device) return set_error(DD_ERR_ARG, "dataset lives on another device");
-
+// The projection in `mode`, its options checked (see project_impl_ex).
+static dd_status project_run(const Dataset& D, int mode, const double* states_dev, bool whitened,
+                             int64_t m, const int64_t* warm_start_idx_dev, const dd_project_opts* opts,
+                             int splits, int budget, double fd, int64_t* idx_out_dev,
+                             double* dist_out_dev, double* dist2_out_dev, hipStream_t st,
+                             const float* fd_q, const int* budget_q, ScratchArena* fixed) {
   const bool scan = !walk_mode(mode) && mode != DD_DIRECT_FP64;
   Scratch sc(D, st, fixed);
   DD_TRY(sc.open());
@@ -762,6 +729,79 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
     opts->stats->slow_tiles = n_items_host < 0 ? (int64_t)items : n_items_host;
   }
   return DD_OK;
+}
+
+// As project_impl; dist2_out_dev (exact DD_ANN only) receives the distance to
+// the second nearest point, -1 where it is not certified; fd_q / budget_q
+// (walk modes, device arrays over the m states) give each state its own
+// radius factor and leaf budget; `fixed` (optional) is a caller's reserve that
+// the call carves every temporary buffer from.
+dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool whitened, int64_t m,
+                          const int64_t* warm_start_idx_dev, const dd_project_opts* opts,
+                          int64_t* idx_out_dev, double* dist_out_dev, double* dist2_out_dev,
+                          hipStream_t st, const float* fd_q, const int* budget_q,
+                          ScratchArena* fixed) {
+  if (m < 0 || m > 0x7FFFFFFFll) return set_error(DD_ERR_ARG, "m must be in [0, 2^31-1]");
+  if (m == 0) return DD_OK;
+  if (!states_dev || !idx_out_dev) return set_error(DD_ERR_ARG, "NULL states or idx_out");
+  const int mode = opts ? opts->mode : DD_EXACT_FP64;
+  const int splits = opts ? opts->splits : 0;
+  if (splits < 0) return set_error(DD_ERR_ARG, "splits must be >= 0");
+  const int budget = opts ? opts->ann_budget : 0;
+  if (budget < 0) return set_error(DD_ERR_ARG, "ann_budget must be >= 0");
+  if (opts && (opts->passes < 0 || opts->passes > 2))
+    return set_error(DD_ERR_ARG, "passes must be 0, 1 or 2");
+  const double discount = opts ? opts->ann_radius_discount : 0.0;
+  if (!(discount >= 0.0 && discount <= 1.0))
+    return set_error(DD_ERR_ARG, "ann_radius_discount must be in [0, 1]");
+  const double fd = 1.0 - discount;
+  if (discount > 0.0 && mode != DD_KMEANS)
+    return set_error(DD_ERR_ARG, "ann_radius_discount applies to the k-means walk only");
+  switch (mode) {
+    case DD_EXACT_FP64:
+    case DD_DIRECT_FP64:
+      if (!(D.packs & DD_PACK_FP64)) return set_error(DD_ERR_UNSUPPORTED, "dataset has no FP64 pack");
+      break;
+    case DD_MIXED_FP32:
+      if (!(D.packs & DD_PACK_FP32) || !(D.packs & DD_PACK_FP64))
+        return set_error(DD_ERR_UNSUPPORTED, "FP32 mode needs the FP32 and FP64 packs");
+      break;
+    case DD_MIXED_BF16:
+      if (!(D.packs & DD_PACK_BF16) || !(D.packs & DD_PACK_FP64))
+        return set_error(DD_ERR_UNSUPPORTED, "BF16 mode needs the BF16 and FP64 packs");
+      break;
+    case DD_MIXED_FP16:
+      if (!(D.packs & DD_PACK_FP16) || !(D.packs & DD_PACK_FP64))
+        return set_error(DD_ERR_UNSUPPORTED, "FP16 mode needs the FP16 and FP64 packs");
+      break;
+    case DD_ANN:
+      if (!(D.packs & DD_PACK_ANN)) return set_error(DD_ERR_UNSUPPORTED, "dataset has no ANN tree");
+      break;
+    case DD_KMEANS:
+      if (!(D.packs & DD_PACK_KMEANS))
+        return set_error(DD_ERR_UNSUPPORTED, "dataset has no k-means tree");
+      break;
+    default:
+      return set_error(DD_ERR_UNSUPPORTED, "projection mode not available");
+  }
+  int cur_dev = -1;
+  DD_HIP(hipGetDevice(&cur_dev));
+  if (cur_dev != D.device) return set_error(DD_ERR_ARG, "dataset lives on another device");
+
+  // An exact walk's answers by scan; a call that asks for the walk's statistics
+  // or second distances walks, and so does one in a caller's reserve (sized for
+  // the walk) or for which the scan finds no room.
+  if (walk_mode(mode) && budget == 0 && fd == 1.0 && !fd_q && !budget_q && !dist2_out_dev && !fixed &&
+      !(opts && opts->stats)) {
+    if (const int by = scan_for_walk(D, m)) {
+      const dd_status rc = project_run(D, by, states_dev, whitened, m, warm_start_idx_dev, opts, 0, 0,
+                                       1.0, idx_out_dev, dist_out_dev, nullptr, st, nullptr, nullptr,
+                                       nullptr);
+      if (rc != DD_ERR_OOM && rc != DD_ERR_TOO_LARGE) return rc;
+    }
+  }
+  return project_run(D, mode, states_dev, whitened, m, warm_start_idx_dev, opts, splits, budget, fd,
+                     idx_out_dev, dist_out_dev, dist2_out_dev, st, fd_q, budget_q, fixed);
 }
 
 dd_status project_whitened(const Dataset& D, const double* qw_dev, int64_t m,

@@ -117,12 +117,12 @@ class DDSolver {
   DevBuf d_fdq, d_budq;            // per-point radius factor and leaf budget
   // associations the previous iteration changed (-1 before the first)
   int64_t last_changed = -1;
-  // passes of the 16-bit scans at iteration it: the bound-seeding pass runs
+  // passes of the 16-bit scans (an exact walk may be one) at iteration it: the bound-seeding pass runs
   // beside the warm start while that start is stale (the first iteration, or
   // after an iteration that changed nearly every association); 0 = warm start
   // alone
   int scan_passes(int it) const {
-    if (mode != DD_MIXED_BF16 && mode != DD_MIXED_FP16) return 0;
+    if (mode != DD_MIXED_BF16 && mode != DD_MIXED_FP16 && !walk_mode(mode)) return 0;
     return (it == 1 || last_changed < 0 || 10 * last_changed > 9 * M.n_mp) ? 2 : 0;
   }
   double cg_tol = 1e-13;
