@@ -676,7 +676,8 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
   // 1. statistics pass: finiteness, max |x|, strided sample of whitened rows
   const int64_t ns = std::min<int64_t>(N, 65536);
   const int64_t stride = std::max<int64_t>(1, N / ns);
-  DevBuf dsamp, flag, mx;
+  TempPool pool;
+  TempBuf dsamp(pool), flag(pool), mx(pool), dmom(pool), dext(pool);
   DD_TRY(dsamp.alloc(sizeof(double) * 12 * (size_t)ns));
   DD_TRY(flag.alloc(sizeof(int)));
   DD_TRY(mx.alloc(sizeof(unsigned long long)));
@@ -694,7 +695,6 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
   unsigned long long bitsx = 0;
   DD_HIP(hipMemcpyAsync(&bad, flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
   DD_HIP(hipMemcpyAsync(&bitsx, mx.p, sizeof(bitsx), hipMemcpyDeviceToHost, st));
-  DevBuf dmom;
   DD_TRY(dmom.alloc(sizeof(double) * (12 + 144)));
   hipLaunchKernelGGL(sample_moments_kernel, dim3(1), dim3(kMomThreads), 0, st, dsamp.as<double>(), ns,
                      dmom.as<double>());
@@ -720,7 +720,6 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     std::memcpy(A.axes, P.axes, sizeof(A.axes));
     std::memcpy(A.mean, P.mean, sizeof(A.mean));
     const unsigned nb = grid_for(ns);
-    DevBuf dext;
     DD_TRY(dext.alloc(sizeof(double) * 2 * kKeyAxes * nb));
     hipLaunchKernelGGL(sample_extent_kernel, dim3(nb), dim3(256), 0, st, dsamp.as<double>(), ns, A,
                        dext.as<double>());
@@ -753,7 +752,7 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
 
   // 3. keys pass, stable sort -> permutation and its inverse
   {
-    DevBuf keys;
+    TempBuf keys(pool);
     DD_TRY(keys.alloc(sizeof(uint32_t) * (size_t)N));
     DD_TRY(D.perm.alloc(sizeof(uint32_t) * (size_t)N));
     for (int64_t f = 0; f < N; f += CH) {
@@ -765,7 +764,7 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
       DD_HIP(hipGetLastError());
     }
     DD_TRY(iota_u32(D.perm.as<uint32_t>(), N, st));
-    DD_TRY(radix_sort_pairs(keys.as<uint32_t>(), D.perm.as<uint32_t>(), N, kKeyAxes * bits, st));
+    DD_TRY(radix_sort_pairs(keys.as<uint32_t>(), D.perm.as<uint32_t>(), N, kKeyAxes * bits, pool, st));
     DD_TRY(build_tile_keys(keys.as<uint32_t>(), N, kTile64, D.tkey, st));
   }
   DD_TRY(D.iperm.alloc(sizeof(uint32_t) * (size_t)N));
@@ -865,7 +864,7 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
   }
 
   // 7. k-means tree over the sorted order
-  if (packs & DD_PACK_KMEANS) DD_TRY(build_kmeans_tree(D, st));
+  if (packs & DD_PACK_KMEANS) DD_TRY(build_kmeans_tree(D, pool, st));
   DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }

@@ -54,6 +54,55 @@ struct DevBuf {
   template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
+// Device blocks of one creation's temporaries, all of whose work is on one stream:
+// a TempBuf that ends hands its block back for the next one without waiting (the
+// stream orders the uses), where a hipFree waits for the device and costs with its
+// hipMalloc about 30 us.  Blocks of kLeast are cut from slabs of kKeep; blocks above
+// kKeep are freed at once; the rest goes with the pool, at the end of the creation.
+class TempPool {
+ public:
+  TempPool() = default;
+  TempPool(const TempPool&) = delete;
+  TempPool& operator=(const TempPool&) = delete;
+  ~TempPool();
+  dd_status take(size_t n, void** p, size_t* cap);
+  void put(void* p, size_t cap);
+
+ private:
+  static constexpr size_t kLeast = (size_t)1 << 20, kKeep = (size_t)16 << 20;
+  void trim();
+  std::vector<std::pair<size_t, void*>> idle;   // (size, block)
+  std::vector<void*> slabs;
+};
+
+struct TempBuf {
+  TempPool& pool;
+  void* p = nullptr;
+  size_t bytes = 0, cap = 0;
+  explicit TempBuf(TempPool& t) : pool(t) {}
+  TempBuf(const TempBuf&) = delete;
+  TempBuf& operator=(const TempBuf&) = delete;
+  ~TempBuf() { release(); }
+  dd_status alloc(size_t n) {
+    release();
+    if (n == 0) return DD_OK;
+    const dd_status rc = pool.take(n, &p, &cap);
+    if (rc == DD_OK) bytes = n;
+    return rc;
+  }
+  void release() {
+    if (p) pool.put(p, cap);
+    p = nullptr;
+    bytes = cap = 0;
+  }
+  void swap(TempBuf& o) {
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
+    std::swap(cap, o.cap);
+  }
+  template <class T> T* as() const { return static_cast<T*>(p); }
+};
+
 // ---------------------------------------------------------------------------
 // Small dense linear algebra on the host (6x6 / 12x12)
 // ---------------------------------------------------------------------------
@@ -232,7 +281,7 @@ dd_status build_tile_keys(const uint32_t* sorted_keys, int64_t N, int rows, DevB
 void choose_group_cells(Dataset& D);
 
 // Builds the k-means tree of DD_PACK_KMEANS over D's sorted FP64 pack.
-dd_status build_kmeans_tree(Dataset& D, hipStream_t st);
+dd_status build_kmeans_tree(Dataset& D, TempPool& pool, hipStream_t st);
 
 }  // namespace dd
 

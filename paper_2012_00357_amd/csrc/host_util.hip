@@ -35,6 +35,71 @@ void DevBuf::release() {
   owned = true;
 }
 
+dd_status TempPool::take(size_t n, void** p, size_t* cap) {
+  auto best = idle.end();
+  for (auto it = idle.begin(); it != idle.end(); ++it)
+    if (it->first >= n && (best == idle.end() || it->first < best->first)) best = it;
+  if (best != idle.end()) {
+    *cap = best->first;
+    *p = best->second;
+    idle.erase(best);
+    return DD_OK;
+  }
+  if (n <= kLeast) {
+    void* slab = nullptr;
+    if (hipMalloc(&slab, kKeep) == hipSuccess) {
+      slabs.push_back(slab);
+      for (size_t o = kLeast; o < kKeep; o += kLeast)
+        idle.emplace_back(kLeast, static_cast<char*>(slab) + o);
+      *p = slab;
+      *cap = kLeast;
+      return DD_OK;
+    }
+    (void)hipGetLastError();
+  }
+  size_t size = n;
+  if (n <= kKeep)
+    for (size = 2 * kLeast; size < n;) size *= 2;
+  hipError_t e = hipMalloc(p, size);
+  if (e != hipSuccess) {   // without the idle blocks, and no more than was asked for
+    (void)hipGetLastError();
+    trim();
+    size = n == kLeast ? n + 1 : n;   // kLeast marks a slab's blocks
+    e = hipMalloc(p, size);
+  }
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+    return set_error(e == hipErrorOutOfMemory ? DD_ERR_OOM : DD_ERR_DEVICE,
+                     std::string("hipMalloc(") + std::to_string(n) + "): " + hipGetErrorString(e));
+  }
+  *cap = size;
+  return DD_OK;
+}
+
+void TempPool::put(void* p, size_t cap) {
+  if (cap > kKeep)
+    (void)hipFree(p);
+  else
+    idle.emplace_back(cap, p);
+}
+
+void TempPool::trim() {   // the blocks that are no part of a slab
+  size_t kept = 0;
+  for (auto& b : idle) {
+    if (b.first == kLeast)
+      idle[kept++] = b;
+    else
+      (void)hipFree(b.second);
+  }
+  idle.resize(kept);
+}
+
+TempPool::~TempPool() {
+  trim();
+  for (void* s : slabs) (void)hipFree(s);
+}
+
 ScratchArena::~ScratchArena() {
   // the last user's work on the block must end before the block is freed
   if (done) (void)hipEventSynchronize(done);

@@ -300,40 +300,40 @@ __device__ inline int splits_to_leaves(uint32_t n) {
 // position), while o's frontier stays within kFan entries (a split replaces one
 // entry by its non-empty children), and become stored nodes when it would not.
 // frontier[o] counts the entries of o.
-__global__ void decide_kernel(Segs G, int64_t S, const uint32_t* __restrict__ okey,
-                              const uint32_t* __restrict__ oidx, const uint32_t* __restrict__ ccnt,
-                              uint32_t* __restrict__ frontier, uint32_t* __restrict__ store_f) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per run, an entry per lane (a thread per run, with its entries in
+// scratch memory and a quadratic ranking, took 190 us a round; 7 now).
+__global__ __launch_bounds__(256) void decide_kernel(Segs G, int64_t S, const uint32_t* __restrict__ okey,
+                                                     const uint32_t* __restrict__ oidx,
+                                                     const uint32_t* __restrict__ ccnt,
+                                                     uint32_t* __restrict__ frontier,
+                                                     uint32_t* __restrict__ store_f) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= S) return;
   const uint32_t o = okey[i];
   if (i > 0 && okey[i - 1] == o) return;   // not the first of its run
-  int n = 1;
-  while (i + n < S && n < kFan && okey[i + n] == o) ++n;
-  uint32_t seg[kFan], size[kFan];
-  uint8_t order[kFan];
-  for (int t = 0; t < n; ++t) {
-    seg[t] = oidx[i + t];
-    size[t] = G.cnt[seg[t]];
-  }
-  for (int t = 0; t < n; ++t) {
-    int rank = 0;
-    for (int u = 0; u < n; ++u)
-      rank += (size[u] < size[t] || (size[u] == size[t] && seg[u] < seg[t])) ? 1 : 0;
-    order[rank] = (uint8_t)t;
+  const bool v = i + lane < S && okey[min(i + lane, S - 1)] == o;
+  const int n = __popcll(__ballot(v));     // kFan = 64 lanes
+  const uint32_t seg = v ? oidx[i + lane] : 0xFFFFFFFFu;
+  const uint32_t size = v ? G.cnt[seg] : 0xFFFFFFFFu;
+  int c = 0;
+  if (v)
+    for (int j = 0; j < kK; ++j) c += ccnt[(int64_t)seg * kK + j] > 0 ? 1 : 0;
+  const int absorb = v && splits_to_leaves(size) % 3 != 0 ? 1 : 0;
+  int rank = 0;
+  for (int u = 0; u < n; ++u) {
+    const uint32_t su = __shfl(size, u), gu = __shfl(seg, u);
+    rank += (su < size || (su == size && gu < seg)) ? 1 : 0;
   }
   int budget = kFan - (int)frontier[o];
   for (int r = 0; r < n; ++r) {
-    const int64_t s = seg[order[r]];
-    int c = 0;
-    for (int j = 0; j < kK; ++j) c += ccnt[s * kK + j] > 0 ? 1 : 0;
-    if (splits_to_leaves(size[order[r]]) % 3 != 0 && c - 1 <= budget) {
-      budget -= c - 1;
-      store_f[s] = 0u;
-    } else {
-      store_f[s] = 1u;
-    }
+    const int at = __ffsll((long long)__ballot(v && rank == r)) - 1;
+    const int cr = __shfl(c, at), ar = __shfl(absorb, at);
+    const bool in = ar && cr - 1 <= budget;
+    if (in) budget -= cr - 1;
+    if (lane == at) store_f[seg] = in ? 0u : 1u;
   }
-  frontier[o] = (uint32_t)(kFan - budget);
+  if (lane == 0) frontier[o] = (uint32_t)(kFan - budget);
 }
 
 // Frontier sizes of the nodes stored this round: their non-empty children.
@@ -353,8 +353,8 @@ __global__ void new_frontier_kernel(int64_t S, const uint32_t* __restrict__ ccnt
 __global__ void children_kernel(int64_t S, const uint32_t* __restrict__ ccnt,
                                 uint32_t* __restrict__ leaf_f, uint32_t* __restrict__ act_f) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= S * kK) return;
-  const uint32_t n = ccnt[i];
+  if (i > S * kK) return;
+  const uint32_t n = i < S * kK ? ccnt[i] : 0u;   // one entry more: the scans' totals
   leaf_f[i] = (n > 0 && n <= (uint32_t)kAnnLeaf) ? 1u : 0u;
   act_f[i] = (n > (uint32_t)kAnnLeaf) ? 1u : 0u;
 }
@@ -643,44 +643,39 @@ __global__ void node_range_kernel(const uint32_t* __restrict__ owner, int64_t n,
 }
 
 // Growable device array (contents kept).
-dd_status grow(DevBuf& b, size_t bytes, hipStream_t st) {
+dd_status grow(TempBuf& b, size_t bytes, hipStream_t st) {
   if (b.bytes >= bytes) return DD_OK;
-  DevBuf n;
+  TempBuf n(b.pool);
   DD_TRY(n.alloc(std::max(bytes, 2 * b.bytes)));
   if (b.bytes) DD_HIP(hipMemcpyAsync(n.p, b.p, b.bytes, hipMemcpyDeviceToDevice, st));
-  DD_HIP(hipStreamSynchronize(st));
-  std::swap(b.p, n.p);
-  std::swap(b.bytes, n.bytes);
+  b.swap(n);
   return DD_OK;
 }
 
 struct SegBufs {
-  DevBuf start, cnt, owner, mean, k;
+  TempBuf buf;
+  int64_t n = 1;
+  explicit SegBufs(TempPool& pool) : buf(pool) {}
   dd_status alloc(int64_t S) {
-    const size_t n = (size_t)std::max<int64_t>(S, 1);
-    DD_TRY(start.alloc(4 * n));
-    DD_TRY(cnt.alloc(4 * n));
-    DD_TRY(owner.alloc(4 * n));
-    DD_TRY(mean.alloc(4 * 12 * n));
-    DD_TRY(k.alloc(4 * n));
-    return DD_OK;
+    n = std::max<int64_t>(S, 1);
+    return buf.alloc(4 * 16 * (size_t)n);
   }
   Segs view() {
-    return Segs{start.as<uint32_t>(), cnt.as<uint32_t>(), owner.as<uint32_t>(), mean.as<float>(),
-                k.as<int>()};
+    uint32_t* p = buf.as<uint32_t>();
+    return Segs{p, p + n, p + 2 * n, reinterpret_cast<float*>(p + 4 * n), reinterpret_cast<int*>(p + 3 * n)};
   }
 };
 
-uint32_t read_u32(const uint32_t* p, hipStream_t st) {
-  uint32_t v = 0;
-  (void)hipMemcpyAsync(&v, p, sizeof(v), hipMemcpyDeviceToHost, st);
-  (void)hipStreamSynchronize(st);
-  return v;
+// Chunks of each node (at most kChunk positions each); entry S is the total's place.
+__global__ void chunk_count_kernel(const uint32_t* __restrict__ cnt, int64_t S,
+                                   uint32_t* __restrict__ cbase) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s <= S) cbase[s] = s < S ? (cnt[s] + (uint32_t)kChunk - 1) / (uint32_t)kChunk : 0u;
 }
 
 }  // namespace
 
-dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
+dd_status build_kmeans_tree(Dataset& D, TempPool& pool, hipStream_t st) {
   const int64_t N = D.N;
   if (N > 0xFFFFFFFFll) return set_error(DD_ERR_TOO_LARGE, "k-means tree: N exceeds 2^32-1");
   // fixed-point scale of the centroid sums: |sum| <= N xmax 2^e < 2^62
@@ -695,7 +690,8 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
   Axes R;
   std::memcpy(R.V, D.V, sizeof(R.V));
 
-  DevBuf ids[2], labels, leaves_b, recs, rec_owner, frontier;
+  TempBuf ids[2] = {TempBuf(pool), TempBuf(pool)}, labels(pool), leaves_b(pool), recs(pool),
+          rec_owner(pool), frontier(pool);
   DD_TRY(ids[0].alloc(4 * (size_t)N));
   DD_TRY(ids[1].alloc(4 * (size_t)N));
   DD_TRY(labels.alloc((size_t)N));
@@ -703,8 +699,10 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
   int cur = 0;
   int64_t n_leaf = 0, n_rec = 0, n_nodes = 1;
 
-  SegBufs segs;
+  SegBufs segs(pool);
   int64_t S = 0;
+  // the round's totals, read back together: stored nodes, leaves, next nodes
+  uint32_t totals[3];
   if (N <= kAnnLeaf) {
     DD_TRY(grow(leaves_b, sizeof(LeafRec), st));
     LeafRec r{0u, (uint32_t)N, 0u, 0u};
@@ -719,10 +717,11 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
     DD_HIP(hipMemcpyAsync(frontier.p, &one, 4, hipMemcpyHostToDevice, st));
     const uint32_t z = 0, n = (uint32_t)N;
     const int k = (int)std::min<int64_t>(kK, (N + kAnnLeaf - 1) / kAnnLeaf);
-    DD_HIP(hipMemcpyAsync(segs.start.p, &z, 4, hipMemcpyHostToDevice, st));
-    DD_HIP(hipMemcpyAsync(segs.cnt.p, &n, 4, hipMemcpyHostToDevice, st));
-    DD_HIP(hipMemcpyAsync(segs.owner.p, &z, 4, hipMemcpyHostToDevice, st));
-    DD_HIP(hipMemcpyAsync(segs.k.p, &k, 4, hipMemcpyHostToDevice, st));
+    const Segs g = segs.view();
+    DD_HIP(hipMemcpyAsync(g.start, &z, 4, hipMemcpyHostToDevice, st));
+    DD_HIP(hipMemcpyAsync(g.cnt, &n, 4, hipMemcpyHostToDevice, st));
+    DD_HIP(hipMemcpyAsync(g.owner, &z, 4, hipMemcpyHostToDevice, st));
+    DD_HIP(hipMemcpyAsync(g.k, &k, 4, hipMemcpyHostToDevice, st));
   }
 
   int round = 0;
@@ -731,26 +730,16 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
     if (round >= kMaxRounds) return set_error(DD_ERR_TOO_LARGE, "k-means tree too deep");
     Segs G = segs.view();
     // chunks of at most kChunk positions per node
-    DevBuf cbase_b, cent_b, acc_b, ccnt_b, cmean_b, forced_b, rad_b;
+    TempBuf cbase_b(pool), cent_b(pool), acc_b(pool), ccnt_b(pool), cmean_b(pool), forced_b(pool),
+        rad_b(pool);
     DD_TRY(cbase_b.alloc(4 * (size_t)(S + 1)));
-    // first chunk of every node (ceil(cnt / kChunk) chunks each); entry S: total
+    // first chunk of every node; entry S: total (at most N / kChunk + S < 2^31)
+    hipLaunchKernelGGL(chunk_count_kernel, dim3(grid_of(S + 1, 256)), dim3(256), 0, st, G.cnt, S,
+                       cbase_b.as<uint32_t>());
+    DD_TRY(exclusive_scan_u32(cbase_b.as<uint32_t>(), S + 1, pool, st));
     uint32_t n_chunks = 0;
-    {
-      std::vector<uint32_t> cnt((size_t)S);
-      DD_HIP(hipMemcpyAsync(cnt.data(), G.cnt, 4 * (size_t)S, hipMemcpyDeviceToHost, st));
-      DD_HIP(hipStreamSynchronize(st));
-      std::vector<uint32_t> base((size_t)S + 1);
-      uint64_t acc = 0;
-      for (int64_t s = 0; s < S; ++s) {
-        base[(size_t)s] = (uint32_t)acc;
-        acc += (cnt[(size_t)s] + (uint64_t)kChunk - 1) / kChunk;
-      }
-      base[(size_t)S] = (uint32_t)acc;
-      if (acc > 0x7FFFFFFFull) return set_error(DD_ERR_TOO_LARGE, "k-means tree: too many chunks");
-      n_chunks = (uint32_t)acc;
-      DD_HIP(hipMemcpyAsync(cbase_b.p, base.data(), 4 * ((size_t)S + 1), hipMemcpyHostToDevice, st));
-      DD_HIP(hipStreamSynchronize(st));
-    }
+    DD_HIP(hipMemcpyAsync(&n_chunks, cbase_b.as<uint32_t>() + S, 4, hipMemcpyDeviceToHost, st));
+    DD_HIP(hipStreamSynchronize(st));
     const uint32_t* cbase = cbase_b.as<uint32_t>();
     DD_TRY(cent_b.alloc(4 * 12 * kK * (size_t)S));
     DD_TRY(acc_b.alloc(8 * kAcc * (size_t)S));
@@ -802,34 +791,47 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
     DD_HIP(hipGetLastError());
 
     // frontier budgets: which of this round's nodes become stored nodes
-    DevBuf store_f, store_at;
-    DD_TRY(store_f.alloc(4 * (size_t)S));
-    DD_TRY(store_at.alloc(4 * (size_t)S));
+    TempBuf store_f(pool), store_at(pool);
+    DD_TRY(store_f.alloc(4 * (size_t)(S + 1)));   // one more: the scan's total
+    DD_TRY(store_at.alloc(4 * (size_t)(S + 1)));
     DD_HIP(hipMemsetAsync(store_f.p, 0, store_f.bytes, st));
     {
-      DevBuf okey, oidx;
+      TempBuf okey(pool), oidx(pool);
       DD_TRY(okey.alloc(4 * (size_t)S));
       DD_TRY(oidx.alloc(4 * (size_t)S));
       DD_HIP(hipMemcpyAsync(okey.p, G.owner, 4 * (size_t)S, hipMemcpyDeviceToDevice, st));
       DD_TRY(iota_u32(oidx.as<uint32_t>(), S, st));
       int obits = 1;
       while (obits < 32 && (1ll << obits) < n_nodes) ++obits;
-      DD_TRY(radix_sort_pairs(okey.as<uint32_t>(), oidx.as<uint32_t>(), S, obits, st));
-      hipLaunchKernelGGL(decide_kernel, dim3(grid_of(S, 256)), dim3(256), 0, st, G, S,
+      DD_TRY(radix_sort_pairs(okey.as<uint32_t>(), oidx.as<uint32_t>(), S, obits, pool, st));
+      hipLaunchKernelGGL(decide_kernel, dim3(grid_of(S, 4)), dim3(256), 0, st, G, S,
                          okey.as<uint32_t>(), oidx.as<uint32_t>(), ccnt_b.as<uint32_t>(),
                          frontier.as<uint32_t>(), store_f.as<uint32_t>());
       DD_HIP(hipGetLastError());
-      DD_HIP(hipStreamSynchronize(st));
     }
-    DD_HIP(hipGetLastError());
     DD_HIP(hipMemcpyAsync(store_at.p, store_f.p, store_f.bytes, hipMemcpyDeviceToDevice, st));
-    DD_TRY(exclusive_scan_u32(store_at.as<uint32_t>(), S, st));
-    const int64_t n_store = (int64_t)read_u32(store_at.as<uint32_t>() + S - 1, st) +
-                            (int64_t)read_u32(store_f.as<uint32_t>() + S - 1, st);
+    DD_TRY(exclusive_scan_u32(store_at.as<uint32_t>(), S + 1, pool, st));
+    // leaves and next round's nodes among the children
+    TempBuf leaf_f(pool), leaf_at(pool), act_f(pool), act_at(pool);
+    const int64_t SK = S * kK;
+    for (TempBuf* f : {&leaf_f, &leaf_at, &act_f, &act_at}) DD_TRY(f->alloc(4 * (size_t)(SK + 1)));
+    hipLaunchKernelGGL(children_kernel, dim3(grid_of(SK + 1, 256)), dim3(256), 0, st, S,
+                       ccnt_b.as<uint32_t>(), leaf_f.as<uint32_t>(), act_f.as<uint32_t>());
+    DD_HIP(hipGetLastError());
+    DD_HIP(hipMemcpyAsync(leaf_at.p, leaf_f.p, leaf_f.bytes, hipMemcpyDeviceToDevice, st));
+    DD_HIP(hipMemcpyAsync(act_at.p, act_f.p, act_f.bytes, hipMemcpyDeviceToDevice, st));
+    DD_TRY(exclusive_scan_u32(leaf_at.as<uint32_t>(), SK + 1, pool, st));
+    DD_TRY(exclusive_scan_u32(act_at.as<uint32_t>(), SK + 1, pool, st));
+    const uint32_t* ends[3] = {store_at.as<uint32_t>() + S, leaf_at.as<uint32_t>() + SK,
+                               act_at.as<uint32_t>() + SK};
+    for (int i = 0; i < 3; ++i)
+      DD_HIP(hipMemcpyAsync(&totals[i], ends[i], 4, hipMemcpyDeviceToHost, st));
+    DD_HIP(hipStreamSynchronize(st));
+    const int64_t n_store = totals[0], new_leaves = totals[1], S2 = totals[2];
     const uint32_t node_base = (uint32_t)n_nodes;
     if (n_store > 0) {
       // their balls and boxes become child records of their owners
-      DevBuf kblo, kbhi;
+      TempBuf kblo(pool), kbhi(pool);
       DD_TRY(rad_b.alloc(8 * (size_t)S));
       DD_TRY(kblo.alloc(4 * 12 * (size_t)S));
       DD_TRY(kbhi.alloc(4 * 12 * (size_t)S));
@@ -857,12 +859,12 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
 
     // stable partition of every node by child
     {
-      DevBuf H;
+      TempBuf H(pool);
       DD_TRY(H.alloc(4 * 4 * (size_t)n_chunks));
       hipLaunchKernelGGL(hist_kernel, dim3(n_chunks), dim3(kThreads), 0, st, G, S, cbase,
                          forced_b.as<uint8_t>(), labels.as<uint8_t>(), H.as<uint32_t>());
       DD_HIP(hipGetLastError());
-      DD_TRY(exclusive_scan_u32(H.as<uint32_t>(), 4 * (int64_t)n_chunks, st));
+      DD_TRY(exclusive_scan_u32(H.as<uint32_t>(), 4 * (int64_t)n_chunks, pool, st));
       DD_HIP(hipMemcpyAsync(ids[1 - cur].p, ids[cur].p, 4 * (size_t)N, hipMemcpyDeviceToDevice, st));
       hipLaunchKernelGGL(scatter_kernel, dim3(n_chunks), dim3(kThreads), 0, st, G, S, cbase,
                          forced_b.as<uint8_t>(), labels.as<uint8_t>(), H.as<uint32_t>(), ids_in,
@@ -872,25 +874,8 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
     }
 
     // leaves and next round's nodes
-    DevBuf leaf_f, leaf_at, act_f, act_at;
-    const int64_t SK = S * kK;
-    DD_TRY(leaf_f.alloc(4 * (size_t)SK));
-    DD_TRY(leaf_at.alloc(4 * (size_t)SK));
-    DD_TRY(act_f.alloc(4 * (size_t)SK));
-    DD_TRY(act_at.alloc(4 * (size_t)SK));
-    hipLaunchKernelGGL(children_kernel, dim3(grid_of(SK, 256)), dim3(256), 0, st, S,
-                       ccnt_b.as<uint32_t>(), leaf_f.as<uint32_t>(), act_f.as<uint32_t>());
-    DD_HIP(hipGetLastError());
-    DD_HIP(hipMemcpyAsync(leaf_at.p, leaf_f.p, leaf_f.bytes, hipMemcpyDeviceToDevice, st));
-    DD_HIP(hipMemcpyAsync(act_at.p, act_f.p, act_f.bytes, hipMemcpyDeviceToDevice, st));
-    DD_TRY(exclusive_scan_u32(leaf_at.as<uint32_t>(), SK, st));
-    DD_TRY(exclusive_scan_u32(act_at.as<uint32_t>(), SK, st));
-    const int64_t new_leaves = (int64_t)read_u32(leaf_at.as<uint32_t>() + SK - 1, st) +
-                               (int64_t)read_u32(leaf_f.as<uint32_t>() + SK - 1, st);
-    const int64_t S2 = (int64_t)read_u32(act_at.as<uint32_t>() + SK - 1, st) +
-                       (int64_t)read_u32(act_f.as<uint32_t>() + SK - 1, st);
     DD_TRY(grow(leaves_b, sizeof(LeafRec) * (size_t)(n_leaf + new_leaves), st));
-    SegBufs next;
+    SegBufs next(pool);
     DD_TRY(next.alloc(S2));
     hipLaunchKernelGGL(compact_kernel, dim3(grid_of(SK, 256)), dim3(256), 0, st, G, S,
                        ccnt_b.as<uint32_t>(), cmean_b.as<float>(), leaf_f.as<uint32_t>(),
@@ -898,18 +883,9 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
                        store_f.as<uint32_t>(), store_at.as<uint32_t>(), node_base,
                        leaves_b.as<LeafRec>(), n_leaf, next.view());
     DD_HIP(hipGetLastError());
-    DD_HIP(hipStreamSynchronize(st));
     n_leaf += new_leaves;
-    std::swap(segs.start.p, next.start.p);
-    std::swap(segs.start.bytes, next.start.bytes);
-    std::swap(segs.cnt.p, next.cnt.p);
-    std::swap(segs.cnt.bytes, next.cnt.bytes);
-    std::swap(segs.owner.p, next.owner.p);
-    std::swap(segs.owner.bytes, next.owner.bytes);
-    std::swap(segs.mean.p, next.mean.p);
-    std::swap(segs.mean.bytes, next.mean.bytes);
-    std::swap(segs.k.p, next.k.p);
-    std::swap(segs.k.bytes, next.k.bytes);
+    segs.buf.swap(next.buf);
+    std::swap(segs.n, next.n);
     S = S2;
     ++round;
   }
@@ -933,13 +909,13 @@ dd_status build_kmeans_tree(Dataset& D, hipStream_t st) {
   n_rec += n_leaf;
 
   // child records grouped by owner (stable), node ranges
-  DevBuf order;
+  TempBuf order(pool);
   DD_TRY(order.alloc(4 * (size_t)n_rec));
   DD_TRY(iota_u32(order.as<uint32_t>(), n_rec, st));
   int bits = 1;
   while (bits < 32 && (1ll << bits) < n_nodes) ++bits;
-  DD_TRY(radix_sort_pairs(rec_owner.as<uint32_t>(), order.as<uint32_t>(), n_rec, bits, st));
-  DevBuf full;
+  DD_TRY(radix_sort_pairs(rec_owner.as<uint32_t>(), order.as<uint32_t>(), n_rec, bits, pool, st));
+  TempBuf full(pool);
   DD_TRY(full.alloc(4 * kKmtBuild * (size_t)n_rec));
   hipLaunchKernelGGL(gather_records_kernel, dim3(grid_of(kKmtBuild * n_rec, 256)), dim3(256), 0, st,
                      recs.as<float>(), order.as<uint32_t>(), n_rec, full.as<float>());

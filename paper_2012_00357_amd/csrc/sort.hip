@@ -144,9 +144,9 @@ __global__ void iota_kernel(uint32_t* __restrict__ v, int64_t n) {
   if (i < n) v[i] = (uint32_t)i;
 }
 
-dd_status exclusive_scan_u32(uint32_t* a, int64_t n, hipStream_t st) {
+dd_status exclusive_scan_u32(uint32_t* a, int64_t n, TempPool& pool, hipStream_t st) {
   int64_t nb = (n + kScanChunk - 1) / kScanChunk;
-  DevBuf sums;
+  TempBuf sums(pool);
   DD_TRY(sums.alloc(sizeof(uint32_t) * (size_t)(nb > 0 ? nb : 1)));
   hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, n,
                      sums.as<uint32_t>());
@@ -154,16 +154,15 @@ dd_status exclusive_scan_u32(uint32_t* a, int64_t n, hipStream_t st) {
   hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, n,
                      sums.as<uint32_t>());
   DD_HIP(hipGetLastError());
-  DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }
 
-dd_status radix_sort_pairs(uint32_t* keys, uint32_t* vals, int64_t n, int key_bits,
+dd_status radix_sort_pairs(uint32_t* keys, uint32_t* vals, int64_t n, int key_bits, TempPool& pool,
                            hipStream_t st) {
   if (n <= 1) return DD_OK;
   if (n > 0xFFFFFFFFll) return set_error(DD_ERR_TOO_LARGE, "radix sort: n exceeds 2^32-1");
   int64_t n_blocks = (n + kSortChunk - 1) / kSortChunk;
-  DevBuf k2, v2, hist;
+  TempBuf k2(pool), v2(pool), hist(pool);
   DD_TRY(k2.alloc(sizeof(uint32_t) * (size_t)n));
   DD_TRY(v2.alloc(sizeof(uint32_t) * (size_t)n));
   DD_TRY(hist.alloc(sizeof(uint32_t) * 256 * (size_t)n_blocks));
@@ -174,7 +173,7 @@ dd_status radix_sort_pairs(uint32_t* keys, uint32_t* vals, int64_t n, int key_bi
     hipLaunchKernelGGL(radix_hist_kernel, dim3((unsigned)n_blocks), dim3(kSortThreads), 0, st, ka,
                        n, shift, hist.as<uint32_t>(), n_blocks);
     DD_HIP(hipGetLastError());
-    DD_TRY(exclusive_scan_u32(hist.as<uint32_t>(), 256 * n_blocks, st));
+    DD_TRY(exclusive_scan_u32(hist.as<uint32_t>(), 256 * n_blocks, pool, st));
     hipLaunchKernelGGL(radix_scatter_kernel, dim3((unsigned)n_blocks), dim3(kSortThreads), 0, st,
                        ka, va, n, shift, hist.as<uint32_t>(), n_blocks, kb, vb);
     DD_HIP(hipGetLastError());
@@ -185,7 +184,6 @@ dd_status radix_sort_pairs(uint32_t* keys, uint32_t* vals, int64_t n, int key_bi
     DD_HIP(hipMemcpyAsync(keys, ka, sizeof(uint32_t) * (size_t)n, hipMemcpyDeviceToDevice, st));
     DD_HIP(hipMemcpyAsync(vals, va, sizeof(uint32_t) * (size_t)n, hipMemcpyDeviceToDevice, st));
   }
-  DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }
 
