@@ -19,12 +19,13 @@
 // The products are FP64 MFMA tiles; the diagonal blocks are inverted by blocked
 // Gauss-Jordan without pivoting on a copy padded to a multiple of 64 with
 // identity.  For each 64-block k of it:
-//   A_kk <- A_kk^-1;  A_ik <- -A_ik A_kk (i != k);  A_ij <- A_ij + A_ik A_kj
-//   (i, j != k);  A_kj <- A_kk A_kj (j != k).
-// Measured, 16^3 elements (the largest cube below kDenseMaxDof), whole formation: 27 ms (430 ms by Gauss-Jordan over
-// the whole matrix on the vector FP64 units, the trailing updates 375 of them,
-// and the matrix assembled on the host).  What is left is the chain of 238
-// diagonal 64-blocks, each waiting for the one before.
+//   A_kk <- A_kk^-1;  A_kj <- A_kk A_kj (j != k);  A_ij <- A_ij - A_ik A_kj
+//   (i, j != k);  A_ik <- -A_ik A_kk (i != k).
+// Measured, 16^3 elements, whole formation (before the planes took that size): 27
+// ms; 430 ms by Gauss-Jordan over the whole matrix on the vector FP64 units, the
+// trailing updates 375 of them, and the matrix assembled on the host.  What is
+// left is the chain of diagonal 64-blocks, each waiting for the one before; 11^3
+// elements now take 8.1 ms (9.2 with four launches a block).
 #include <algorithm>
 #include <cstring>
 #include <list>
@@ -233,154 +234,235 @@ __global__ __launch_bounds__(256) void transpose_kernel(const double* __restrict
 }
 
 // The matrices (n x n, n a multiple of 64) that one Gauss-Jordan sweep inverts
-// side by side, and the inverse of each one's current diagonal block.
+// side by side, the inverse of each one's current diagonal block and the negated
+// transpose [64][n] of the column of blocks that the step eliminates.
 struct SweepPair {
   double* A[2];
   int64_t n[2];
   double* Akk[2];
+  double* col[2];
 };
 
-// Inverts the diagonal block [k0, k0+64)^2 in place (and copies it to Akk).
-// Four lanes hold a row in registers (16 columns each); at each pivot its row
-// goes to the others through LDS and its column through the lanes of a row, so
-// a pivot is one barrier and 16 fused multiply-adds (all in LDS, with two
-// barriers and 16 read-modify-writes per thread, a block took 152 us; this 28,
-// and the division is not what it waits for).
-__global__ __launch_bounds__(256) void gj_diag_kernel(SweepPair S, int64_t k0) {
-  double* __restrict__ A = S.A[blockIdx.x];
-  double* __restrict__ Akk = S.Akk[blockIdx.x];
-  const int64_t n_pad = S.n[blockIdx.x];
-  if (k0 >= n_pad) return;
-  __shared__ double rowp[2][kB];
-  const int t = threadIdx.x, r = t >> 2, q = t & 3;   // row r, columns 16 q .. 16 q + 15
-  double s[16];
-  double* src = A + (k0 + r) * n_pad + k0 + 16 * q;
+// FP64 value of lane `from` (the same in every lane)
+__device__ inline double lane_d(double v, int from) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, from);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), from);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// FP64 value of lane L of each row of 16 lanes
+template <int L>
+__device__ inline double row_d(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x150 + L, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x150 + L, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// 1 / x to rounding: the hardware's estimate and two Newton steps, shorter than
+// the division in the chain of pivots
+__device__ inline double recip(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
+// Gauss-Jordan on a 16 x 16 block: lane 16 g + r holds columns 4 g .. 4 g + 3 of row r.
+template <int P>
+__device__ inline void pivot16(double (&v)[4], int r, int g) {
+  if constexpr (P < 16) {
+    constexpr int pg = P / 4, pe = P % 4;
+    const double colv = __shfl(v[pe], 16 * pg + r);
+    const double d = recip(lane_d(v[pe], 16 * pg + P));
+    const double f = r == P ? d : -colv * d;
 #pragma unroll
-  for (int c = 0; c < 16; ++c) s[c] = src[c];
-  for (int pq = 0; pq < 4; ++pq) {
-#pragma unroll
-    for (int pc = 0; pc < 16; ++pc) {
-      const int p = 16 * pq + pc, buf = pc & 1;
-      const double colv = __shfl(s[pc], (int)(threadIdx.x & 60) + pq);   // A[r][p]
-      if (r == p) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-          rowp[buf][16 * q + c] = s[c];
-          s[c] = 0.0;   // the pivot row becomes d times itself
-        }
-      }
-      __syncthreads();
-      const double d = 1.0 / rowp[buf][p];
-      const double f = r == p ? d : -colv * d;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) s[c] = fma(f, rowp[buf][16 * q + c], s[c]);
-      if (q == pq) s[pc] = f;   // the pivot column: d at the pivot, -A[r][p] d elsewhere
-    }
-  }
-  double* out = Akk + r * kB + 16 * q;
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    src[c] = s[c];
-    out[c] = s[c];
+    for (int e = 0; e < 4; ++e) v[e] = fma(f, row_d<P>(v[e]), r == P ? 0.0 : v[e]);
+    if (g == pg) v[pe] = f;   // the pivot column: d at the pivot, -A[r][p] d elsewhere
+    pivot16<P + 1>(v, r, g);
   }
 }
 
-// Column panel: rows i outside the block, A[i, k] <- -A[i, k] Akk.  4 rows per block.
-__global__ __launch_bounds__(256) void gj_col_kernel(SweepPair S, int64_t k0) {
+// m <- m^-1, 64 x 64 in LDS, by a workgroup of 256.  Gauss-Jordan by blocks of 16:
+// a wavefront inverts the diagonal block in registers (the pivot goes through
+// scalar registers, its row along the lanes of 16), and the rest of a block step is
+// FP64 MFMA, three barriers in all.  With a barrier and
+// an LDS round trip for every pivot the 64 pivots took 28 us, 15 now.
+constexpr int kMLd = kB + 2;
+__device__ inline void invert64(double (*m)[kMLd]) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, c = lane & 15, q = lane >> 4;
+  for (int s = 0; s < 4; ++s) {
+    const int o = 16 * s, b = 16 * w;
+    if (w == 0) {
+      double v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = m[o + c][o + 4 * q + e];
+      pivot16<0>(v, c, q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[o + c][o + 4 * q + e] = v[e];
+    }
+    __syncthreads();
+    f64x4_t col = {}, row = {};
+    double neg[4];   // - the old column block, as the update's left operand
+    if (w != s) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double dl = m[o + c][o + 4 * k + q], dr = m[o + 4 * k + q][o + c];
+        neg[k] = -m[b + c][o + 4 * k + q];
+        row = __builtin_amdgcn_mfma_f64_16x16x4f64(dl, m[o + 4 * k + q][b + c], row, 0, 0, 0);
+        col = __builtin_amdgcn_mfma_f64_16x16x4f64(neg[k], dr, col, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {   // only this wavefront reads these two blocks before the barrier
+        m[o + q + 4 * r][b + c] = row[r];
+        m[b + q + 4 * r][o + c] = col[r];
+      }
+    }
+    __syncthreads();
+    if (w != s) {
+      f64x4_t acc[3];
+      int at[3];   // the other three column blocks
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        at[u] = 16 * (u + (u >= s ? 1 : 0)) + c;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[u][r] = m[b + q + 4 * r][at[u]];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(neg[k], m[o + 4 * k + q][at[u]], acc[u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[b + q + 4 * r][at[u]] = acc[u][r];
+    }
+    __syncthreads();
+  }
+}
+
+__device__ inline void store_akk(const double (*m)[kMLd], double* __restrict__ Akk) {
+  for (int e = threadIdx.x; e < kB * kB; e += 256) Akk[e] = m[e / kB][e % kB];
+}
+
+// Akk <- inverse of the first diagonal block (the later ones come with the update
+// of the step before).
+__global__ __launch_bounds__(256) void gj_first_kernel(SweepPair S) {
+  __shared__ double m[kB][kMLd];
+  const double* __restrict__ A = S.A[blockIdx.x];
+  const int64_t n = S.n[blockIdx.x];
+  for (int e = threadIdx.x; e < kB * kB; e += 256) m[e / kB][e % kB] = A[(e / kB) * n + e % kB];
+  __syncthreads();
+  invert64(m);
+  store_akk(m, S.Akk[blockIdx.x]);
+}
+
+// The panels of step k, a workgroup per 16 rows of the column or 16 columns of the
+// row, a wavefront 16 of its 64 outputs, in FP64 MFMA: col <- -A_ik^T, A_ik <- -A_ik
+// Akk, A_kj <- Akk A_kj (i, j != k); the last workgroup stores A_kk <- Akk.
+__global__ __launch_bounds__(256) void gj_panel_kernel(SweepPair S, int64_t k0) {
   double* __restrict__ A = S.A[blockIdx.y];
   const double* __restrict__ Akk = S.Akk[blockIdx.y];
-  const int64_t n_pad = S.n[blockIdx.y];
-  if (k0 >= n_pad) return;
-  __shared__ double inv[kB][kB + 1];
-  __shared__ double row[4][kB];
-  const int t = threadIdx.x;
-  for (int e = t; e < kB * kB; e += 256) inv[e / kB][e % kB] = Akk[e];
-  const int ri = t / kB, c = t % kB;
-  int64_t i = (int64_t)blockIdx.x * 4 + ri;      // index among rows outside the block
-  if (i >= k0) i += kB;
-  const bool v = i < n_pad;
-  row[ri][c] = v ? A[i * n_pad + k0 + c] : 0.0;
-  __syncthreads();
-  if (!v) return;
-  double acc = 0.0;
-#pragma unroll 8
-  for (int q = 0; q < kB; ++q) acc = fma(row[ri][q], inv[q][c], acc);
-  A[i * n_pad + k0 + c] = -acc;
+  double* __restrict__ col = S.col[blockIdx.y];
+  const int64_t n = S.n[blockIdx.y], strips = (n - kB) / 16, id = blockIdx.x;
+  if (k0 >= n || id > 2 * strips) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
+  if (id == 2 * strips) {
+    for (int r = w; r < kB; r += 4) A[(k0 + r) * n + k0 + lane] = Akk[r * kB + lane];
+    return;
+  }
+  const bool is_row = id >= strips;
+  int64_t x0 = 16 * (is_row ? id - strips : id);   // first row of the column, column of the row
+  if (x0 >= k0) x0 += kB;
+  double a[16], d[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    a[s] = is_row ? A[(k0 + 4 * s + q) * n + x0 + c] : -A[(x0 + c) * n + k0 + 4 * s + q];
+    d[s] = is_row ? Akk[(16 * w + c) * kB + 4 * s + q] : Akk[(4 * s + q) * kB + 16 * w + c];
+  }
+  f64x4_t acc = {};
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+    acc = is_row ? __builtin_amdgcn_mfma_f64_16x16x4f64(d[s], a[s], acc, 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], d[s], acc, 0, 0, 0);
+  __syncthreads();   // every wavefront has read the strip that all of them overwrite
+  if (!is_row)
+#pragma unroll
+    for (int s = 0; s < 16; ++s)
+      if (s / 4 == w) col[(4 * s + q) * n + x0 + c] = a[s];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    A[is_row ? (k0 + 16 * w + q + 4 * r) * n + x0 + c : (x0 + q + 4 * r) * n + k0 + 16 * w + c] = acc[r];
 }
 
-// Trailing update of one 64x64 tile outside block row/column k:
-// A[I, J] += A[I, k] A[k, J], a wavefront 32 x 32 of it in FP64 MFMA.
+// Trailing update of step k, a workgroup per 64x64 tile outside block row and
+// column k: A[I, J] += col[I]^T A[k, J], a wavefront 32 x 32 of it in FP64 MFMA, both
+// operands straight from L2 (rows of 16 doubles), all loads in flight at once.
+// The first workgroup has the next diagonal block and goes on to invert it while
+// the others run, so that a step waits for two launches instead of four: 1344^2,
+// two matrices, 36 us a step (71 with the panels, the update through LDS and the
+// diagonal block in launches of their own).
 __global__ __launch_bounds__(256) void gj_update_kernel(SweepPair S, int64_t k0) {
+  __shared__ double m[kB][kMLd];
   double* __restrict__ A = S.A[blockIdx.y];
-  const int64_t n_pad = S.n[blockIdx.y];
-  if (k0 >= n_pad || blockIdx.x >= (n_pad / kB - 1) * (n_pad / kB - 1)) return;
-  __shared__ double a[kB][kB + 2];   // [k][row] of A[I, k]
-  __shared__ double b[kB][kB + 2];   // A[k, J]
-  const int64_t nb = n_pad / kB;
-  int64_t bi = blockIdx.x % (nb - 1), bj = blockIdx.x / (nb - 1);
-  const int64_t kb = k0 / kB;
+  const double* __restrict__ col = S.col[blockIdx.y];
+  const int64_t n = S.n[blockIdx.y];
+  const int64_t nb = n / kB, kb = k0 / kB;
+  if (k0 >= n || blockIdx.x >= (nb - 1) * (nb - 1)) return;
+  int64_t tile = blockIdx.x;
+  const bool next = kb + 1 < nb && tile == 0;
+  if (kb + 1 < nb) {   // the next diagonal block's tile first
+    const int64_t diag = kb * (nb - 1) + kb;
+    tile = tile == 0 ? diag : tile <= diag ? tile - 1 : tile;
+  }
+  int64_t bi = tile % (nb - 1), bj = tile / (nb - 1);
   if (bi >= kb) ++bi;
   if (bj >= kb) ++bj;
-  const int64_t I0 = bi * kB, J0 = bj * kB;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  for (int e = t; e < kB * kB; e += 256) {
-    const int r = e / kB, c = e % kB;
-    a[c][r] = A[(I0 + r) * n_pad + k0 + c];
-    b[r][c] = A[(k0 + r) * n_pad + J0 + c];
-  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wi = 32 * (wave >> 1), wj = 32 * (wave & 1), c = lane & 15, q = lane >> 4;
+  const int64_t i0 = bi * kB + wi, j0 = bj * kB + wj;
+  double av[16][2], bv[16][2];
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      av[s][u] = col[(4 * s + q) * n + i0 + 16 * u + c];
+      bv[s][u] = A[(k0 + 4 * s + q) * n + j0 + 16 * u + c];
+    }
   f64x4_t acc[2][2];
-  double* tile = A + (I0 + wi + q) * n_pad + J0 + wj + c;
+  double* out = A + (i0 + q) * n + j0 + c;
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[u][v][r] = tile[(16 * u + 4 * r) * n_pad + 16 * v];
-  __syncthreads();
-#pragma unroll 4
-  for (int s = 0; s < kB / 4; ++s) {
-    double av[2], bv[2];
+      for (int r = 0; r < 4; ++r) acc[u][v][r] = out[(16 * u + 4 * r) * n + 16 * v];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      av[u] = a[4 * s + q][wi + 16 * u + c];
-      bv[u] = b[4 * s + q][wj + 16 * u + c];
-    }
+  for (int s = 0; s < 16; ++s)
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int v = 0; v < 2; ++v)
-        acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[v], acc[u][v], 0, 0, 0);
+        acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][u], bv[s][v], acc[u][v], 0, 0, 0);
+  if (!next) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[(16 * u + 4 * r) * n + 16 * v] = acc[u][v][r];
+    return;
   }
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) tile[(16 * u + 4 * r) * n_pad + 16 * v] = acc[u][v][r];
-}
-
-// Row panel: columns j outside the block, A[k, j] <- Akk A[k, j].  4 columns per block.
-__global__ __launch_bounds__(256) void gj_row_kernel(SweepPair S, int64_t k0) {
-  double* __restrict__ A = S.A[blockIdx.y];
-  const double* __restrict__ Akk = S.Akk[blockIdx.y];
-  const int64_t n_pad = S.n[blockIdx.y];
-  if (k0 >= n_pad) return;
-  __shared__ double inv[kB][kB + 1];
-  __shared__ double colv[4][kB];
-  const int t = threadIdx.x;
-  for (int e = t; e < kB * kB; e += 256) inv[e / kB][e % kB] = Akk[e];
-  const int cj = t / kB, r = t % kB;
-  int64_t j = (int64_t)blockIdx.x * 4 + cj;
-  if (j >= k0) j += kB;
-  const bool v = j < n_pad;
-  colv[cj][r] = v ? A[(k0 + r) * n_pad + j] : 0.0;
+      for (int r = 0; r < 4; ++r) m[wi + 16 * u + q + 4 * r][wj + 16 * v + c] = acc[u][v][r];
   __syncthreads();
-  if (!v) return;
-  double acc = 0.0;
-#pragma unroll 8
-  for (int q = 0; q < kB; ++q) acc = fma(inv[r][q], colv[cj][q], acc);
-  A[(k0 + r) * n_pad + j] = acc;
+  invert64(m);
+  store_akk(m, S.Akk[blockIdx.y]);   // its place in A is the next panels' to fill
 }
 
 // out[r] = (BACK: out[r] -) sum_j row[j] v[j] for both systems (v and out: the
@@ -419,17 +501,23 @@ unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per)
 
 }  // namespace
 
+// Doubles of one matrix's part of a sweep's workspace (Akk, col).
+static int64_t sweep_len(int64_t n) { return kB * kB + kB * n; }
+
+static SweepPair sweep_of(double* A, int64_t n, double* work) {
+  return {{A}, {n}, {work}, {work + kB * kB}};
+}
+
 // In-place inverses of the first `count` matrices of the pair.
 static void gauss_jordan(const SweepPair& S, int count, hipStream_t st) {
   const int64_t n = count > 1 ? std::max(S.n[0], S.n[1]) : S.n[0], nb = n / kB;
+  hipLaunchKernelGGL(gj_first_kernel, dim3(count), dim3(256), 0, st, S);
   for (int64_t k0 = 0; k0 < n; k0 += kB) {
-    hipLaunchKernelGGL(gj_diag_kernel, dim3(count), dim3(256), 0, st, S, k0);
-    if (nb == 1) return;
-    const dim3 panel(blocks_for(n - kB, 4), count);
-    hipLaunchKernelGGL(gj_col_kernel, panel, dim3(256), 0, st, S, k0);
-    hipLaunchKernelGGL(gj_update_kernel, dim3((unsigned)((nb - 1) * (nb - 1)), count), dim3(256), 0,
-                       st, S, k0);
-    hipLaunchKernelGGL(gj_row_kernel, panel, dim3(256), 0, st, S, k0);
+    hipLaunchKernelGGL(gj_panel_kernel, dim3((unsigned)(2 * (n - kB) / 16 + 1), count), dim3(256), 0, st,
+                       S, k0);
+    if (nb > 1)
+      hipLaunchKernelGGL(gj_update_kernel, dim3((unsigned)((nb - 1) * (nb - 1)), count), dim3(256), 0,
+                         st, S, k0);
   }
 }
 
@@ -464,7 +552,7 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
     DD_TRY(sbuf.alloc(sizeof(double) * (size_t)(wmax * wmax)));
     DD_TRY(bbuf.alloc(sizeof(double) * (size_t)(bmax * bmax)));
   }
-  DD_TRY(akk.alloc(sizeof(double) * kB * kB));
+  DD_TRY(akk.alloc(sizeof(double) * (size_t)sweep_len(P > 1 ? wmax : n_pad)));
   DD_TRY(dke.alloc(sizeof(double) * 24 * 24));
   DD_TRY(dmask.alloc((size_t)n));
   DD_HIP(hipMemcpyAsync(dke.p, Ke, sizeof(double) * 24 * 24, hipMemcpyHostToDevice, st));
@@ -478,7 +566,7 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
                        dke.as<double>(), dmask.as<uint8_t>(), (int64_t)0, n, (int64_t)0, X, n_pad,
                        (double*)nullptr, (int64_t)0);
     hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, X, n, n_pad);
-    gauss_jordan({{X}, {n_pad}, {akk.as<double>()}}, 1, st);
+    gauss_jordan(sweep_of(X, n_pad, akk.as<double>()), 1, st);
     DD_HIP(hipGetLastError());
     DD_HIP(hipStreamSynchronize(st));
     return DD_OK;
@@ -498,7 +586,7 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
       gemm64<false, true>(b, b, pb, -1.0, L, n_pad, B, pb, 1.0, W, w, st);
     }
     DD_HIP(hipMemcpyAsync(S, W, sizeof(double) * (size_t)(w * w), hipMemcpyDeviceToDevice, st));
-    gauss_jordan({{W}, {w}, {akk.as<double>()}}, 1, st);
+    gauss_jordan(sweep_of(W, w, akk.as<double>()), 1, st);
     DD_HIP(hipMemcpy2DAsync(X + o * n_pad + o, sizeof(double) * n_pad, W, sizeof(double) * w,
                             sizeof(double) * b, (size_t)b, hipMemcpyDeviceToDevice, st));
     // one Newton step, X += X (I - S X), the residual in B: without it the errors
@@ -577,7 +665,8 @@ static int64_t plane_h_len(const PlaneBlocks& B) {
 // Up to kDenseMaxDof DOFs K^-1 or the planes, whichever is applied sooner; beyond
 // it the planes as long as the dataset's cache holds them (cubes of up to 27
 // elements a side), else CG.  Formation, first solve of one iteration with it:
-// n = 16 13 ms (K^-1 27), 20 28 (CG 28), 24 64 (CG 55), 27 111 (CG 85).
+// n = 16 9.7 ms (K^-1 27 when it still took that size), 20 21 (CG 28), 24 45 (CG 55),
+// 27 78 (CG 85).
 PCKind pc_kind(int64_t nx, int64_t ny, int64_t nz) {
   const PlaneBlocks B = plane_blocks(nx, ny, nz);
   const int64_t n = (nz + 1) * B.face;
@@ -775,7 +864,7 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
   DevBuf work, val, akk, dke, dmask;
   DD_TRY(work.alloc(sizeof(double) * (size_t)(6 * wmax * wmax)));
   DD_TRY(val.alloc(sizeof(double) * (size_t)(2 * 27 * B.face)));
-  DD_TRY(akk.alloc(sizeof(double) * 2 * kB * kB));
+  DD_TRY(akk.alloc(sizeof(double) * (size_t)(2 * sweep_len(wmax))));
   DD_TRY(dke.alloc(sizeof(double) * 24 * 24));
   DD_TRY(dmask.alloc((size_t)n));
   DD_HIP(hipMemcpyAsync(dke.p, Ke, sizeof(double) * 24 * 24, hipMemcpyHostToDevice, st));
@@ -817,7 +906,8 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
       hipLaunchKernelGGL(identity_kernel, dim3(blocks_for(b * b, 256)), dim3(256), 0, st, R, b);
       S.A[q] = W;
       S.n[q] = w;
-      S.Akk[q] = akk.as<double>() + q * kB * kB;
+      S.Akk[q] = akk.as<double>() + q * sweep_len(wmax);
+      S.col[q] = S.Akk[q] + kB * kB;
       res.g[q] = {b, b, b, S0, w, W, w, R, b};
       add.g[q] = {b, b, b, W, w, R, b, X, ld};
     }
