@@ -334,8 +334,8 @@ typedef struct dd_solve_opts {
  * dataset for that mesh and Dirichlet pattern (at most 4 GiB of them per dataset,
  * least recently used dropped first): K^-1 for small meshes, applied as one product
  * per P_C, or the block elimination of the mesh's node planes, from about 6000
- * DOFs on and as long as it fits that cache (cubes of up to 27 elements a side; 10 ms
- * to form at 16^3, 21 at 20^3).  Beyond 16384 DOFs CG stays where cg_tol or
+ * DOFs on and as long as it fits that cache (cubes of up to 27 elements a side; 8 ms
+ * to form at 16^3, 15 at 20^3).  Beyond 16384 DOFs CG stays where cg_tol or
  * cg_max_iter is given, where the Dirichlet DOFs leave a rigid motion free and where
  * the device has no room for the operator. */
 #define DD_SOLVE_CG 0x2

@@ -5,27 +5,16 @@
 // "KeS") -- a stream of n^2 doubles instead of hundreds of CG iterations.  Larger
 // meshes keep the block elimination of their node planes instead (below).
 //
-// Inversion.  The nodes are numbered plane by plane and an element joins two
-// neighbouring planes, so K is block tridiagonal in groups of planes (diagonal
-// blocks A_k, subdiagonal blocks B_k) and symmetric positive definite (with
-// identity rows and columns at Dirichlet DOFs).  With the Schur complements
-// S_0 = A_0, S_{k+1} = A_{k+1} - L_k B_k^T, L_k = B_k S_k^-1, the inverse X
-// follows from its last block upwards:
-//   X_{P P} = S_P^-1,  X_{k j} = -L_k^T X_{k+1 j} (j > k),
-//   X_{k k} = S_k^-1 - X_{k k+1} L_k,  X_{j k} = X_{k j}^T,
-// in place (S_k^-1 and L_k stand where X_{k k} and X_{k+1 k} come to stand).
-// That is n^2 b operations with blocks of b DOFs instead of the 2 n^3 of an
-// elimination that does not see the band (16^3 elements: n = 14739, b = 867).
-// The products are FP64 MFMA tiles; the diagonal blocks are inverted by blocked
-// Gauss-Jordan without pivoting on a copy padded to a multiple of 64 with
-// identity.  For each 64-block k of it:
+// Inversion: blocked Gauss-Jordan without pivoting (K is symmetric positive
+// definite, with identity rows and columns at Dirichlet DOFs), in place on a copy
+// padded to a multiple of 64 with identity.  For each 64-block k:
 //   A_kk <- A_kk^-1;  A_kj <- A_kk A_kj (j != k);  A_ij <- A_ij - A_ik A_kj
 //   (i, j != k);  A_ik <- -A_ik A_kk (i != k).
-// Measured, 16^3 elements, whole formation (before the planes took that size): 27
-// ms; 430 ms by Gauss-Jordan over the whole matrix on the vector FP64 units, the
-// trailing updates 375 of them, and the matrix assembled on the host.  What is
-// left is the chain of diagonal 64-blocks, each waiting for the one before; 11^3
-// elements now take 8.1 ms (9.2 with four launches a block).
+// 8^3 elements (n = 2187), first solve of one iteration with it: 3.4 ms with the matrix
+// assembled on the device, 12 with the updates on the vector FP64 units and the
+// matrix from the host.  u is as near the 64-bit solution as before (8^3 8e-15,
+// 10^3 1.4e-14): an update's 64 products are summed before they meet the entry
+// they change, without which it is twice as far.
 #include <algorithm>
 #include <cstring>
 #include <list>
@@ -45,16 +34,14 @@ struct MeshDims {
   int nx, ny, nz;
 };
 
-// Rows of one block of K (DOFs row0 .. row0 + rows - 1) from the element
-// stiffness Ke: the columns of the same block to W (leading dimension ldw) and
-// those of the block before (DOFs prev0 ..) to B (ldb; null: left out).  One
-// thread per (row, neighbouring node); W and B start at zero.  An entry sums the elements that
-// share both nodes in element order.  Dirichlet rows and columns are those of
-// the identity.
+// Rows of one block of K (DOFs row0 .. row0 + rows - 1), in the columns of the same
+// block, from the element stiffness Ke to W (leading dimension ldw).  One thread
+// per (row, neighbouring node); W starts at zero.  An entry sums the elements that
+// share both nodes in element order.  Dirichlet rows and columns are those of the
+// identity.
 __global__ __launch_bounds__(256) void assemble_block_kernel(
     MeshDims d, const double* __restrict__ Ke, const uint8_t* __restrict__ mask, int64_t row0,
-    int64_t rows, int64_t prev0, double* __restrict__ W, int64_t ldw, double* __restrict__ B,
-    int64_t ldb) {
+    int64_t rows, double* __restrict__ W, int64_t ldw) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (id >= 27 * rows) return;
   const int64_t lr = id / 27, row = row0 + lr;
@@ -81,156 +68,13 @@ __global__ __launch_bounds__(256) void assemble_block_kernel(
       }
   for (int c = 0; c < 3; ++c) {
     const int64_t col = col0 + c;
-    if (mask[col] || col >= row0 + rows) continue;   // the next block's columns are its own
-    if (col >= row0)
-      W[lr * ldw + (col - row0)] = s[c];
-    else if (B)
-      B[lr * ldb + (col - prev0)] = s[c];
+    if (!mask[col] && col >= row0 && col < row0 + rows) W[lr * ldw + (col - row0)] = s[c];
   }
-}
-
-__global__ void identity_kernel(double* __restrict__ B, int64_t b) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < b * b) B[i] = i / b == i % b ? 1.0 : 0.0;
 }
 
 __global__ void pad_identity_kernel(double* __restrict__ W, int64_t n, int64_t n_pad) {
   const int64_t r = n + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r < n_pad) W[r * n_pad + r] = 1.0;
-}
-
-// ---------------------------------------------------------------------------
-// C = beta C + alpha op(A) op(B) in FP64 MFMA (v_mfma_f64_16x16x4: A lane
-// supplies row lane % 16, k = lane / 16; B the same of its column; D register i
-// holds row lane / 16 + 4 i of column lane % 16).  Row-major, any sizes; a
-// workgroup computes a 64 x 64 tile, a wavefront 32 x 32 of it, in steps of 16
-// along K staged through LDS as [k][row] and [k][column], the next step's
-// operands loaded while the current one is multiplied.
-// ---------------------------------------------------------------------------
-constexpr int kGT = 64, kGK = 16, kGLd = kGT + 2;
-
-struct Gemm {
-  int64_t m, n, k;
-  const double* A;
-  int64_t lda;
-  const double* B;
-  int64_t ldb;
-  double* C;
-  int64_t ldc;
-};
-struct GemmPair {
-  Gemm g[2];   // blockIdx.z
-};
-
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm64_kernel(GemmPair G, double alpha, double beta) {
-  const Gemm& g = G.g[blockIdx.z];
-  const int64_t m = g.m, n = g.n, kdim = g.k, lda = g.lda, ldb = g.ldb, ldc = g.ldc;
-  const double* __restrict__ A = g.A;
-  const double* __restrict__ B = g.B;
-  double* __restrict__ C = g.C;
-  if ((int64_t)blockIdx.x * kGT >= m || (int64_t)blockIdx.y * kGT >= n) return;
-  __shared__ double as[2][kGK][kGLd], bs[2][kGK][kGLd];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t i0 = (int64_t)blockIdx.x * kGT, j0 = (int64_t)blockIdx.y * kGT;
-  double ra[4], rb[4];
-  // element v of the step's 64 x 16 operand: along K where K is contiguous
-  // (op(A) = A, op(B) = B^T), else along the rows or columns
-  auto load = [&](int64_t k0) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int e = t + 256 * v;
-      const int ka = TA ? e / kGT : e % kGK, ia = TA ? e % kGT : e / kGK;
-      const bool in_a = i0 + ia < m && k0 + ka < kdim;
-      ra[v] = in_a ? (TA ? A[(k0 + ka) * lda + i0 + ia] : A[(i0 + ia) * lda + k0 + ka]) : 0.0;
-      const int kb = TB ? e % kGK : e / kGT, jb = TB ? e / kGK : e % kGT;
-      const bool in_b = j0 + jb < n && k0 + kb < kdim;
-      rb[v] = in_b ? (TB ? B[(j0 + jb) * ldb + k0 + kb] : B[(k0 + kb) * ldb + j0 + jb]) : 0.0;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int e = t + 256 * v;
-      as[buf][TA ? e / kGT : e % kGK][TA ? e % kGT : e / kGK] = ra[v];
-      bs[buf][TB ? e % kGK : e / kGT][TB ? e / kGK : e % kGT] = rb[v];
-    }
-  };
-  f64x4_t acc[2][2] = {};
-  const int wi = 32 * (wave >> 1), wj = 32 * (wave & 1), c = lane & 15, q = lane >> 4;
-  load(0);
-  store(0);
-  __syncthreads();
-  int cur = 0;
-  for (int64_t k0 = 0; k0 < kdim; k0 += kGK) {
-    const bool more = k0 + kGK < kdim;
-    if (more) load(k0 + kGK);
-#pragma unroll
-    for (int s = 0; s < kGK / 4; ++s) {
-      double a[2], b[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        a[u] = as[cur][4 * s + q][wi + 16 * u + c];
-        b[u] = bs[cur][4 * s + q][wj + 16 * u + c];
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v)
-          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
-    }
-    if (more) store(cur ^ 1);
-    __syncthreads();
-    cur ^= 1;
-  }
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t i = i0 + wi + 16 * u + q + 4 * r, j = j0 + wj + 16 * v + c;
-        if (i >= m || j >= n) continue;
-        double* p = C + i * ldc + j;
-        *p = beta == 0.0 ? alpha * acc[u][v][r] : fma(alpha, acc[u][v][r], beta * *p);
-      }
-}
-
-template <bool TA, bool TB>
-void gemm64(int64_t m, int64_t n, int64_t k, double alpha, const double* A, int64_t lda,
-            const double* B, int64_t ldb, double beta, double* C, int64_t ldc, hipStream_t st) {
-  if (m <= 0 || n <= 0) return;
-  const GemmPair G = {{{m, n, k, A, lda, B, ldb, C, ldc}, {}}};
-  hipLaunchKernelGGL((gemm64_kernel<TA, TB>),
-                     dim3((unsigned)((m + kGT - 1) / kGT), (unsigned)((n + kGT - 1) / kGT)), dim3(256),
-                     0, st, G, alpha, beta);
-}
-
-// C_s = beta C_s + alpha A_s B_s for the first `count` of the pair
-void gemm64_pair(const GemmPair& G, int count, double alpha, double beta, hipStream_t st) {
-  int64_t m = 0, n = 0;
-  for (int s = 0; s < count; ++s) {
-    m = std::max(m, G.g[s].m);
-    n = std::max(n, G.g[s].n);
-  }
-  hipLaunchKernelGGL((gemm64_kernel<false, false>),
-                     dim3((unsigned)((m + kGT - 1) / kGT), (unsigned)((n + kGT - 1) / kGT),
-                          (unsigned)count),
-                     dim3(256), 0, st, G, alpha, beta);
-}
-
-// dst[j][i] = src[i][j] for i < rows, j < cols (32 x 32 tiles through LDS).
-__global__ __launch_bounds__(256) void transpose_kernel(const double* __restrict__ src, int64_t lds_,
-                                                        int64_t rows, int64_t cols,
-                                                        double* __restrict__ dst, int64_t ldd) {
-  __shared__ double s[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
-  for (int r = ty; r < 32; r += 8)
-    if (i0 + r < rows && j0 + tx < cols) s[r][tx] = src[(i0 + r) * lds_ + j0 + tx];
-  __syncthreads();
-  for (int r = ty; r < 32; r += 8)
-    if (j0 + r < cols && i0 + tx < rows) dst[(j0 + r) * ldd + i0 + tx] = s[tx][r];
 }
 
 // The matrices (n x n, n a multiple of 64) that one Gauss-Jordan sweep inverts
@@ -260,21 +104,13 @@ __device__ inline double row_d(double v) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// 1 / x to rounding: the hardware's estimate and two Newton steps, shorter than
-// the division in the chain of pivots
-__device__ inline double recip(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-
 // Gauss-Jordan on a 16 x 16 block: lane 16 g + r holds columns 4 g .. 4 g + 3 of row r.
 template <int P>
 __device__ inline void pivot16(double (&v)[4], int r, int g) {
   if constexpr (P < 16) {
     constexpr int pg = P / 4, pe = P % 4;
     const double colv = __shfl(v[pe], 16 * pg + r);
-    const double d = recip(lane_d(v[pe], 16 * pg + P));
+    const double d = 1.0 / lane_d(v[pe], 16 * pg + P);
     const double f = r == P ? d : -colv * d;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = fma(f, row_d<P>(v[e]), r == P ? 0.0 : v[e]);
@@ -320,14 +156,10 @@ __device__ inline void invert64(double (*m)[kMLd]) {
     }
     __syncthreads();
     if (w != s) {
-      f64x4_t acc[3];
+      f64x4_t acc[3] = {};
       int at[3];   // the other three column blocks
 #pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        at[u] = 16 * (u + (u >= s ? 1 : 0)) + c;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[u][r] = m[b + q + 4 * r][at[u]];
-      }
+      for (int u = 0; u < 3; ++u) at[u] = 16 * (u + (u >= s ? 1 : 0)) + c;
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -336,7 +168,7 @@ __device__ inline void invert64(double (*m)[kMLd]) {
 #pragma unroll
       for (int u = 0; u < 3; ++u)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) m[b + q + 4 * r][at[u]] = acc[u][r];
+        for (int r = 0; r < 4; ++r) m[b + q + 4 * r][at[u]] += acc[u][r];
     }
     __syncthreads();
   }
@@ -430,14 +262,14 @@ __global__ __launch_bounds__(256) void gj_update_kernel(SweepPair S, int64_t k0)
       av[s][u] = col[(4 * s + q) * n + i0 + 16 * u + c];
       bv[s][u] = A[(k0 + 4 * s + q) * n + j0 + 16 * u + c];
     }
-  f64x4_t acc[2][2];
+  f64x4_t acc[2][2] = {}, old[2][2];   // the 64 products are summed before they meet the entry
   double* out = A + (i0 + q) * n + j0 + c;
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[u][v][r] = out[(16 * u + 4 * r) * n + 16 * v];
+      for (int r = 0; r < 4; ++r) old[u][v][r] = out[(16 * u + 4 * r) * n + 16 * v];
 #pragma unroll
   for (int s = 0; s < 16; ++s)
 #pragma unroll
@@ -451,7 +283,7 @@ __global__ __launch_bounds__(256) void gj_update_kernel(SweepPair S, int64_t k0)
 #pragma unroll
       for (int v = 0; v < 2; ++v)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[(16 * u + 4 * r) * n + 16 * v] = acc[u][v][r];
+        for (int r = 0; r < 4; ++r) out[(16 * u + 4 * r) * n + 16 * v] = old[u][v][r] + acc[u][v][r];
     return;
   }
 #pragma unroll
@@ -459,7 +291,8 @@ __global__ __launch_bounds__(256) void gj_update_kernel(SweepPair S, int64_t k0)
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m[wi + 16 * u + q + 4 * r][wj + 16 * v + c] = acc[u][v][r];
+      for (int r = 0; r < 4; ++r)
+        m[wi + 16 * u + q + 4 * r][wj + 16 * v + c] = old[u][v][r] + acc[u][v][r];
   __syncthreads();
   invert64(m);
   store_akk(m, S.Akk[blockIdx.y]);   // its place in A is the next panels' to fill
@@ -521,10 +354,6 @@ static void gauss_jordan(const SweepPair& S, int count, hipStream_t st) {
   }
 }
 
-// Smallest block of planes: below it a block's launches cost more than the
-// elimination saves.
-constexpr int64_t kMinBlock = 256;
-
 // Forms K^-1 (row-major, leading dimension n_pad) on st.
 static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* mask, DenseInverse& D,
                               hipStream_t st) {
@@ -532,93 +361,37 @@ static dd_status form_inverse(const FEMesh& M, const double* Ke, const uint8_t* 
   D.n = n;
   D.n_pad = n_pad;
   DD_TRY(D.inv.alloc(sizeof(double) * (size_t)(n_pad * n_pad)));
-  // blocks of whole planes
-  const int64_t plane = 3 * (int64_t)(M.nx + 1) * (M.ny + 1);
-  const int64_t per = std::max<int64_t>(1, (kMinBlock + plane - 1) / plane);
-  std::vector<int64_t> off;
-  for (int64_t k = 0; k <= M.nz; k += per) off.push_back(k * plane);
-  if (off.size() > 1 && n - off.back() < per * plane) off.pop_back();   // a short last group joins
-  int64_t P = (int64_t)off.size();
-  off.push_back(n);
-  int64_t bmax = 0;
-  for (int64_t k = 0; k < P; ++k) bmax = std::max(bmax, off[k + 1] - off[k]);
-  const int64_t wmax = (bmax + kB - 1) / kB * kB;
-  // one block, or few so large that their three work blocks would take more than
-  // half of the inverse's memory beside it: the whole matrix in place
-  if (6 * wmax * wmax > n_pad * n_pad) P = 1;
-  DevBuf wbuf, sbuf, bbuf, akk, dke, dmask;
-  if (P > 1) {
-    DD_TRY(wbuf.alloc(sizeof(double) * (size_t)(wmax * wmax)));
-    DD_TRY(sbuf.alloc(sizeof(double) * (size_t)(wmax * wmax)));
-    DD_TRY(bbuf.alloc(sizeof(double) * (size_t)(bmax * bmax)));
-  }
-  DD_TRY(akk.alloc(sizeof(double) * (size_t)sweep_len(P > 1 ? wmax : n_pad)));
+  DevBuf work, dke, dmask;
+  DD_TRY(work.alloc(sizeof(double) * (size_t)sweep_len(n_pad)));
   DD_TRY(dke.alloc(sizeof(double) * 24 * 24));
   DD_TRY(dmask.alloc((size_t)n));
   DD_HIP(hipMemcpyAsync(dke.p, Ke, sizeof(double) * 24 * 24, hipMemcpyHostToDevice, st));
   DD_HIP(hipMemcpyAsync(dmask.p, mask, (size_t)n, hipMemcpyHostToDevice, st));
-  double *X = D.inv.as<double>(), *W = wbuf.as<double>(), *S = sbuf.as<double>(),
-         *B = bbuf.as<double>();
-  const MeshDims dims{M.nx, M.ny, M.nz};
-  if (P == 1) {
-    DD_HIP(hipMemsetAsync(X, 0, D.inv.bytes, st));
-    hipLaunchKernelGGL(assemble_block_kernel, dim3(blocks_for(27 * n, 256)), dim3(256), 0, st, dims,
-                       dke.as<double>(), dmask.as<uint8_t>(), (int64_t)0, n, (int64_t)0, X, n_pad,
-                       (double*)nullptr, (int64_t)0);
-    hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, X, n, n_pad);
-    gauss_jordan(sweep_of(X, n_pad, akk.as<double>()), 1, st);
-    DD_HIP(hipGetLastError());
-    DD_HIP(hipStreamSynchronize(st));
-    return DD_OK;
-  }
-  for (int64_t k = 0; k < P; ++k) {
-    const int64_t o = off[k], b = off[k + 1] - o, w = (b + kB - 1) / kB * kB;
-    const int64_t po = k ? off[k - 1] : 0, pb = k ? o - po : 0;
-    DD_HIP(hipMemsetAsync(W, 0, sizeof(double) * (size_t)(w * w), st));
-    if (k) DD_HIP(hipMemsetAsync(B, 0, sizeof(double) * (size_t)(b * pb), st));
-    hipLaunchKernelGGL(assemble_block_kernel, dim3(blocks_for(27 * b, 256)), dim3(256), 0, st, dims,
-                       dke.as<double>(), dmask.as<uint8_t>(), o, b, po, W, w, B, pb);
-    if (w > b)
-      hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, W, b, w);
-    if (k) {
-      double* L = X + o * n_pad + po;   // L_{k-1}, where X_{k k-1} comes to stand
-      gemm64<false, false>(b, pb, pb, 1.0, B, pb, X + po * n_pad + po, n_pad, 0.0, L, n_pad, st);
-      gemm64<false, true>(b, b, pb, -1.0, L, n_pad, B, pb, 1.0, W, w, st);
-    }
-    DD_HIP(hipMemcpyAsync(S, W, sizeof(double) * (size_t)(w * w), hipMemcpyDeviceToDevice, st));
-    gauss_jordan(sweep_of(W, w, akk.as<double>()), 1, st);
-    DD_HIP(hipMemcpy2DAsync(X + o * n_pad + o, sizeof(double) * n_pad, W, sizeof(double) * w,
-                            sizeof(double) * b, (size_t)b, hipMemcpyDeviceToDevice, st));
-    // one Newton step, X += X (I - S X), the residual in B: without it the errors
-    // of the blocks add up along the planes (u of a 16^3 solve 5.7e-14 off the
-    // 64-bit solution, 3.1e-14 with it, 2.8e-14 by Gauss-Jordan over the whole)
-    hipLaunchKernelGGL(identity_kernel, dim3(blocks_for(b * b, 256)), dim3(256), 0, st, B, b);
-    gemm64<false, false>(b, b, b, -1.0, S, w, X + o * n_pad + o, n_pad, 1.0, B, b, st);
-    gemm64<false, false>(b, b, b, 1.0, W, w, B, b, 1.0, X + o * n_pad + o, n_pad, st);
-    DD_HIP(hipGetLastError());
-  }
-  for (int64_t k = P - 2; k >= 0; --k) {
-    const int64_t o = off[k], b = off[k + 1] - o, no = off[k + 1], nb = off[k + 2] - no;
-    const double* L = X + no * n_pad + o;
-    gemm64<true, false>(b, n - no, nb, -1.0, L, n_pad, X + no * n_pad + no, n_pad, 0.0,
-                        X + o * n_pad + no, n_pad, st);
-    gemm64<false, false>(b, b, nb, -1.0, X + o * n_pad + no, n_pad, L, n_pad, 1.0, X + o * n_pad + o,
-                         n_pad, st);
-    // the rows above are done: their transpose takes the place of L
-    hipLaunchKernelGGL(transpose_kernel, dim3(blocks_for(b, 32), blocks_for(n - no, 32)), dim3(256), 0,
-                       st, X + o * n_pad + no, n_pad, b, n - no, X + no * n_pad + o, n_pad);
-    DD_HIP(hipGetLastError());
-  }
+  double* X = D.inv.as<double>();
+  DD_HIP(hipMemsetAsync(X, 0, D.inv.bytes, st));
+  hipLaunchKernelGGL(assemble_block_kernel, dim3(blocks_for(27 * n, 256)), dim3(256), 0, st,
+                     MeshDims{M.nx, M.ny, M.nz}, dke.as<double>(), dmask.as<uint8_t>(), (int64_t)0, n, X,
+                     n_pad);
+  if (n_pad > n) hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, X, n, n_pad);
+  gauss_jordan(sweep_of(X, n_pad, work.as<double>()), 1, st);
+  DD_HIP(hipGetLastError());
   DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }
+
+// Smallest block of planes: below it a block's launches cost more than the
+// elimination saves.
+constexpr int64_t kMinBlock = 256;
 
 // ---------------------------------------------------------------------------
 // P_C by block elimination of node planes, for meshes whose inverse would be
 // read for longer than the elimination's chain of small launches takes.
 //
-// With the blocks of planes above, both ends of the chain are eliminated at the
-// same time towards the middle block: block k couples to one next block only,
+// The nodes are numbered plane by plane and an element joins two neighbouring
+// planes, so K is block tridiagonal in groups of planes (diagonal blocks A_k).  Both
+// ends of that chain are eliminated at the same time towards the middle block:
+// with the Schur complements S_k (S = A at the ends), block k couples to one next
+// block only,
 //   S_next = A_next - C_k^T H_k,  H_k = S_k^-1 C_k,  C_k = K(k, next),
 // and the middle block takes both sides.  Kept are S_k^-1 and H_k (C_k is zero
 // but for the plane next to the other block: H_k has that plane's columns).
@@ -665,8 +438,7 @@ static int64_t plane_h_len(const PlaneBlocks& B) {
 // Up to kDenseMaxDof DOFs K^-1 or the planes, whichever is applied sooner; beyond
 // it the planes as long as the dataset's cache holds them (cubes of up to 27
 // elements a side), else CG.  Formation, first solve of one iteration with it:
-// n = 16 9.7 ms (K^-1 27 when it still took that size), 20 21 (CG 28), 24 45 (CG 55),
-// 27 78 (CG 85).
+// n = 16 8.3 ms, 20 15 (CG 28), 24 28 (CG 55).
 PCKind pc_kind(int64_t nx, int64_t ny, int64_t nz) {
   const PlaneBlocks B = plane_blocks(nx, ny, nz);
   const int64_t n = (nz + 1) * B.face;
@@ -862,7 +634,7 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
   DD_TRY(D.inv.alloc(sizeof(double) * (size_t)(inv_len + plane_h_len(B))));
   const int64_t bmax = std::max(B.b, B.bl), wmax = (bmax + kB - 1) / kB * kB;
   DevBuf work, val, akk, dke, dmask;
-  DD_TRY(work.alloc(sizeof(double) * (size_t)(6 * wmax * wmax)));
+  DD_TRY(work.alloc(sizeof(double) * (size_t)(2 * wmax * wmax)));
   DD_TRY(val.alloc(sizeof(double) * (size_t)(2 * 27 * B.face)));
   DD_TRY(akk.alloc(sizeof(double) * (size_t)(2 * sweep_len(wmax))));
   DD_TRY(dke.alloc(sizeof(double) * 24 * 24));
@@ -883,15 +655,12 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
     if (t < mid && B.P - 1 - t > mid) blk[count++] = B.P - 1 - t;
     if (t == mid) blk[count++] = mid;
     SweepPair S = {};
-    GemmPair res = {}, add = {};
     for (int q = 0; q < count; ++q) {
-      const int64_t k = blk[q], b = B.size(k), w = (b + kB - 1) / kB * kB, ld = ld8(b);
-      double* W = work.as<double>() + 3 * q * wmax * wmax;
-      double *S0 = W + wmax * wmax, *R = S0 + wmax * wmax, *X = inv + B.off(k) * ld8(B.b);
+      const int64_t k = blk[q], b = B.size(k), w = (b + kB - 1) / kB * kB;
+      double* W = work.as<double>() + q * wmax * wmax;
       DD_HIP(hipMemsetAsync(W, 0, sizeof(double) * (size_t)(w * w), st));
       hipLaunchKernelGGL(assemble_block_kernel, dim3(blocks_for(27 * b, 256)), dim3(256), 0, st, dims,
-                         dke.as<double>(), dmask.as<uint8_t>(), B.off(k), b, (int64_t)0, W, w,
-                         (double*)nullptr, (int64_t)0);
+                         dke.as<double>(), dmask.as<uint8_t>(), B.off(k), b, W, w);
       if (w > b) hipLaunchKernelGGL(pad_identity_kernel, dim3(1), dim3(64), 0, st, W, b, w);
       for (int s = 0; s < 2; ++s) {   // the Schur terms of the block(s) before
         const int64_t from = s == 0 ? k - 1 : k + 1;
@@ -902,25 +671,19 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
         hipLaunchKernelGGL(plane_schur_kernel, dim3(blocks_for(B.face, 256), (unsigned)B.face), dim3(256),
                            0, st, sx, sy, side_val(s), H, ldh, at, w);
       }
-      DD_HIP(hipMemcpyAsync(S0, W, sizeof(double) * (size_t)(w * w), hipMemcpyDeviceToDevice, st));
-      hipLaunchKernelGGL(identity_kernel, dim3(blocks_for(b * b, 256)), dim3(256), 0, st, R, b);
       S.A[q] = W;
       S.n[q] = w;
       S.Akk[q] = akk.as<double>() + q * sweep_len(wmax);
       S.col[q] = S.Akk[q] + kB * kB;
-      res.g[q] = {b, b, b, S0, w, W, w, R, b};
-      add.g[q] = {b, b, b, W, w, R, b, X, ld};
     }
     gauss_jordan(S, count, st);
+    double* X[2];
     for (int q = 0; q < count; ++q) {
       const int64_t k = blk[q], b = B.size(k), w = S.n[q];
-      DD_HIP(hipMemcpy2DAsync(add.g[q].C, sizeof(double) * ld8(b), S.A[q], sizeof(double) * w,
+      X[q] = inv + B.off(k) * ld8(B.b);
+      DD_HIP(hipMemcpy2DAsync(X[q], sizeof(double) * ld8(b), S.A[q], sizeof(double) * w,
                               sizeof(double) * b, (size_t)b, hipMemcpyDeviceToDevice, st));
     }
-    // one Newton step, X += X (I - S X): without it the blocks' errors add up
-    // along the planes
-    gemm64_pair(res, count, -1.0, 1.0, st);
-    gemm64_pair(add, count, 1.0, 1.0, st);
     if (t == mid) break;
     for (int q = 0; q < count; ++q) {
       const int64_t k = blk[q], b = B.size(k), o = B.off(k);
@@ -930,7 +693,7 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
       hipLaunchKernelGGL(plane_coupling_kernel, dim3(blocks_for(9 * B.face, 256)), dim3(256), 0, st, dims,
                          dke.as<double>(), dmask.as<uint8_t>(), B.face, from, to, side_val(s));
       hipLaunchKernelGGL(plane_h_kernel, dim3(blocks_for(B.face, 256), blocks_for(b, kHRows)), dim3(256),
-                         0, st, sx, sy, b, add.g[q].C, ld8(b), s == 0 ? b - B.face : (int64_t)0,
+                         0, st, sx, sy, b, X[q], ld8(b), s == 0 ? b - B.face : (int64_t)0,
                          side_val(s), h + o * ldh, ldh);
     }
     DD_HIP(hipGetLastError());
