@@ -83,10 +83,11 @@ __device__ inline float wave_max(float v) {
 // Box of ROWS consecutive rows of the sorted FP64 pack, a row per lane: FP64
 // coordinates on the principal axes, rounded outward to FP32 before the
 // minimum and maximum (rounding is monotone, so the result is the outward
-// rounding of the FP64 extremes).
+// rounding of the FP64 extremes).  Writes the rows' |x|^2 on the way.
 template <int ROWS>
 __global__ __launch_bounds__(ROWS) void tile_box_kernel(const double* __restrict__ w64, int64_t N,
                                                         const double* __restrict__ V,
+                                                        double* __restrict__ n64,
                                                         float* __restrict__ box) {
   __shared__ float part[ROWS / 64][24];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -95,6 +96,10 @@ __global__ __launch_bounds__(ROWS) void tile_box_kernel(const double* __restrict
   double v[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) v[k] = x[k];
+  double n2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) n2 = fma(v[k], v[k], n2);
+  if (i < N) n64[i] = n2;
 #pragma unroll
   for (int a = 0; a < 12; ++a) {
     double y = 0.0;
@@ -175,10 +180,12 @@ dd_status build_tile_boxes(const Dataset& D, int rows, const TileBoxes* from, Ti
                        B.tile.as<float>());
   } else if (rows == 256) {
     hipLaunchKernelGGL(tile_box_kernel<256>, dim3((unsigned)n), dim3(256), 0, st,
-                       D.w64.as<double>(), D.N, D.vrot.as<double>(), B.tile.as<float>());
+                       D.w64.as<double>(), D.N, D.vrot.as<double>(), D.n64.as<double>(),
+                       B.tile.as<float>());
   } else if (rows == 128) {
     hipLaunchKernelGGL(tile_box_kernel<128>, dim3((unsigned)n), dim3(128), 0, st,
-                       D.w64.as<double>(), D.N, D.vrot.as<double>(), B.tile.as<float>());
+                       D.w64.as<double>(), D.N, D.vrot.as<double>(), D.n64.as<double>(),
+                       B.tile.as<float>());
   } else {
     return set_error(DD_ERR_ARG, "tile boxes: rows");
   }

@@ -42,33 +42,36 @@ __device__ inline bool whiten_row(const double* __restrict__ strain,
 
 // Pass 1 over a chunk of rows first .. first+n-1: non-finite flag, max |w|
 // (non-negative doubles order like their bit patterns) and the strided sample
-// rows {s * stride : s < ns} used for the principal axes.
+// rows {s * stride : s < ns} used for the principal axes.  At most kStatBlocks
+// blocks: a block per 256 rows queued its maximum with 131072 others on one
+// address (2^25 points, 1.56 ms; 0.58 now).
+constexpr unsigned kStatBlocks = 4096;
 __global__ __launch_bounds__(256) void stats_kernel(const double* __restrict__ strain,
                                                     const double* __restrict__ stress, int64_t n,
                                                     int64_t first, Mat6x2 M, int64_t stride,
                                                     int64_t ns, double* __restrict__ samp,
                                                     int* __restrict__ bad,
                                                     unsigned long long* __restrict__ maxn) {
-  __shared__ double red[256];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ double red[4];
   double v = 0.0;
-  if (i < n) {
+  bool all = true;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     double w[12];
-    if (!whiten_row(strain, stress, i, M, w)) atomicOr(bad, 1);
+    all = whiten_row(strain, stress, i, M, w) && all;
     double s = 0.0;
     for (int k = 0; k < 12; ++k) s = fma(w[k], w[k], s);
-    v = isfinite(s) ? sqrt(s) : 0.0;
+    v = fmax(v, isfinite(s) ? sqrt(s) : 0.0);
     const int64_t g = first + i;
     if (g % stride == 0 && g / stride < ns)
       for (int k = 0; k < 12; ++k) samp[12 * (g / stride) + k] = w[k];
   }
-  red[threadIdx.x] = v;
+  if (!all) atomicOr(bad, 1);
+  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + off]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicMax(maxn, (unsigned long long)__double_as_longlong(red[0]));
+  if (threadIdx.x == 0)
+    atomicMax(maxn, (unsigned long long)__double_as_longlong(
+                        fmax(fmax(red[0], red[1]), fmax(red[2], red[3]))));
 }
 
 // Mean and second moments of the sample rows x[ns][12], each sum over the rows in
@@ -194,34 +197,46 @@ __global__ void invert_perm_kernel(const uint32_t* __restrict__ perm, int64_t n,
   if (i < n) iperm[perm[i]] = (uint32_t)i;
 }
 
-// Pass 3: each point's whitened row goes to its sorted position: the FP64 pack
-// with |x|^2, and the FP32 pack (round to nearest) with the FP32-rounded
-// squared norm of the stored values.
-__global__ void scatter_kernel(const double* __restrict__ strain, const double* __restrict__ stress,
-                               int64_t n, int64_t first, Mat6x2 M,
-                               const uint32_t* __restrict__ iperm, double* __restrict__ w64,
-                               double* __restrict__ n64, float* __restrict__ w32,
-                               float* __restrict__ n32) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// Pass 3: each point's whitened row goes to its sorted position in the FP64 pack,
+// and in the FP32 pack (round to nearest) with the FP32-rounded squared norm of the
+// stored values.  The FP64 norms come with the tile boxes, in order: 8 bytes each
+// scattered, they were a third of this pass (2^25 points, 4.0 ms; 2.8 now).
+__global__ __launch_bounds__(256) void scatter_kernel(const double* __restrict__ strain,
+                                                      const double* __restrict__ stress, int64_t n,
+                                                      int64_t first, Mat6x2 M,
+                                                      const uint32_t* __restrict__ iperm,
+                                                      double* __restrict__ w64,
+                                                      float* __restrict__ w32, float* __restrict__ n32) {
+  __shared__ double out[12 * 256];
+  __shared__ int64_t pos[256];
+  const int t = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + t;
+  const bool v = i < n;
   double w[12];
-  whiten_row(strain, stress, i, M, w);
-  const int64_t p = iperm[first + i];
+  whiten_row(strain, stress, v ? i : n - 1, M, w);
+  const int64_t p = v ? (int64_t)iperm[first + i] : 0;
   if (w64) {
-    double s = 0.0;
-    for (int k = 0; k < 12; ++k) {
-      w64[12 * p + k] = w[k];
-      s = fma(w[k], w[k], s);
+    // a row's 96 bytes leave together, 16 from each of six lanes
+    for (int k = 0; k < 12; ++k) out[12 * t + k] = w[k];
+    pos[t] = p;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 6; ++u) {
+      const int e = t + 256 * u, row = e / 6, part = e % 6;
+      if (i0 + row < n)
+        *reinterpret_cast<double2*>(w64 + 12 * pos[row] + 2 * part) =
+            make_double2(out[12 * row + 2 * part], out[12 * row + 2 * part + 1]);
     }
-    n64[p] = s;
   }
-  if (w32) {
+  if (w32 && v) {
     double s = 0.0;
+    float f[12];
     for (int k = 0; k < 12; ++k) {
-      const float v = (float)w[k];
-      w32[12 * p + k] = v;
-      s = fma((double)v, (double)v, s);
+      f[k] = (float)w[k];
+      s = fma((double)f[k], (double)f[k], s);
     }
+    float4* o = reinterpret_cast<float4*>(w32 + 12 * p);
+    for (int k = 0; k < 3; ++k) o[k] = make_float4(f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3]);
     n32[p] = (float)s;
   }
 }
@@ -374,30 +389,6 @@ __device__ inline double wave_max_d(double v) {
   return v;
 }
 
-// One wavefront per leaf of kAnnLeaf consecutive sorted points.
-__global__ __launch_bounds__(256) void ann_leaf_box_kernel(const double* __restrict__ w64, int64_t N,
-                                                           Rot12 R, int64_t n_leaf,
-                                                           float* __restrict__ box) {
-  const int lane = threadIdx.x & 63;
-  const int64_t leaf = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (leaf >= n_leaf) return;
-  const int64_t i = leaf * kAnnLeaf + lane;
-  const bool v = i < N;
-  double x[12];
-  for (int k = 0; k < 12; ++k) x[k] = v ? w64[12 * i + k] : 0.0;
-  float* b = box + 24 * leaf;
-  for (int a = 0; a < 12; ++a) {
-    double y = 0.0;
-    for (int k = 0; k < 12; ++k) y = fma(R.V[12 * k + a], x[k], y);
-    const double lo = wave_min_d(v ? y : INFINITY);
-    const double hi = wave_max_d(v ? y : -INFINITY);
-    if (lane == 0) {
-      b[a] = __double2float_rd(lo);
-      b[12 + a] = __double2float_ru(hi);
-    }
-  }
-}
-
 // One wavefront per node: the box of its (up to) kAnnFan child boxes.
 __global__ __launch_bounds__(256) void ann_node_box_kernel(const float* __restrict__ child,
                                                            int64_t n_child, int64_t n_node,
@@ -419,48 +410,112 @@ __global__ __launch_bounds__(256) void ann_node_box_kernel(const float* __restri
   }
 }
 
-// Compact leaf of the walk (one wavefront per leaf): centre, radius and the
-// scaled FP16 offsets of its points, in principal-axis coordinates.
-__global__ __launch_bounds__(256) void ann_leaf_pack_kernel(const double* __restrict__ w64,
-                                                            int64_t N, Rot12 R, int64_t n_leaf,
-                                                            float* __restrict__ meta,
-                                                            _Float16* __restrict__ h16) {
+// Extremes over the wavefront (every lane active): rows of 16 by DPP, then the rows.
+template <int C>
+__device__ inline float dpp_f(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), C, 0xF, 0xF, false));
+}
+__device__ inline float lane_f(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+template <int C>
+__device__ inline double dpp_d(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, C, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), C, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ inline double lane_d(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ inline float wave_min_f(float v) {
+  v = fminf(v, dpp_f<0xB1>(v));    // quad xor 1
+  v = fminf(v, dpp_f<0x4E>(v));    // quad xor 2
+  v = fminf(v, dpp_f<0x141>(v));   // half-row mirror
+  v = fminf(v, dpp_f<0x140>(v));   // row mirror
+  return fminf(fminf(lane_f(v, 0), lane_f(v, 16)), fminf(lane_f(v, 32), lane_f(v, 48)));
+}
+
+// One wavefront per leaf of kAnnLeaf consecutive sorted points: the leaf's box in
+// principal-axis coordinates, rounded outward, and the walk's compact leaf (centre,
+// radius and the scaled FP16 offsets of its points in the same coordinates).  A
+// pass over the points for both; the extremes are rounded before they are
+// reduced (rounding is monotone, so the bounds are the same), in FP32 on DPP
+// rather than in FP64 through LDS.  2^25 points: 1.7 ms; 2.86 as two kernels.
+__global__ __launch_bounds__(256) void ann_leaf_kernel(const double* __restrict__ w64, int64_t N,
+                                                       Rot12 R, int64_t n_leaf, float* __restrict__ box,
+                                                       float* __restrict__ meta,
+                                                       _Float16* __restrict__ h16) {
   const int lane = threadIdx.x & 63;
   const int64_t leaf = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (leaf >= n_leaf) return;
   const int64_t i = leaf * kAnnLeaf + lane;
   const bool v = i < N;
   int cnt = __popcll(__ballot(v));
-  // the point in principal-axis coordinates y = V^T x (the boxes' frame)
+  // the point in principal-axis coordinates y = V^T x
   double x[12];
   {
     double w[12];
-    for (int k = 0; k < 12; ++k) w[k] = v ? w64[12 * i + k] : 0.0;
+    const double2* src = reinterpret_cast<const double2*>(w64 + 12 * (v ? i : leaf * kAnnLeaf));
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const double2 d = src[k];
+      w[2 * k] = v ? d.x : 0.0;
+      w[2 * k + 1] = v ? d.y : 0.0;
+    }
     for (int a = 0; a < 12; ++a) {
       double y = 0.0;
       for (int k = 0; k < 12; ++k) y = fma(R.V[12 * k + a], w[k], y);
       x[a] = y;
     }
   }
+  for (int a = 0; a < 12; ++a) {
+    const float lo = wave_min_f(v ? __double2float_rd(x[a]) : INFINITY);
+    const float hi = -wave_min_f(v ? -__double2float_ru(x[a]) : INFINITY);
+    if (lane == 0) {
+      box[24 * leaf + a] = lo;
+      box[24 * leaf + 12 + a] = hi;
+    }
+  }
   float c[12];
   for (int k = 0; k < 12; ++k) {
+    // the sum in lane 0, halves, then quarters and so on added pairwise
     double sum = x[k];
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-    sum = __shfl(sum, 0);   // one value for every lane (the butterfly order differs per lane)
-    c[k] = (float)(sum / (double)cnt);
+    sum += __shfl_xor(sum, 32);
+    sum += __shfl_xor(sum, 16);
+    sum += dpp_d<0x128>(sum);   // from lane + 8 of the row
+    sum += dpp_d<0x104>(sum);   // + 4
+    sum += dpp_d<0x102>(sum);   // + 2
+    sum += dpp_d<0x101>(sum);   // + 1
+    const double total = lane_d(sum, 0);
+    c[k] = (float)(cnt == kAnnLeaf ? total * (1.0 / kAnnLeaf) : total / (double)cnt);   // the same value
   }
   double d2 = 0.0;
   for (int k = 0; k < 12; ++k) {
     const double t = x[k] - (double)c[k];
     d2 = fma(t, t, d2);
   }
-  double r = v ? sqrt(d2) : 0.0;
-  r = wave_max_d(r);
-  float rf = __double2float_ru(r * (1.0 + 1e-12));
+  const double r = v ? sqrt(d2) : 0.0;
+  float rf = -wave_min_f(-__double2float_ru(r * (1.0 + 1e-12)));
   rf = fmaxf(rf, 9.5367431640625e-07f);   // 2^-20: bounded scaled offsets for tiny leaves
   const double inv = 1.0 / (double)rf;
-  for (int k = 0; k < 12; ++k)
-    h16[12 * i + k] = v ? (_Float16)((x[k] - (double)c[k]) * inv) : (_Float16)0.0f;
+  uint2* out = reinterpret_cast<uint2*>(h16 + 12 * i);   // 24 bytes a point
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    uint32_t u[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int k = 4 * q + 2 * e;
+      const _Float16 a = v ? (_Float16)((x[k] - (double)c[k]) * inv) : (_Float16)0.0f;
+      const _Float16 b = v ? (_Float16)((x[k + 1] - (double)c[k + 1]) * inv) : (_Float16)0.0f;
+      u[e] = (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+    }
+    out[q] = make_uint2(u[0], u[1]);
+  }
   if (lane == 0) {
     float* m = meta + 16 * leaf;
     for (int k = 0; k < 12; ++k) m[k] = c[k];
@@ -687,7 +742,8 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     const int64_t n = std::min(CH, N - f);
     const double *e, *s;
     DD_TRY(src.rows(f, n, &e, &s, st));
-    hipLaunchKernelGGL(stats_kernel, dim3(grid_for(n)), dim3(256), 0, st, e, s, n, f, M, stride, ns,
+    hipLaunchKernelGGL(stats_kernel, dim3(std::min(grid_for(n), kStatBlocks)), dim3(256), 0, st, e, s, n,
+                       f, M, stride, ns,
                        dsamp.as<double>(), flag.as<int>(), mx.as<unsigned long long>());
     DD_HIP(hipGetLastError());
   }
@@ -789,8 +845,7 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     const double *e, *s;
     DD_TRY(src.rows(f, n, &e, &s, st));
     hipLaunchKernelGGL(scatter_kernel, dim3(grid_for(n)), dim3(256), 0, st, e, s, n, f, M,
-                       D.iperm.as<uint32_t>(), D.w64.as<double>(), D.n64.as<double>(),
-                       D.w32.as<float>(), D.n32.as<float>());
+                       D.iperm.as<uint32_t>(), D.w64.as<double>(), D.w32.as<float>(), D.n32.as<float>());
     DD_HIP(hipGetLastError());
   }
   if (D.n_pad64 > N) {
@@ -829,8 +884,10 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     int l = 0;
     DD_TRY(D.ann_box[0].alloc(sizeof(float) * 24 * (size_t)n));
     D.ann_n[0] = n;
-    hipLaunchKernelGGL(ann_leaf_box_kernel, dim3(grid_for(n, 4)), dim3(256), 0, st,
-                       D.w64.as<double>(), N, R, n, D.ann_box[0].as<float>());
+    DD_TRY(D.ann_meta.alloc(sizeof(float) * 16 * (size_t)n));
+    DD_TRY(D.ann_h16.alloc(sizeof(uint16_t) * 12 * (size_t)(n * kAnnLeaf)));
+    hipLaunchKernelGGL(ann_leaf_kernel, dim3(grid_for(n, 4)), dim3(256), 0, st, D.w64.as<double>(), N, R,
+                       n, D.ann_box[0].as<float>(), D.ann_meta.as<float>(), D.ann_h16.as<_Float16>());
     DD_HIP(hipGetLastError());
     while (n > kAnnFan) {
       const int64_t m = (n + kAnnFan - 1) / kAnnFan;
@@ -845,12 +902,6 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
     }
     D.ann_levels = l + 1;
     const int64_t nl = D.ann_n[0];
-    DD_TRY(D.ann_meta.alloc(sizeof(float) * 16 * (size_t)nl));
-    DD_TRY(D.ann_h16.alloc(sizeof(uint16_t) * 12 * (size_t)(nl * kAnnLeaf)));
-    hipLaunchKernelGGL(ann_leaf_pack_kernel, dim3(grid_for(nl, 4)), dim3(256), 0, st,
-                       D.w64.as<double>(), N, R, nl, D.ann_meta.as<float>(),
-                       D.ann_h16.as<_Float16>());
-    DD_HIP(hipGetLastError());
     if (D.ann_levels >= 2) {
       DD_TRY(D.ann_q0.alloc(24 * (size_t)nl));
       hipLaunchKernelGGL(ann_qbox_kernel, dim3(grid_for(nl)), dim3(256), 0, st,
