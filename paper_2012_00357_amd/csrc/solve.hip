@@ -199,8 +199,9 @@ __global__ void gather_z_kernel(const int64_t* __restrict__ idx, int64_t n_mp, i
   }
 }
 
-// RHS by gathering, per DOF, the contributions of its (<= 8) elements and their
-// Gauss points: one wavefront per DOF, lane 8 a + g taking Gauss point g of the
+// RHS by gathering, per node, the contributions of its (<= 8) elements and their
+// Gauss points: one wavefront per node (its three DOFs read
+// the states once), lane 8 a + g taking Gauss point g of the
 // element whose local node a is the DOF's node, then a fixed-order wave sum.
 // E = A_e{w B^T C eps*} - K_fd u_D on free DOFs and u_D on Dirichlet DOFs (the
 // identity rows of K carry the prescribed displacement), S = f - A_e{w B^T sig*}
@@ -211,40 +212,41 @@ __global__ __launch_bounds__(256) void assemble_rhs_kernel(
     const uint8_t* __restrict__ mask, const double* __restrict__ f, const double* __restrict__ uD,
     const double* __restrict__ lift, double* __restrict__ E, double* __restrict__ S) {
   const int lane = threadIdx.x & 63;
-  const int64_t dof = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t n_dof = 3 * (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
-  if (dof >= n_dof) return;   // wave-uniform
-  if (mask[dof]) {
-    if (lane == 0) {
-      E[dof] = uD ? uD[dof] : 0.0;
-      S[dof] = 0.0;
-    }
-    return;
-  }
-  const int comp = (int)(dof % 3);
-  const int64_t nd = dof / 3;
+  const int64_t nd = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (nd >= (int64_t)(nx + 1) * (ny + 1) * (nz + 1)) return;   // wave-uniform
   const int i = (int)(nd % (nx + 1));
   const int j = (int)((nd / (nx + 1)) % (ny + 1));
   const int k = (int)(nd / ((int64_t)(nx + 1) * (ny + 1)));
   const int a = lane >> 3, g = lane & 7;
   const int ex = i - (a & 1), ey = j - ((a >> 1) & 1), ez = k - (a >> 2);
-  double se = 0.0, ss = 0.0;
+  double se[3] = {0.0, 0.0, 0.0}, ss[3] = {0.0, 0.0, 0.0};
   if (ex >= 0 && ey >= 0 && ez >= 0 && ex < nx && ey < ny && ez < nz) {
     const int64_t el = ex + (int64_t)nx * (ey + (int64_t)ny * ez);
     const double* z = zc + 12 * (8 * el + g);
     for (int r = 0; r < 6; ++r) {
-      const double bv = Bo.B[g][24 * r + 3 * a + comp];
-      se = fma(bv, z[r], se);
-      ss = fma(bv, z[6 + r], ss);
+      const double ze = z[r], zs = z[6 + r];
+      for (int comp = 0; comp < 3; ++comp) {
+        const double bv = Bo.B[g][24 * r + 3 * a + comp];
+        se[comp] = fma(bv, ze, se[comp]);
+        ss[comp] = fma(bv, zs, ss[comp]);
+      }
     }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    se += __shfl_xor(se, off);
-    ss += __shfl_xor(ss, off);
-  }
-  if (lane == 0) {
-    E[dof] = lift ? w * se - lift[dof] : w * se;
-    S[dof] = f[dof] - w * ss;
+  for (int off = 32; off > 0; off >>= 1)
+    for (int comp = 0; comp < 3; ++comp) {
+      se[comp] += __shfl_xor(se[comp], off);
+      ss[comp] += __shfl_xor(ss[comp], off);
+    }
+  if (lane != 0) return;
+  for (int comp = 0; comp < 3; ++comp) {
+    const int64_t dof = 3 * nd + comp;
+    if (mask[dof]) {
+      E[dof] = uD ? uD[dof] : 0.0;
+      S[dof] = 0.0;
+    } else {
+      E[dof] = lift ? w * se[comp] - lift[dof] : w * se[comp];
+      S[dof] = f[dof] - w * ss[comp];
+    }
   }
 }
 
@@ -528,9 +530,13 @@ __global__ __launch_bounds__(256) void recover_kernel(int nx, int ny, int nz, BO
 // partial sums of block b.  Block b sums a fixed range of material points (the
 // squared differences read as one flat, coalesced array), its waves reduce in a
 // fixed shuffle order and the block stores its partials; the block that takes
-// the last ticket adds the partials in block order and resets the ticket, so
-// the result does not depend on which block finishes last.
-constexpr int kScalBlocks = 32;
+// the last ticket adds the partials, one a thread, in the same fixed order and
+// resets the ticket, so the result does not depend on which block finishes last.
+// A block per 256 material points between 32 and 256 (64000 points: 40 us by 32, 14 now).
+constexpr int kScalBlocks = 256;
+static unsigned scal_blocks(int64_t nm) {
+  return (unsigned)std::max<int64_t>(32, std::min<int64_t>(kScalBlocks, (nm + 255) / 256));
+}
 __global__ __launch_bounds__(256) void iter_scalars_kernel(
     int64_t n_mp, double w, const double* __restrict__ yw, const double* __restrict__ zw,
     const double* __restrict__ dist, const int64_t* __restrict__ idx_new,
@@ -570,10 +576,16 @@ __global__ __launch_bounds__(256) void iter_scalars_kernel(
   __syncthreads();
   if (!last) return;
   __threadfence();
+  const volatile double* part = out + 4;   // at most a partial sum per thread
+  double v[3];
+  for (int k = 0; k < 3; ++k) v[k] = t < (int)gridDim.x ? part[3 * t + k] : 0.0;
+  for (int off = 32; off > 0; off >>= 1)
+    for (int k = 0; k < 3; ++k) v[k] += __shfl_down(v[k], off);
+  if ((t & 63) == 0)
+    for (int k = 0; k < 3; ++k) ws[k][t >> 6] = v[k];
+  __syncthreads();
   if (t < 3) {
-    const volatile double* part = out + 4;
-    double sum = 0.0;
-    for (unsigned b = 0; b < gridDim.x; ++b) sum += part[3 * b + t];
+    const double sum = ((ws[t][0] + ws[t][1]) + ws[t][2]) + ws[t][3];
     out[t] = t == 0 ? 0.5 * w * sum : (t == 1 ? w * sum : sum);
   }
   if (t == 0) *reinterpret_cast<volatile unsigned*>(out + 3) = 0u;
@@ -989,7 +1001,7 @@ dd_status DDSolver::pc_begin() {
   hipLaunchKernelGGL(gather_z_kernel, dim3(g256(nm)), dim3(256), 0, st, d_idx.as<int64_t>(), nm,
                      ds->N, ds->iperm.as<uint32_t>(), ds->w64.as<double>(), Lm, d_zw.as<double>(),
                      d_zc.as<double>(), reinterpret_cast<int*>(d_cgstat.as<char>() + 32));
-  hipLaunchKernelGGL(assemble_rhs_kernel, dim3(g256(64 * nd)), dim3(256), 0, st, M.nx, M.ny, M.nz, M.w,
+  hipLaunchKernelGGL(assemble_rhs_kernel, dim3(g256(64 * M.n_nodes)), dim3(256), 0, st, M.nx, M.ny, M.nz, M.w,
                      Bo, d_zc.as<double>(), d_mask.as<uint8_t>(), d_f.as<double>(),
                      d_uD.as<double>(), d_lift.as<double>(), d_b.as<double>(),
                      d_b.as<double>() + nd);
@@ -1077,7 +1089,7 @@ dd_status DDSolver::pc_end() {
 
 dd_status DDSolver::scalars_begin() {
   const int64_t nm = M.n_mp;
-  hipLaunchKernelGGL(iter_scalars_kernel, dim3(kScalBlocks), dim3(256), 0, st, nm, M.w, d_yw.as<double>(),
+  hipLaunchKernelGGL(iter_scalars_kernel, dim3(scal_blocks(nm)), dim3(256), 0, st, nm, M.w, d_yw.as<double>(),
                      d_zw.as<double>(), d_dist.as<double>(), d_idx_new.as<int64_t>(),
                      d_idx.as<int64_t>(), d_scal.as<double>());
   DD_HIP(hipGetLastError());
@@ -1187,7 +1199,7 @@ dd_status DDSolver::constraint_projection() {
   hipLaunchKernelGGL(gather_z_kernel, dim3(g256(nm)), dim3(256), 0, st, d_idx.as<int64_t>(), nm,
                      ds->N, ds->iperm.as<uint32_t>(), ds->w64.as<double>(), Lm, d_zw.as<double>(),
                      d_zc.as<double>(), reinterpret_cast<int*>(d_cgstat.as<char>() + 32));
-  hipLaunchKernelGGL(assemble_rhs_kernel, dim3(g256(64 * nd)), dim3(256), 0, st, M.nx, M.ny, M.nz, M.w,
+  hipLaunchKernelGGL(assemble_rhs_kernel, dim3(g256(64 * M.n_nodes)), dim3(256), 0, st, M.nx, M.ny, M.nz, M.w,
                      Bo, d_zc.as<double>(), d_mask.as<uint8_t>(), d_f.as<double>(),
                      d_uD.as<double>(), d_lift.as<double>(), d_b.as<double>(),
                      d_b.as<double>() + nd);
@@ -1263,7 +1275,7 @@ dd_status DDSolver::run(int max_iter, dd_solve_result* res) {
     DD_HIP(hipEventRecord(ev.e[0], st));
     DD_TRY(project_step(it));
     DD_HIP(hipEventRecord(ev.e[1], st));
-    hipLaunchKernelGGL(iter_scalars_kernel, dim3(kScalBlocks), dim3(256), 0, st, nm, M.w, d_yw.as<double>(),
+    hipLaunchKernelGGL(iter_scalars_kernel, dim3(scal_blocks(nm)), dim3(256), 0, st, nm, M.w, d_yw.as<double>(),
                        d_zw.as<double>(), d_dist.as<double>(), d_idx_new.as<int64_t>(),
                        d_idx.as<int64_t>(), d_scal.as<double>());
     DD_HIP(hipGetLastError());
