@@ -55,3 +55,28 @@ def test_scan_equals_walk(L, C0, N, packs, sizes):
             L.dd_project(ds, to_dev(y), mode="fp16")
         assert ex.value.status == 8
     ds.close()
+
+
+@pytest.mark.parametrize("m", [1, 9, 16383, 16384, 16391])
+def test_large_walk_equals_fp64_scan(L, C0, m):
+    """Beyond the scans' sizes the walk takes queries in spatial order (from 16384,
+    grids that are and are not a multiple of the XCDs) and, without a warm start, the
+    seed bound: the FP64 scan's answers, bit for bit."""
+    import torch
+    N = (1 << 24) + 4097
+    g = torch.Generator(device="cuda").manual_seed(77)
+    C = torch.from_numpy(np.ascontiguousarray(C0)).cuda()
+    e = 1e-3 * torch.randn(N, 6, dtype=torch.float64, device="cuda", generator=g)
+    s = e @ C
+    ds = L.dd_dataset_create(e, s, C0, packs=FP64 | ANN)
+    pick = torch.randint(0, N, (m,), device="cuda", generator=g)
+    y = torch.cat([e[pick], s[pick]], 1)
+    y = (y * (1.0 + 0.2 * torch.randn(m, 12, dtype=torch.float64, device="cuda", generator=g))).contiguous()
+    if m > 1:
+        y[m // 2, 5] = float("nan")
+    ref, dref = L.dd_project(ds, y, mode="fp64")
+    for warm in (None, pick):
+        got, dist = L.dd_project(ds, y, warm_start_idx=warm, mode="ann")
+        assert torch.equal(got, ref)
+        assert np.array_equal(dist.cpu().numpy(), dref.cpu().numpy(), equal_nan=True)
+    ds.close()
