@@ -548,16 +548,18 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
   DD_TRY(sc.get(Q.u64, (size_t)m));
   DD_TRY(sc.get(Q.u32, (size_t)m));
   DD_TRY(sc.get(Q.invalid, (size_t)m));
-  // Walks on large data sets.  Many queries go in spatial order, so that the walks
-  // that run together share the tree's lines in L2 (2^26 points, warm: 32768
-  // queries 2.38 against 2.59 ms, 16384 1.55 against 1.65; up to 4096 it gains
-  // nothing).  An exact walk without a warm start begins with the scans' seed bound
-  // (2^26 points: 512 queries 0.63 against 1.18 ms, 32768 2.62 against 5.21).  Smaller
-  // data sets have the scan (scan_for_walk).
-  const bool large_walk = walk_mode(mode) && !fixed && D.N > kTreeScanMax;
-  const bool sorted_walk = large_walk && m >= 16384;
-  const bool seeded_walk = large_walk && !warm_start_idx_dev && budget == 0 && fd == 1.0 && !fd_q &&
-                           !budget_q && !dist2_out_dev;
+  // Exact walks on large data sets.  The box tree's walks of many queries go in
+  // spatial order, so that those which run together share the tree's lines in L2
+  // (2^26 points, warm: 32768 queries 2.38 against 2.59 ms, 16384 1.55 against 1.65;
+  // up to 4096 it gains nothing, and the approximate walks, which visit a few
+  // leaves, lose: k-means tree, 2^24 points, f_d = 0.4, 64000 queries 0.69 against 0.65
+  // ms).  A walk without a warm start begins with the scans' seed bound (2^26 points:
+  // 512 queries 0.63 against 1.18 ms, 32768 2.62 against 5.21).  Smaller data sets have
+  // the scan (scan_for_walk).
+  const bool large_walk = walk_mode(mode) && !fixed && D.N > kTreeScanMax && budget == 0 && fd == 1.0 &&
+                          !fd_q && !budget_q;
+  const bool sorted_walk = large_walk && mode == DD_ANN && m >= 16384;
+  const bool seeded_walk = large_walk && !warm_start_idx_dev && !dist2_out_dev;
   int* order = nullptr;
   if (cull || walk_mode(mode)) DD_TRY(sc.get(Q.yq, (size_t)m * 12));
   if (cull || sorted_walk) {
