@@ -70,7 +70,6 @@ struct AnnArgs {
   const float* yq;         // [m][12] queries on the principal axes (prep_kernel)
   float xmax;
   int budget;
-  bool by_xcd;             // L is in spatial order
   QueryList L;
   const double* qw;
   const double* qn2;
@@ -329,11 +328,7 @@ __global__ __launch_bounds__(256, 6) void ann_walk_kernel(AnnArgs A) {
   __shared__ float s_clb[kWaves][kCand];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // workgroups are dealt to the eight XCDs in turn: of queries in spatial order
-  // each XCD takes a contiguous run, whose walks share its L2
-  const unsigned run = gridDim.x / 8u;   // the grid is a multiple of 8 then
-  const int64_t blk = A.by_xcd ? (int64_t)(blockIdx.x % 8u) * run + blockIdx.x / 8u : blockIdx.x;
-  const int64_t p = blk * kWaves + wv;
+  const int64_t p = (int64_t)blockIdx.x * kWaves + wv;
   if (p >= list_len(A.L)) return;
   const int64_t q = list_query(A.L, p);
   // one wave per query: the per-query accuracy is wave-uniform (scalar registers)
@@ -673,7 +668,7 @@ __global__ __launch_bounds__(256, 6) void ann_walk_kernel(AnnArgs A) {
 dd_status launch_ann_walk(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t len_max,
                           const int64_t* warm, int budget, Outputs out, int* fb_list, int* fb_count,
                           unsigned long long* counters, double* dist2, hipStream_t st, bool kmt,
-                          double fd, const float* fd_q, const int* budget_q, bool spatial) {
+                          double fd, const float* fd_q, const int* budget_q) {
   if (dist2 && (budget != 0 || (kmt && fd != 1.0) || fd_q || budget_q))
     return set_error(DD_ERR_ARG, "second distances need the exact walk");
   if (!(fd >= 0.0 && fd <= 1.0)) return set_error(DD_ERR_ARG, "f_d must be in [0, 1]");
@@ -721,9 +716,7 @@ dd_status launch_ann_walk(const Dataset& D, const QueryPrep& Q, QueryList L, int
   A.fb_list = fb_list;
   A.fb_count = fb_count;
   A.counters = counters;
-  unsigned blocks = (unsigned)((len_max + kWaves - 1) / kWaves);
-  A.by_xcd = spatial;
-  if (spatial) blocks = (blocks + 7) / 8 * 8;
+  const unsigned blocks = (unsigned)((len_max + kWaves - 1) / kWaves);
   A.dist2 = dist2;
   if (kmt) {
     if (dist2)

@@ -284,7 +284,6 @@ __global__ __launch_bounds__(256) void order_scatter_kernel(QueryPrep Q, int64_t
   const unsigned p = cell_add(Q.hist, v ? (int)Q.key[i] : -1);
   if (!v) return;
   order[p] = (int)i;
-  if (!R.qw) return;   // the order alone
   const double2* q = reinterpret_cast<const double2*>(Q.qw + 12 * i);
   double2* r = reinterpret_cast<double2*>(R.qw + 12 * (int64_t)p);
   double2 x[6];

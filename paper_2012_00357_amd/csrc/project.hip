@@ -548,35 +548,27 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
   DD_TRY(sc.get(Q.u64, (size_t)m));
   DD_TRY(sc.get(Q.u32, (size_t)m));
   DD_TRY(sc.get(Q.invalid, (size_t)m));
-  // Exact walks on large data sets.  The box tree's walks of many queries go in
-  // spatial order, so that those which run together share the tree's lines in L2
-  // (2^26 points, warm: 32768 queries 2.38 against 2.59 ms, 16384 1.55 against 1.65;
-  // up to 4096 it gains nothing, and the approximate walks, which visit a few
-  // leaves, lose: k-means tree, 2^24 points, f_d = 0.4, 64000 queries 0.69 against 0.65
-  // ms).  A walk without a warm start begins with the scans' seed bound (2^26 points:
-  // 512 queries 0.63 against 1.18 ms, 32768 2.62 against 5.21).  Smaller data sets have
+  // An exact walk on a large data set without a warm start begins with the scans'
+  // seed bound (2^26 points: 512 queries 0.63 against 1.18 ms, 32768 2.62 against 5.21;
+  // k-means tree, 2^24 points, 32768 queries 2.17 against 2.60).  Smaller data sets have
   // the scan (scan_for_walk).
-  const bool large_walk = walk_mode(mode) && !fixed && D.N > kTreeScanMax && budget == 0 && fd == 1.0 &&
-                          !fd_q && !budget_q;
-  const bool sorted_walk = large_walk && mode == DD_ANN && m >= 16384;
-  const bool seeded_walk = large_walk && !warm_start_idx_dev && !dist2_out_dev;
-  int* order = nullptr;
+  const bool seeded_walk = walk_mode(mode) && !fixed && D.N > kTreeScanMax && !warm_start_idx_dev &&
+                           budget == 0 && fd == 1.0 && !fd_q && !budget_q && !dist2_out_dev;
   if (cull || walk_mode(mode)) DD_TRY(sc.get(Q.yq, (size_t)m * 12));
-  if (cull || sorted_walk) {
+  if (cull) {
     DD_TRY(sc.get(Q.key, (size_t)m));
     Q.key_bits = group_key_bits(m);
   }
-  if (sorted_walk) DD_TRY(sc.get(order, (size_t)m));
   // [0] fb1, [1] fb2, [2..3] candidates (u64), [4..5] slow tiles (u64),
   // [6..7] (query, point) pairs of a culled scan (u64),
   // [32..) ANN walk statistics (kCounterSlots slots of kCounterStride u64, each
   // slot on its own 128-byte line)
   constexpr int kNumCounters = 32 + 2 * kCounterStride * kCounterSlots;
-  const int n_zero = kNumCounters + (Q.key ? 1 << Q.key_bits : 0);   // counters, then the key histogram
+  const int n_zero = kNumCounters + (cull ? 1 << Q.key_bits : 0);   // counters, then the key histogram
   int* counters = nullptr;
   DD_TRY(sc.get(counters, n_zero));
   DD_HIP(hipMemsetAsync(counters, 0, n_zero * sizeof(int), st));
-  if (Q.key) Q.hist = reinterpret_cast<unsigned*>(counters + kNumCounters);
+  if (cull) Q.hist = reinterpret_cast<unsigned*>(counters + kNumCounters);
   const bool scan16 = (mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16);
   DD_TRY(prepare_queries(D, states_dev, whitened, m, warm_start_idx_dev,
                          scan16 ? (double)D.sc16.s : 1.0, Q, st));
@@ -617,12 +609,8 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
     if (dist2_out_dev && (budget != 0 || fd < 1.0))
       return set_error(DD_ERR_ARG, "second distances need the exact walk");
     if (seeded_walk) DD_TRY(launch_seed(D, Q, m, 1.0, st));
-    if (sorted_walk) {
-      DD_TRY(launch_order(Q, m, D.sc16, QueryPrep{}, order, st));
-      all.list = order;
-    }
     DD_TRY(launch_ann_walk(D, Q, all, m, warm_start_idx_dev, budget, out, fb, counters, ann,
-                           dist2_out_dev, st, mode == DD_KMEANS, fd, fd_q, budget_q, sorted_walk));
+                           dist2_out_dev, st, mode == DD_KMEANS, fd, fd_q, budget_q));
     DD_TRY(timing.mark(2, st));
     uint32_t* hw = sc.host_word(1);
     DD_HIP(hipMemcpyAsync(hw, counters, sizeof(int), hipMemcpyDeviceToHost, st));

@@ -191,7 +191,7 @@ dd_status launch_ann_walk(const Dataset& D, const QueryPrep& Q, QueryList L, int
                           const int64_t* warm, int budget, Outputs out, int* fb_list, int* fb_count,
                           unsigned long long* counters, double* dist2, hipStream_t st,
                           bool kmt = false, double fd = 1.0, const float* fd_q = nullptr,
-                          const int* budget_q = nullptr, bool spatial = false);   // L in spatial order
+                          const int* budget_q = nullptr);
 
 // u32[q] = min(u32[q], min over the S split bounds U[p][S]).
 dd_status launch_reduce_bounds(QueryList L, int64_t list_len_max, const float* U, int S, float* u32,

@@ -200,9 +200,9 @@ __global__ void gather_z_kernel(const int64_t* __restrict__ idx, int64_t n_mp, i
 }
 
 // RHS by gathering, per node, the contributions of its (<= 8) elements and their
-// Gauss points: one wavefront per node (its three DOFs read
-// the states once), lane 8 a + g taking Gauss point g of the
-// element whose local node a is the DOF's node, then a fixed-order wave sum.
+// Gauss points: one wavefront per node (its three DOFs read the states once), lane
+// 8 a + g taking Gauss point g of the element whose local node a it is, then a
+// fixed-order wave sum per DOF.
 // E = A_e{w B^T C eps*} - K_fd u_D on free DOFs and u_D on Dirichlet DOFs (the
 // identity rows of K carry the prescribed displacement), S = f - A_e{w B^T sig*}
 // on free DOFs and 0 on Dirichlet DOFs (eta vanishes there).  uD and lift may be

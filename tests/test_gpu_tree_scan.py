@@ -59,9 +59,8 @@ def test_scan_equals_walk(L, C0, N, packs, sizes):
 
 @pytest.mark.parametrize("m", [1, 9, 16383, 16384, 16391])
 def test_large_walk_equals_fp64_scan(L, C0, m):
-    """Beyond the scans' sizes the walk takes queries in spatial order (from 16384,
-    grids that are and are not a multiple of the XCDs) and, without a warm start, the
-    seed bound: the FP64 scan's answers, bit for bit."""
+    """Beyond the scans' sizes the walk begins, without a warm start, with the seed
+    bound: the FP64 scan's answers, bit for bit."""
     import torch
     N = (1 << 24) + 4097
     g = torch.Generator(device="cuda").manual_seed(77)
