@@ -34,6 +34,23 @@ dd_status set_error(dd_status st, const std::string& msg);
     if (s_ != DD_OK) return s_;       \
   } while (0)
 
+// Device memory of the host objects below.  A released block of 1 MiB and more is
+// kept for the next allocation of about its size: memory given to the driver is
+// cleared by it before it is given out again, at about 40 GB/s, and once a
+// process (or those before it) has been through the device's memory, every
+// creation waits for that (2^25 points with BF16 pack and box tree, 6.5 GB: 157 to 173
+// ms where the driver has no clean memory left, 20 where it has, 16 from here).
+// At most kPoolBytes are kept per device, for at most
+// kPoolSeconds after their release (checked at each allocation, release and
+// projection); an allocation that fails frees them all and is tried again, and so
+// does dd_dataset_destroy(NULL).  A block is kept only once the device has
+// finished with it, so that any stream may have it next.
+constexpr size_t kPoolBytes = (size_t)8 << 30;
+constexpr int kPoolSeconds = 5;
+hipError_t device_alloc(void** p, size_t n);
+void device_free(void* p);
+void device_pool_trim(bool all);   // frees what has been kept for too long, or all
+
 // Device buffer owned by a host object; released in the destructor.
 struct DevBuf {
   void* p = nullptr;

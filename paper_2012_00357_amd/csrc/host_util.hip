@@ -1,6 +1,11 @@
 // Host utilities: error reporting, device buffers, small dense linear algebra.
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstring>
+#include <list>
+#include <mutex>
+#include <unordered_map>
 
 #include "dd_internal.h"
 
@@ -13,11 +18,138 @@ dd_status set_error(dd_status st, const std::string& msg) {
   return st;
 }
 
+namespace {
+
+using PoolClock = std::chrono::steady_clock;
+struct PoolBlock {
+  void* p;
+  size_t size;
+  int device;
+  PoolClock::time_point since;
+};
+struct Pool {
+  std::mutex mu;
+  std::unordered_map<void*, std::pair<size_t, int>> out;   // blocks in use: size, device
+  std::list<PoolBlock> idle;                               // oldest first
+  std::atomic<int> n_idle{0};
+};
+constexpr size_t kPoolLeast = (size_t)1 << 20;
+// Never destroyed: objects released at exit may still come here.
+Pool& pool() {
+  static Pool* p = new Pool;
+  return *p;
+}
+
+// Takes the idle blocks that `which` accepts out of the pool and frees them outside its lock.
+template <class F>
+void pool_drop(F which) {
+  std::vector<void*> gone;
+  {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    for (auto it = P.idle.begin(); it != P.idle.end();) {
+      if (which(*it)) {
+        gone.push_back(it->p);
+        it = P.idle.erase(it);
+      } else {
+        ++it;
+      }
+    }
+    P.n_idle = (int)P.idle.size();
+  }
+  for (void* p : gone) (void)hipFree(p);
+}
+
+}  // namespace
+
+void device_pool_trim(bool all) {
+  if (pool().n_idle.load() == 0) return;
+  const auto old = PoolClock::now() - std::chrono::seconds(kPoolSeconds);
+  pool_drop([&](const PoolBlock& b) { return all || b.since < old; });
+}
+
+hipError_t device_alloc(void** p, size_t n) {
+  if (n < kPoolLeast) return hipMalloc(p, n);
+  device_pool_trim(false);
+  Pool& P = pool();
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    auto best = P.idle.end();
+    for (auto it = P.idle.begin(); it != P.idle.end(); ++it)
+      if (it->device == dev && it->size >= n && it->size <= n + n / 8 &&
+          (best == P.idle.end() || it->size < best->size))
+        best = it;
+    if (best != P.idle.end()) {
+      *p = best->p;
+      P.out[best->p] = {best->size, dev};
+      P.idle.erase(best);
+      P.n_idle = (int)P.idle.size();
+      return hipSuccess;
+    }
+  }
+  e = hipMalloc(p, n);
+  if (e != hipSuccess && P.n_idle.load() > 0) {
+    (void)hipGetLastError();
+    device_pool_trim(true);
+    e = hipMalloc(p, n);
+  }
+  if (e == hipSuccess) {
+    std::lock_guard<std::mutex> lk(P.mu);
+    P.out[*p] = {n, dev};
+  }
+  return e;
+}
+
+void device_free(void* p) {
+  Pool& P = pool();
+  PoolBlock b{p, 0, 0, {}};
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    auto it = P.out.find(p);
+    if (it != P.out.end()) {
+      b.size = it->second.first;
+      b.device = it->second.second;
+      P.out.erase(it);
+    }
+  }
+  int dev = 0;
+  // as hipFree does: whatever still runs on the device may use the block
+  if (b.size == 0 || b.size > kPoolBytes || hipGetDevice(&dev) != hipSuccess || dev != b.device ||
+      hipDeviceSynchronize() != hipSuccess) {
+    (void)hipFree(p);
+    return;
+  }
+  std::vector<void*> gone;
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    size_t total = b.size;
+    for (const PoolBlock& k : P.idle)
+      if (k.device == dev) total += k.size;
+    for (auto it = P.idle.begin(); total > kPoolBytes && it != P.idle.end();) {   // the oldest go
+      if (it->device != dev) {
+        ++it;
+        continue;
+      }
+      total -= it->size;
+      gone.push_back(it->p);
+      it = P.idle.erase(it);
+    }
+    b.since = PoolClock::now();
+    P.idle.push_back(b);
+    P.n_idle = (int)P.idle.size();
+  }
+  for (void* g : gone) (void)hipFree(g);
+  device_pool_trim(false);
+}
+
 dd_status DevBuf::alloc(size_t n) {
   release();
   owned = true;
   if (n == 0) return DD_OK;
-  hipError_t e = hipMalloc(&p, n);
+  hipError_t e = device_alloc(&p, n);
   if (e != hipSuccess) {
     p = nullptr;
     (void)hipGetLastError();   // a caller that goes on without the buffer starts clean
@@ -29,7 +161,7 @@ dd_status DevBuf::alloc(size_t n) {
 }
 
 void DevBuf::release() {
-  if (p && owned) (void)hipFree(p);
+  if (p && owned) device_free(p);
   p = nullptr;
   bytes = 0;
   owned = true;
@@ -47,7 +179,7 @@ dd_status TempPool::take(size_t n, void** p, size_t* cap) {
   }
   if (n <= kLeast) {
     void* slab = nullptr;
-    if (hipMalloc(&slab, kKeep) == hipSuccess) {
+    if (device_alloc(&slab, kKeep) == hipSuccess) {
       slabs.push_back(slab);
       for (size_t o = kLeast; o < kKeep; o += kLeast)
         idle.emplace_back(kLeast, static_cast<char*>(slab) + o);
@@ -60,12 +192,12 @@ dd_status TempPool::take(size_t n, void** p, size_t* cap) {
   size_t size = n;
   if (n <= kKeep)
     for (size = 2 * kLeast; size < n;) size *= 2;
-  hipError_t e = hipMalloc(p, size);
+  hipError_t e = device_alloc(p, size);
   if (e != hipSuccess) {   // without the idle blocks, and no more than was asked for
     (void)hipGetLastError();
     trim();
     size = n == kLeast ? n + 1 : n;   // kLeast marks a slab's blocks
-    e = hipMalloc(p, size);
+    e = device_alloc(p, size);
   }
   if (e != hipSuccess) {
     *p = nullptr;
@@ -79,7 +211,7 @@ dd_status TempPool::take(size_t n, void** p, size_t* cap) {
 
 void TempPool::put(void* p, size_t cap) {
   if (cap > kKeep)
-    (void)hipFree(p);
+    device_free(p);
   else
     idle.emplace_back(cap, p);
 }
@@ -90,20 +222,20 @@ void TempPool::trim() {   // the blocks that are no part of a slab
     if (b.first == kLeast)
       idle[kept++] = b;
     else
-      (void)hipFree(b.second);
+      device_free(b.second);
   }
   idle.resize(kept);
 }
 
 TempPool::~TempPool() {
   trim();
-  for (void* s : slabs) (void)hipFree(s);
+  for (void* s : slabs) device_free(s);
 }
 
 ScratchArena::~ScratchArena() {
   // the last user's work on the block must end before the block is freed
   if (done) (void)hipEventSynchronize(done);
-  if (block) (void)hipFree(block);
+  if (block) device_free(block);
   if (pinned) (void)hipHostFree(pinned);
   if (done) (void)hipEventDestroy(done);
 }

@@ -68,6 +68,12 @@ struct Scratch {
       return set_error(DD_ERR_TOO_LARGE, "projection scratch beyond the caller's reserve");
     void* p = nullptr;
     hipError_t e = hipMallocAsync(&p, bytes, st);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      device_pool_trim(true);
+      e = hipMallocAsync(&p, bytes, st);
+      if (e != hipSuccess) (void)hipGetLastError();
+    }
     if (e != hipSuccess)
       return set_error(e == hipErrorOutOfMemory ? DD_ERR_OOM : DD_ERR_DEVICE,
                        std::string("hipMallocAsync: ") + hipGetErrorString(e));
@@ -93,10 +99,10 @@ struct Scratch {
         D.arena_bytes -= old;
         return;
       }
-      if (a->block) (void)hipFree(a->block);
+      if (a->block) device_free(a->block);
       a->block = nullptr;
       a->bytes = 0;
-      if (hipMalloc(&p, grown) == hipSuccess) {
+      if (device_alloc(&p, grown) == hipSuccess) {
         a->block = p;
         a->bytes = grown;
       } else {
@@ -748,6 +754,7 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
                           ScratchArena* fixed) {
   if (m < 0 || m > 0x7FFFFFFFll) return set_error(DD_ERR_ARG, "m must be in [0, 2^31-1]");
   if (m == 0) return DD_OK;
+  device_pool_trim(false);
   if (!states_dev || !idx_out_dev) return set_error(DD_ERR_ARG, "NULL states or idx_out");
   const int mode = opts ? opts->mode : DD_EXACT_FP64;
   const int splits = opts ? opts->splits : 0;

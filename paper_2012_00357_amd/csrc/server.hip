@@ -670,6 +670,7 @@ extern "C" dd_status dd_server_create(const dd_dataset* ds, size_t hbm_budget_by
   DD_HIP(hipSetDevice(D.device));
   if (hbm_budget_bytes == 0) {
     size_t fr = 0, tot = 0;
+    device_pool_trim(true);   // what is kept for the next allocation is free memory
     DD_HIP(hipMemGetInfo(&fr, &tot));
     hbm_budget_bytes = fr / 2;
   }
@@ -690,7 +691,7 @@ extern "C" dd_status dd_server_create(const dd_dataset* ds, size_t hbm_budget_by
   DD_HIP(hipEventCreateWithFlags(&s.scratch->done, hipEventDisableTiming));
   DD_HIP(hipHostMalloc((void**)&s.scratch->pinned, sizeof(uint32_t) * kArenaPinnedWords,
                        hipHostMallocDefault));
-  DD_HIP(hipMalloc(&s.scratch->block, scratch_bytes));
+  DD_HIP(device_alloc(&s.scratch->block, scratch_bytes));
   s.scratch->bytes = scratch_bytes;
   s.peak_used = s.reserve;
   DD_HIP(hipStreamCreateWithFlags(&s.pst, hipStreamNonBlocking));
