@@ -487,12 +487,15 @@ __global__ __launch_bounds__(256) void cull_kernel(
   const int64_t p = (int64_t)group * 64 + lane;
   const bool v = p < m && !invalid[p < m ? p : 0];
   float y[12], U = -INFINITY, slack = 0.0f, r2 = -INFINITY;
+  // squares past the FP32 range say nothing: such a query keeps every tile, with
+  // coordinates that leave no inf - inf in the tests (a NaN there drops the tile)
+  const float reach = v ? (float)sqrt(qn2[p]) + xmax : 0.0f;
+  const bool all = !(reach < 0x1p60f);
 #pragma unroll
-  for (int a = 0; a < 12; ++a) y[a] = v ? yq[12 * p + a] : 0.0f;
+  for (int a = 0; a < 12; ++a) y[a] = v && !all ? yq[12 * p + a] : 0.0f;
   if (v) {
-    const float reach = (float)sqrt(qn2[p]) + xmax;
-    slack = kEps22 * reach + 1e-30f;
-    if (reach < 0x1p60f) {
+    if (!all) {
+      slack = kEps22 * reach + 1e-30f;
       U = u32[p] * u_scale;
       float e2 = 0.0f;
 #pragma unroll
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(256) void cull_kernel(
       const float t = (U + slack) * (1.0f + 0x1p-18f);
       r2 = t * t * (1.0f + 0x1p-16f) - e2 * (1.0f - 0x1p-16f) + 1e-37f;
     } else {
-      U = r2 = INFINITY;   // squares past the FP32 range say nothing: every tile is kept
+      U = r2 = INFINITY;
     }
   }
   if (!__any(r2 != -INFINITY)) return;   // no query here
