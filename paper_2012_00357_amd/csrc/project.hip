@@ -213,19 +213,24 @@ int64_t mask_run(int64_t n_tiles, int64_t m, int sub, size_t room) {
   return std::min<int64_t>(std::min<int64_t>(m, kMaskQueries),
                            std::max<int64_t>(words, 1) * 32 * sub);
 }
+// Words of one of a run's two mask arrays, whose rows plan_kernel reads 16 bytes at a
+// time: both begin at a multiple of four words, whatever the widths of the runs.
+size_t mask_len(int64_t n_tiles, int64_t run, int sub) {
+  return ((size_t)n_tiles * mask_words(run, sub) + 3) & ~(size_t)3;
+}
 size_t mask_bytes(int64_t n_tiles, int64_t run, int sub) {
-  return aligned((size_t)n_tiles * 8 * mask_words(run, sub) + 16) +
+  return aligned(8 * mask_len(n_tiles, run, sub) + 16) +
          aligned((size_t)n_tiles * kMaskParts * sizeof(uint2));
 }
 dd_status alloc_masks(Scratch& sc, int64_t n_tiles, int64_t run, int sub, TileMasks& M) {
-  const size_t masks = 2 * (size_t)n_tiles * mask_words(run, sub);
+  const size_t len = mask_len(n_tiles, run, sub);
   uint32_t* z = nullptr;
-  DD_TRY(sc.get(z, masks + 4));
+  DD_TRY(sc.get(z, 2 * len + 4));
   M.zero = z;
-  M.zero_bytes = ((masks + 4) * 4 + 15) & ~(size_t)15;   // pieces are 256-byte multiples
+  M.zero_bytes = (2 * len + 4) * 4;
   M.n_entry = z;
   M.mask = z + 4;
-  M.left = M.mask + masks / 2;
+  M.left = M.mask + len;
   DD_TRY(sc.get(M.entry, (size_t)n_tiles * kMaskParts));
   M.sub = sub;
   return DD_OK;
