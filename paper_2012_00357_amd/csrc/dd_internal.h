@@ -50,6 +50,22 @@ constexpr int kPoolSeconds = 5;
 hipError_t device_alloc(void** p, size_t n);
 void device_free(void* p);
 void device_pool_trim(bool all);   // frees what has been kept for too long, or all
+// Returns to the driver what the library holds on the device without using it: the
+// idle temporaries of the creation that runs on this thread, and every kept block.
+void device_give_back();
+// An allocation (a function that returns its hipError_t), tried again after that if
+// there was no memory for it; leaves no error behind.
+template <class F>
+hipError_t alloc_or_give_back(F alloc) {
+  hipError_t e = alloc();
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    device_give_back();
+    e = alloc();
+  }
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
 
 // Device buffer owned by a host object; released in the destructor.
 struct DevBuf {
@@ -75,19 +91,21 @@ struct DevBuf {
 // a TempBuf that ends hands its block back for the next one without waiting (the
 // stream orders the uses), where a hipFree waits for the device and costs with its
 // hipMalloc about 30 us.  Blocks of kLeast are cut from slabs of kKeep; blocks above
-// kKeep are freed at once; the rest goes with the pool, at the end of the creation.
+// kKeep are freed at once; the rest goes with the pool, at the end of the creation,
+// or when an allocation on its thread finds no memory (device_give_back).
 class TempPool {
  public:
-  TempPool() = default;
+  TempPool();
   TempPool(const TempPool&) = delete;
   TempPool& operator=(const TempPool&) = delete;
   ~TempPool();
   dd_status take(size_t n, void** p, size_t* cap);
   void put(void* p, size_t cap);
+  void trim();   // frees the idle blocks, and the slabs if none of their blocks is in use
 
  private:
   static constexpr size_t kLeast = (size_t)1 << 20, kKeep = (size_t)16 << 20;
-  void trim();
+  TempPool* before;   // the thread's pool until this one ends
   std::vector<std::pair<size_t, void*>> idle;   // (size, block)
   std::vector<void*> slabs;
 };

@@ -68,8 +68,15 @@ void device_pool_trim(bool all) {
   pool_drop([&](const PoolBlock& b) { return all || b.since < old; });
 }
 
+static thread_local TempPool* t_temps = nullptr;
+
+void device_give_back() {
+  if (t_temps) t_temps->trim();
+  device_pool_trim(true);
+}
+
 hipError_t device_alloc(void** p, size_t n) {
-  if (n < kPoolLeast) return hipMalloc(p, n);
+  if (n < kPoolLeast) return alloc_or_give_back([&] { return hipMalloc(p, n); });
   device_pool_trim(false);
   Pool& P = pool();
   int dev = 0;
@@ -90,12 +97,7 @@ hipError_t device_alloc(void** p, size_t n) {
       return hipSuccess;
     }
   }
-  e = hipMalloc(p, n);
-  if (e != hipSuccess && P.n_idle.load() > 0) {
-    (void)hipGetLastError();
-    device_pool_trim(true);
-    e = hipMalloc(p, n);
-  }
+  e = alloc_or_give_back([&] { return hipMalloc(p, n); });
   if (e == hipSuccess) {
     std::lock_guard<std::mutex> lk(P.mu);
     P.out[*p] = {n, dev};
@@ -152,7 +154,6 @@ dd_status DevBuf::alloc(size_t n) {
   hipError_t e = device_alloc(&p, n);
   if (e != hipSuccess) {
     p = nullptr;
-    (void)hipGetLastError();   // a caller that goes on without the buffer starts clean
     return set_error(e == hipErrorOutOfMemory ? DD_ERR_OOM : DD_ERR_DEVICE,
                      std::string("hipMalloc(") + std::to_string(n) + "): " + hipGetErrorString(e));
   }
@@ -187,21 +188,17 @@ dd_status TempPool::take(size_t n, void** p, size_t* cap) {
       *cap = kLeast;
       return DD_OK;
     }
-    (void)hipGetLastError();
   }
   size_t size = n;
   if (n <= kKeep)
     for (size = 2 * kLeast; size < n;) size *= 2;
   hipError_t e = device_alloc(p, size);
-  if (e != hipSuccess) {   // without the idle blocks, and no more than was asked for
-    (void)hipGetLastError();
-    trim();
-    size = n == kLeast ? n + 1 : n;   // kLeast marks a slab's blocks
+  if (e != hipSuccess && size > n) {   // no more than was asked for
+    size = n == kLeast ? n + 1 : n;    // kLeast marks a slab's blocks
     e = device_alloc(p, size);
   }
   if (e != hipSuccess) {
     *p = nullptr;
-    (void)hipGetLastError();
     return set_error(e == hipErrorOutOfMemory ? DD_ERR_OOM : DD_ERR_DEVICE,
                      std::string("hipMalloc(") + std::to_string(n) + "): " + hipGetErrorString(e));
   }
@@ -216,7 +213,7 @@ void TempPool::put(void* p, size_t cap) {
     idle.emplace_back(cap, p);
 }
 
-void TempPool::trim() {   // the blocks that are no part of a slab
+void TempPool::trim() {
   size_t kept = 0;
   for (auto& b : idle) {
     if (b.first == kLeast)
@@ -225,11 +222,19 @@ void TempPool::trim() {   // the blocks that are no part of a slab
       device_free(b.second);
   }
   idle.resize(kept);
+  if (kept * kLeast == slabs.size() * kKeep) {
+    for (void* s : slabs) device_free(s);
+    slabs.clear();
+    idle.clear();
+  }
 }
+
+TempPool::TempPool() : before(t_temps) { t_temps = this; }
 
 TempPool::~TempPool() {
   trim();
   for (void* s : slabs) device_free(s);
+  t_temps = before;
 }
 
 ScratchArena::~ScratchArena() {

@@ -67,13 +67,7 @@ struct Scratch {
     if (fixed)
       return set_error(DD_ERR_TOO_LARGE, "projection scratch beyond the caller's reserve");
     void* p = nullptr;
-    hipError_t e = hipMallocAsync(&p, bytes, st);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      device_pool_trim(true);
-      e = hipMallocAsync(&p, bytes, st);
-      if (e != hipSuccess) (void)hipGetLastError();
-    }
+    const hipError_t e = alloc_or_give_back([&] { return hipMallocAsync(&p, bytes, st); });
     if (e != hipSuccess)
       return set_error(e == hipErrorOutOfMemory ? DD_ERR_OOM : DD_ERR_DEVICE,
                        std::string("hipMallocAsync: ") + hipGetErrorString(e));
@@ -105,8 +99,6 @@ struct Scratch {
       if (device_alloc(&p, grown) == hipSuccess) {
         a->block = p;
         a->bytes = grown;
-      } else {
-        (void)hipGetLastError();
       }
       std::lock_guard<std::mutex> lk(D.arena_mu);
       D.arena_bytes += (int64_t)a->bytes - old;

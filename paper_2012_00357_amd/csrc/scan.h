@@ -154,10 +154,9 @@ dd_status launch_merge_rerank(const Dataset& D, const QueryPrep& Q, QueryList L,
 // Plain FP64 direct-form scan with lexicographic (dist, original index) minimum,
 // split over the data, followed by its merge.  The per-split partial results
 // (list_len x splits, splits = choose_splits(list blocks, tiles, S)) go to
-// part_d / part_o when both are given, else to stream-ordered allocations.
+// part_d / part_o.
 dd_status run_direct(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t list_len, int S,
-                     Outputs out, hipStream_t st, double* part_d = nullptr,
-                     uint32_t* part_o = nullptr);
+                     Outputs out, hipStream_t st, double* part_d, uint32_t* part_o);
 
 // Splits of a scan over the data (FP64 and direct scans): `requested` if > 0;
 // with fewer than 64 query blocks one round of workgroups (512), otherwise

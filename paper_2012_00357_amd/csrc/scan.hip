@@ -466,24 +466,13 @@ dd_status run_direct(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t 
   int64_t n_tiles = (D.N + kDirectRows - 1) / kDirectRows;
   int64_t qblocks = (list_len_max + 255) / 256;
   S = choose_splits(qblocks, n_tiles, S);
-  const bool own = !(part_d && part_o);
-  double* pd = part_d;
-  uint32_t* po = part_o;
-  if (own) {
-    DD_HIP(hipMallocAsync((void**)&pd, sizeof(double) * (size_t)(list_len_max * S), st));
-    DD_HIP(hipMallocAsync((void**)&po, sizeof(uint32_t) * (size_t)(list_len_max * S), st));
-  }
   hipLaunchKernelGGL(direct_kernel, dim3((unsigned)(qblocks * S)), dim3(256), 0, st,
                      D.w64.as<double>(), D.w64.p ? nullptr : D.w32.as<float>(),
-                     D.perm.as<uint32_t>(), n_tiles, D.N, Q.qw, L, S, pd, po);
+                     D.perm.as<uint32_t>(), n_tiles, D.N, Q.qw, L, S, part_d, part_o);
   DD_HIP(hipGetLastError());
-  hipLaunchKernelGGL(merge_direct_kernel, dim3(grid1(list_len_max)), dim3(256), 0, st, L, S, pd, po,
-                     Q.invalid, out);
+  hipLaunchKernelGGL(merge_direct_kernel, dim3(grid1(list_len_max)), dim3(256), 0, st, L, S, part_d,
+                     part_o, Q.invalid, out);
   DD_HIP(hipGetLastError());
-  if (own) {
-    DD_HIP(hipFreeAsync(pd, st));
-    DD_HIP(hipFreeAsync(po, st));
-  }
   return DD_OK;
 }
 

@@ -29,3 +29,33 @@ def test_mask_rows_are_aligned(tmp_path):
         assert all(p % 16 == 0 for p, w in rows if w % 4 == 0)
         """)
     assert out
+
+
+@pytest.mark.parametrize("packs", ["FP64 | ANN | BF16", "FP64 | FP32", "FP64 | KMEANS | FP16"])
+def test_idle_memory_fails_no_allocation(tmp_path, packs):
+    """What the library holds without using it (idle temporaries of a creation, blocks of
+    destroyed objects) is given up before an allocation fails, of any size: what can be
+    created in some memory can be created in more, and after a destroyed data set too."""
+    scenario(tmp_path, f"""
+        n, ok = 1 << 18, []
+        base = hip.fake_live()
+        for mb in range(20, 140, 1):
+            hip.fake_limit(base + (mb << 20))
+            rc, ds = create(dd, n, {packs})
+            assert rc in (0, 3)
+            ok.append(rc == 0)
+            if rc == 0:
+                dd.dd_dataset_destroy(ds)
+            dd.dd_dataset_destroy(None)
+        print(ok)
+        assert not ok[0] and all(ok[ok.index(True):]), "created in less memory than this"
+        hip.fake_limit(base + (400 << 20))
+        rc, ds = create(dd, n, {packs})
+        dd.dd_dataset_destroy(ds)
+        assert hip.fake_live() > base                 # kept blocks
+        hip.fake_limit(hip.fake_live())               # and not a byte beside them
+        rc, ds = create(dd, 100, FP64)                # small buffers only
+        assert rc == 0, dd.dd_last_error()
+        rc = project(dd, ds, 5000, "fp64")            # stream-ordered scratch
+        assert rc == 0, dd.dd_last_error()
+        """)
