@@ -122,7 +122,7 @@ typedef enum dd_mode {
 #define DD_PACK_ANN 0x10u   /* box tree over the sorted order, compact leaves (implies FP64): DD_ANN */
 #define DD_PACK_KMEANS 0x20u /* k-means tree, compact leaves (implies FP64): DD_KMEANS */
 /* A data set with a tree, 2^13 to 2^24 points and no 16-bit pack keeps the FP16 one for
- * its exact searches as well (36 bytes a point), if the device has room for it;
+ * its exact searches as well (32 bytes a point), if the device has room for it;
  * DD_MIXED_FP16 stays unavailable on it. */
 #define DD_PACK_DEFAULT (DD_PACK_FP64 | DD_PACK_BF16)
 

@@ -862,19 +862,8 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
   // boxes of the scans' tiles
   DD_TRY(build_tile_boxes(D, kTile64, nullptr, D.boxes, st));
 
-  // 5. tile-centred 16-bit packs, from the sorted FP64 pack; a data set with a
-  // tree holds one for its exact searches too, as long as the device has room
-  if (packs & (DD_PACK_BF16 | DD_PACK_FP16)) {
-    DD_TRY(build_pack16(D, packs, tile, st));
-  } else if ((packs & (DD_PACK_ANN | DD_PACK_KMEANS)) && N >= kTreeScanMin && N <= kTreeScanMax) {
-    const dd_status rc = build_pack16(D, DD_PACK_FP16, tile, st);
-    if (rc == DD_ERR_OOM) {
-      DD_HIP(hipStreamSynchronize(st));
-      D.wfp16.release();
-    } else {
-      DD_TRY(rc);
-    }
-  }
+  // 5. tile-centred 16-bit packs, from the sorted FP64 pack
+  if (packs & (DD_PACK_BF16 | DD_PACK_FP16)) DD_TRY(build_pack16(D, packs, tile, st));
 
   // 6. ANN box tree over the sorted order
   if (packs & DD_PACK_ANN) {
@@ -916,6 +905,21 @@ static dd_status create_impl(Source& src, int64_t N, const double* C, const dd_d
 
   // 7. k-means tree over the sorted order
   if (packs & DD_PACK_KMEANS) DD_TRY(build_kmeans_tree(D, pool, st));
+
+  // 8. the 16-bit pack of a tree's exact searches, last: nobody asked for it, so
+  // it takes only what everything else leaves
+  if ((packs & (DD_PACK_ANN | DD_PACK_KMEANS)) && !(packs & (DD_PACK_BF16 | DD_PACK_FP16)) &&
+      N >= kTreeScanMin && N <= kTreeScanMax) {
+    const dd_status rc = build_pack16(D, DD_PACK_FP16, tile, st);
+    if (rc == DD_ERR_OOM) {
+      DD_HIP(hipStreamSynchronize(st));
+      for (DevBuf* b : {&D.wfp16, &D.centre, &D.radius, &D.boxes16.tile, &D.boxes16.chunk, &D.boxes16.root})
+        b->release();
+      D.boxes16.n_tiles = D.n_tiles = 0;
+    } else {
+      DD_TRY(rc);
+    }
+  }
   DD_HIP(hipStreamSynchronize(st));
   return DD_OK;
 }

@@ -163,7 +163,7 @@ constexpr int kKmtRecord = 20;     // floats per k-means tree child record (80 B
 
 // projection modes that walk a tree (warm starts, budgets, skipping)
 inline bool walk_mode(int mode) { return mode == DD_ANN || mode == DD_KMEANS; }
-// Sizes of the data sets with a tree that also hold a 16-bit pack (36 bytes a
+// Sizes of the data sets with a tree that also hold a 16-bit pack (32 bytes a
 // point) for exact searches by scan (scan_for_walk).
 constexpr int64_t kTreeScanMin = (int64_t)1 << 13, kTreeScanMax = (int64_t)1 << 24;
 constexpr int kAnnMaxLevels = 6;   // 64^6 leaves exceed any N <= 2^31 - 1

@@ -59,3 +59,29 @@ def test_idle_memory_fails_no_allocation(tmp_path, packs):
         rc = project(dd, ds, 5000, "fp64")            # stream-ordered scratch
         assert rc == 0, dd.dd_last_error()
         """)
+
+
+@pytest.mark.parametrize("packs", ["ANN", "KMEANS", "ANN | KMEANS"])
+def test_unrequested_pack_takes_what_is_left(tmp_path, packs):
+    """The 16-bit pack that a tree's exact searches use fails no creation: what can be
+    created in some memory can be created in more.  Where it finds no room it leaves
+    nothing behind, and the searches walk."""
+    scenario(tmp_path, f"""
+        n, sizes = 1 << 20, []
+        base = hip.fake_live()
+        for mb in range(90, 400, 3):
+            hip.fake_limit(base + (mb << 20))
+            rc, ds = create(dd, n, FP64 | {packs})
+            assert rc in (0, 3)
+            sizes.append(held(dd, ds) if rc == 0 else 0)
+            if rc == 0:
+                dd.dd_project(ds, vp(4096), 600, None, ctypes.byref(ProjectOpts(MODE["{packs.split()[0].lower()}"])), vp(4096), None, None)
+                dd.dd_dataset_destroy(ds)
+            dd.dd_dataset_destroy(None)
+        least = next(i for i, s in enumerate(sizes) if s)
+        print(sizes)
+        assert least > 0 and all(sizes[least:]), "created in less memory than this"
+        without, whole = sizes[least], sizes[-1]
+        assert whole - without >= 32 * n            # no part of the pack stays without the rest
+        assert set(sizes) == {{0, without, whole}}
+        """)
