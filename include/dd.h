@@ -219,9 +219,8 @@ dd_status dd_dataset_create_streamed(int64_t N, const double* C, dd_fill_fn fill
 
 /* Release a dataset's device memory.  Up to 8 GiB of released memory per device stays
  * with the process for its next allocations (memory given to the driver is cleared at
- * about 40 GB/s before it is given out again), for at most 5 seconds as seen by the
- * library's next call, and is given up at once when an allocation of the library fails;
- * NULL gives it up now. */
+ * about 40 GB/s before it is given out again), each block for at most 5 seconds, and is
+ * given up at once when an allocation of the library fails; NULL gives it up now. */
 dd_status dd_dataset_destroy(dd_dataset* ds);
 
 /* Number of points, and bytes of device memory the dataset holds: its packs and

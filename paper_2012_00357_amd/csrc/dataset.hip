@@ -971,7 +971,7 @@ extern "C" dd_status dd_dataset_create_streamed(int64_t N, const double* C, dd_f
 
 extern "C" dd_status dd_dataset_destroy(dd_dataset* ds) {
   delete ds;
-  if (!ds) dd::device_pool_trim(true);
+  if (!ds) dd::device_pool_trim();
   return DD_OK;
 }
 

@@ -40,16 +40,16 @@ dd_status set_error(dd_status st, const std::string& msg);
 // process (or those before it) has been through the device's memory, every
 // creation waits for that (2^25 points with BF16 pack and box tree, 6.5 GB: 157 to 173
 // ms where the driver has no clean memory left, 20 where it has, 16 from here).
-// At most kPoolBytes are kept per device, for at most
-// kPoolSeconds after their release (checked at each allocation, release and
-// projection); an allocation that fails frees them all and is tried again, and so
+// At most kPoolBytes are kept per device, each block for at most kPoolSeconds after
+// its release (a thread of the library frees it then, whether the program calls the
+// library or not); an allocation that fails frees them all and is tried again, and so
 // does dd_dataset_destroy(NULL).  A block is kept only once the device has
 // finished with it, so that any stream may have it next.
 constexpr size_t kPoolBytes = (size_t)8 << 30;
 constexpr int kPoolSeconds = 5;
 hipError_t device_alloc(void** p, size_t n);
 void device_free(void* p);
-void device_pool_trim(bool all);   // frees what has been kept for too long, or all
+void device_pool_trim();   // frees every kept block
 // Returns to the driver what the library holds on the device without using it: the
 // idle temporaries of the creation that runs on this thread, and every kept block.
 void device_give_back();

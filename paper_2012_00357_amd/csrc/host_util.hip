@@ -1,10 +1,16 @@
 // Host utilities: error reporting, device buffers, small dense linear algebra.
-#include <atomic>
+#include <unistd.h>
+
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
+#include <cstdlib>
 #include <cstring>
 #include <list>
 #include <mutex>
+#include <new>
+#include <system_error>
+#include <thread>
 #include <unordered_map>
 
 #include "dd_internal.h"
@@ -31,7 +37,10 @@ struct Pool {
   std::mutex mu;
   std::unordered_map<void*, std::pair<size_t, int>> out;   // blocks in use: size, device
   std::list<PoolBlock> idle;                               // oldest first
-  std::atomic<int> n_idle{0};
+  std::condition_variable cv;                              // for the reaper: a first block, or stop
+  std::thread reaper;
+  pid_t pid = 0;                                           // the process it runs in
+  bool stop = false;
 };
 constexpr size_t kPoolLeast = (size_t)1 << 20;
 // Never destroyed: objects released at exit may still come here.
@@ -40,44 +49,77 @@ Pool& pool() {
   return *p;
 }
 
-// Takes the idle blocks that `which` accepts out of the pool and frees them outside its lock.
-template <class F>
-void pool_drop(F which) {
-  std::vector<void*> gone;
-  {
-    Pool& P = pool();
-    std::lock_guard<std::mutex> lk(P.mu);
-    for (auto it = P.idle.begin(); it != P.idle.end();) {
-      if (which(*it)) {
-        gone.push_back(it->p);
-        it = P.idle.erase(it);
-      } else {
-        ++it;
-      }
+// Frees blocks whose time is over, with no call of the library needed for it.
+void reap() {
+  Pool& P = pool();
+  // hipFree here must not end a capture that some other thread of the program has open
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  std::unique_lock<std::mutex> lk(P.mu);
+  while (!P.stop) {
+    if (P.idle.empty()) {
+      P.cv.wait(lk);
+      continue;
     }
-    P.n_idle = (int)P.idle.size();
+    const auto due = P.idle.front().since + std::chrono::seconds(kPoolSeconds);
+    if (PoolClock::now() < due) {
+      P.cv.wait_until(lk, due);
+      continue;
+    }
+    void* p = P.idle.front().p;
+    P.idle.pop_front();
+    lk.unlock();
+    (void)hipFree(p);
+    lk.lock();
   }
-  for (void* p : gone) (void)hipFree(p);
+}
+
+// Ends the reaper before the HIP runtime's own end.  (A child made by fork has no such
+// thread, only its record.)
+void stop_reaper() {
+  Pool& P = pool();
+  if (P.pid != getpid()) return;
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    P.stop = true;
+  }
+  P.cv.notify_one();
+  if (P.reaper.joinable()) P.reaper.join();
+}
+
+// Whether a block may be kept: the reaper runs in this process (P.mu held).
+bool reaper_runs(Pool& P) {
+  if (P.pid == 0) {
+    P.pid = getpid();
+    try {
+      if (std::atexit(stop_reaper) == 0) P.reaper = std::thread(reap);
+    } catch (const std::system_error&) {
+    }
+  }
+  return P.reaper.joinable() && !P.stop && P.pid == getpid();
 }
 
 }  // namespace
 
-void device_pool_trim(bool all) {
-  if (pool().n_idle.load() == 0) return;
-  const auto old = PoolClock::now() - std::chrono::seconds(kPoolSeconds);
-  pool_drop([&](const PoolBlock& b) { return all || b.since < old; });
+void device_pool_trim() {
+  std::list<PoolBlock> gone;
+  {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    gone.swap(P.idle);
+  }
+  for (const PoolBlock& b : gone) (void)hipFree(b.p);
 }
 
 static thread_local TempPool* t_temps = nullptr;
 
 void device_give_back() {
   if (t_temps) t_temps->trim();
-  device_pool_trim(true);
+  device_pool_trim();
 }
 
 hipError_t device_alloc(void** p, size_t n) {
   if (n < kPoolLeast) return alloc_or_give_back([&] { return hipMalloc(p, n); });
-  device_pool_trim(false);
   Pool& P = pool();
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -91,16 +133,21 @@ hipError_t device_alloc(void** p, size_t n) {
         best = it;
     if (best != P.idle.end()) {
       *p = best->p;
-      P.out[best->p] = {best->size, dev};
+      try {
+        P.out[best->p] = {best->size, dev};
+      } catch (const std::bad_alloc&) {
+      }
       P.idle.erase(best);
-      P.n_idle = (int)P.idle.size();
       return hipSuccess;
     }
   }
   e = alloc_or_give_back([&] { return hipMalloc(p, n); });
   if (e == hipSuccess) {
     std::lock_guard<std::mutex> lk(P.mu);
-    P.out[*p] = {n, dev};
+    try {
+      P.out[*p] = {n, dev};
+    } catch (const std::bad_alloc&) {   // not known: not kept
+    }
   }
   return e;
 }
@@ -124,27 +171,33 @@ void device_free(void* p) {
     (void)hipFree(p);
     return;
   }
-  std::vector<void*> gone;
+  std::list<PoolBlock> gone;
+  try {
+    gone.push_back(b);
+  } catch (const std::bad_alloc&) {
+    (void)hipFree(p);
+    return;
+  }
   {
     std::lock_guard<std::mutex> lk(P.mu);
-    size_t total = b.size;
-    for (const PoolBlock& k : P.idle)
-      if (k.device == dev) total += k.size;
-    for (auto it = P.idle.begin(); total > kPoolBytes && it != P.idle.end();) {   // the oldest go
-      if (it->device != dev) {
-        ++it;
-        continue;
+    gone.front().since = PoolClock::now();
+    if (reaper_runs(P)) {
+      if (P.idle.empty()) P.cv.notify_one();
+      P.idle.splice(P.idle.end(), gone);
+      size_t total = 0;
+      for (const PoolBlock& k : P.idle)
+        if (k.device == dev) total += k.size;
+      for (auto it = P.idle.begin(); total > kPoolBytes;) {   // the oldest go
+        const auto next = std::next(it);
+        if (it->device == dev) {
+          total -= it->size;
+          gone.splice(gone.end(), P.idle, it);
+        }
+        it = next;
       }
-      total -= it->size;
-      gone.push_back(it->p);
-      it = P.idle.erase(it);
     }
-    b.since = PoolClock::now();
-    P.idle.push_back(b);
-    P.n_idle = (int)P.idle.size();
   }
-  for (void* g : gone) (void)hipFree(g);
-  device_pool_trim(false);
+  for (const PoolBlock& g : gone) (void)hipFree(g.p);
 }
 
 dd_status DevBuf::alloc(size_t n) {

@@ -751,7 +751,6 @@ dd_status project_impl_ex(const Dataset& D, const double* states_dev, bool white
                           ScratchArena* fixed) {
   if (m < 0 || m > 0x7FFFFFFFll) return set_error(DD_ERR_ARG, "m must be in [0, 2^31-1]");
   if (m == 0) return DD_OK;
-  device_pool_trim(false);
   if (!states_dev || !idx_out_dev) return set_error(DD_ERR_ARG, "NULL states or idx_out");
   const int mode = opts ? opts->mode : DD_EXACT_FP64;
   const int splits = opts ? opts->splits : 0;

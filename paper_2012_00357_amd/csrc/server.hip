@@ -670,7 +670,7 @@ extern "C" dd_status dd_server_create(const dd_dataset* ds, size_t hbm_budget_by
   DD_HIP(hipSetDevice(D.device));
   if (hbm_budget_bytes == 0) {
     size_t fr = 0, tot = 0;
-    device_pool_trim(true);   // what is kept for the next allocation is free memory
+    device_pool_trim();   // what is kept for the next allocation is free memory
     DD_HIP(hipMemGetInfo(&fr, &tot));
     hbm_budget_bytes = fr / 2;
   }

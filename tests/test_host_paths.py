@@ -85,3 +85,28 @@ def test_unrequested_pack_takes_what_is_left(tmp_path, packs):
         assert whole - without >= 32 * n            # no part of the pack stays without the rest
         assert set(sizes) == {{0, without, whole}}
         """)
+
+
+def test_kept_memory_goes_without_a_call(tmp_path):
+    """Released blocks leave the process after their five seconds although the program does
+    not call the library again, and the process ends normally with some kept (also where
+    a child process of it ended first)."""
+    scenario(tmp_path, """
+        import os
+        base = hip.fake_live()
+        rc, ds = create(dd, 1 << 18, FP64 | BF16)
+        dd.dd_dataset_destroy(ds)
+        kept = hip.fake_live() - base
+        assert kept > 20 << 20
+        t = time.time()
+        while hip.fake_live() > base and time.time() - t < 8.0:
+            time.sleep(0.05)
+        assert hip.fake_live() == base and 4.0 < time.time() - t < 7.0
+        rc, ds = create(dd, 1 << 18, FP64 | BF16)
+        dd.dd_dataset_destroy(ds)
+        assert hip.fake_live() > base
+        child = os.fork()
+        if child == 0:
+            sys.exit(0)          # runs the exit handlers, without the thread
+        assert os.waitpid(child, 0)[1] == 0
+        """)
