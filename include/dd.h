@@ -217,10 +217,12 @@ dd_status dd_dataset_create_streamed(int64_t N, const double* C, dd_fill_fn fill
                                      const dd_dataset_opts* opts, void* hip_stream,
                                      dd_dataset** out);
 
-/* Release a dataset's device memory.  Up to 8 GiB of released memory per device stays
- * with the process for its next allocations (memory given to the driver is cleared at
- * about 40 GB/s before it is given out again), each block for at most 5 seconds, and is
- * given up at once when an allocation of the library fails; NULL gives it up now. */
+/* Release a dataset's device memory.  Of the blocks that the creation, projections and
+ * solves on a dataset have released, up to 8 GiB per device stay with the process for
+ * the next ones of the same size (memory given to the driver is cleared at about 40 GB/s
+ * before it is given out again), each for at most 5 seconds, and are given up at once
+ * when an allocation of the library fails; NULL gives them up now.  A server's memory
+ * (dd_server_create) is never kept. */
 dd_status dd_dataset_destroy(dd_dataset* ds);
 
 /* Number of points, and bytes of device memory the dataset holds: its packs and

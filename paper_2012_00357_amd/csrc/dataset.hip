@@ -946,6 +946,7 @@ extern "C" dd_status dd_dataset_create(const double* strain, const double* stres
   *out = nullptr;
   if (!strain || !stress || !C) return dd::set_error(DD_ERR_ARG, "NULL input pointer");
   if (N < 1 || N > 0x7FFFFFFFll) return dd::set_error(DD_ERR_ARG, "N must be in [1, 2^31-1]");
+  dd::KeepScope keep;
   if (opts && (opts->flags & DD_DATASET_HOST_INPUT)) {
     dd::HostSource src(strain, stress, N);
     dd_status s = src.init();
@@ -963,6 +964,7 @@ extern "C" dd_status dd_dataset_create_streamed(int64_t N, const double* C, dd_f
   *out = nullptr;
   if (!fill || !C) return dd::set_error(DD_ERR_ARG, "NULL producer or metric");
   if (N < 1 || N > 0x7FFFFFFFll) return dd::set_error(DD_ERR_ARG, "N must be in [1, 2^31-1]");
+  dd::KeepScope keep;
   dd::FillSource src(fill, user, N);
   dd_status s = src.init();
   if (s != DD_OK) return s;

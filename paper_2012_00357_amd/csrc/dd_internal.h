@@ -34,19 +34,32 @@ dd_status set_error(dd_status st, const std::string& msg);
     if (s_ != DD_OK) return s_;       \
   } while (0)
 
-// Device memory of the host objects below.  A released block of 1 MiB and more is
-// kept for the next allocation of about its size: memory given to the driver is
-// cleared by it before it is given out again, at about 40 GB/s, and once a
-// process (or those before it) has been through the device's memory, every
-// creation waits for that (2^25 points with BF16 pack and box tree, 6.5 GB: 157 to 173
-// ms where the driver has no clean memory left, 20 where it has, 16 from here).
+// Device memory of the host objects below.  A released block of 1 MiB and more that
+// was allocated in a KeepScope is kept for the next such allocation of its size:
+// memory given to the driver is cleared by it before it is given out again, at about
+// 40 GB/s, and once a process (or those before it) has been through the device's
+// memory, every creation waits for that (2^25 points with BF16 pack and box tree, 6.5
+// GB: 157 to 173 ms where the driver has no clean memory left, 20 where it has, 16
+// from here).
 // At most kPoolBytes are kept per device, each block for at most kPoolSeconds after
 // its release (a thread of the library frees it then, whether the program calls the
 // library or not); an allocation that fails frees them all and is tried again, and so
 // does dd_dataset_destroy(NULL).  A block is kept only once the device has
-// finished with it, so that any stream may have it next.
+// finished with it, so that any stream may have it next.  The scopes are the calls that
+// create a data set, project or solve; what a server allocates goes back to the
+// driver at once, as its budget says.
 constexpr size_t kPoolBytes = (size_t)8 << 30;
 constexpr int kPoolSeconds = 5;
+class KeepScope {   // of the thread's allocations
+ public:
+  KeepScope();
+  ~KeepScope();
+  KeepScope(const KeepScope&) = delete;
+  KeepScope& operator=(const KeepScope&) = delete;
+
+ private:
+  bool before;
+};
 hipError_t device_alloc(void** p, size_t n);
 void device_free(void* p);
 void device_pool_trim();   // frees every kept block

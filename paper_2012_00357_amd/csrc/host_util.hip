@@ -118,26 +118,26 @@ void device_give_back() {
   device_pool_trim();
 }
 
+static thread_local bool t_keep = false;
+KeepScope::KeepScope() : before(t_keep) { t_keep = true; }
+KeepScope::~KeepScope() { t_keep = before; }
+
 hipError_t device_alloc(void** p, size_t n) {
-  if (n < kPoolLeast) return alloc_or_give_back([&] { return hipMalloc(p, n); });
+  if (n < kPoolLeast || !t_keep) return alloc_or_give_back([&] { return hipMalloc(p, n); });
   Pool& P = pool();
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   {
     std::lock_guard<std::mutex> lk(P.mu);
-    auto best = P.idle.end();
-    for (auto it = P.idle.begin(); it != P.idle.end(); ++it)
-      if (it->device == dev && it->size >= n && it->size <= n + n / 8 &&
-          (best == P.idle.end() || it->size < best->size))
-        best = it;
-    if (best != P.idle.end()) {
-      *p = best->p;
+    for (auto it = P.idle.begin(); it != P.idle.end(); ++it) {
+      if (it->device != dev || it->size != n) continue;
+      *p = it->p;
       try {
-        P.out[best->p] = {best->size, dev};
+        P.out[it->p] = {n, dev};
       } catch (const std::bad_alloc&) {
       }
-      P.idle.erase(best);
+      P.idle.erase(it);
       return hipSuccess;
     }
   }

@@ -831,6 +831,7 @@ extern "C" dd_status dd_project(const dd_dataset* ds, const double* states_dev, 
                                 const int64_t* warm_start_idx_dev, const dd_project_opts* opts,
                                 int64_t* idx_out_dev, double* dist_out_dev, void* hip_stream) {
   if (!ds) return dd::set_error(DD_ERR_ARG, "dataset is NULL");
+  dd::KeepScope keep;
   return dd::project_impl(ds->d, states_dev, false, m, warm_start_idx_dev, opts, idx_out_dev,
                           dist_out_dev, static_cast<hipStream_t>(hip_stream));
 }

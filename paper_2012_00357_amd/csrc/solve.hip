@@ -1349,6 +1349,7 @@ extern "C" dd_status dd_solve(const dd_dataset* ds, const dd_mesh* mesh,
   if (!ds || !mesh || !dirichlet_mask || !nodal_force || !init_idx)
     return set_error(DD_ERR_ARG, "dd_solve: NULL argument");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  KeepScope keep;
   DDSolver S;
   DD_TRY(S.setup(ds->d, *mesh, dirichlet_mask, nodal_force, opts, st));
   DD_TRY(S.set_assignment(init_idx));

@@ -110,3 +110,46 @@ def test_kept_memory_goes_without_a_call(tmp_path):
             sys.exit(0)          # runs the exit handlers, without the thread
         assert os.waitpid(child, 0)[1] == 0
         """)
+
+
+def test_server_memory_is_not_kept(tmp_path):
+    """What a server allocates goes back to the driver when it releases it: its budget
+    bounds what it holds, and nothing of it stays behind."""
+    scenario(tmp_path, """
+        rc, ds = create(dd, 1 << 18, FP64 | BF16)
+        dd.dd_dataset_destroy(None)
+        base = hip.fake_live()
+        budget = 400 << 20
+        hip.fake_peak()
+        rc, srv = server(dd, ds, budget, "bf16", 4096)
+        assert rc == 0, dd.dd_last_error()
+        for n in (6, 8, 7):                    # operators of 10 to 38 MB, formed and kept by the data set
+            assert dd.dd_server_wait(srv, submit(dd, srv, n, n, n), None, 60.0) in (0, 5)
+        assert hip.fake_peak() - base <= budget
+        operators = 8 * sum(((3 * (n + 1) ** 3 + 63) // 64 * 64) ** 2 for n in (6, 8, 7))
+        reserve = stats(dd, srv).reserve_bytes
+        slack = 1 << 20                        # buffers below 256 bytes, rounded up
+        assert hip.fake_live() - base <= reserve + operators + slack, (hip.fake_live() - base, reserve, operators)
+        dd.dd_server_destroy(srv)
+        assert hip.fake_live() - base <= operators + slack
+        dd.dd_dataset_destroy(ds)
+        dd.dd_dataset_destroy(None)
+        """)
+
+
+def test_kept_blocks_are_counted_as_they_are(tmp_path):
+    """A data set in blocks that another one left is as large as in its own."""
+    scenario(tmp_path, """
+        sizes = []
+        for first in (0, 290_000, 262_144):
+            if first:
+                rc, ds = create(dd, first, FP64 | BF16)
+                dd.dd_dataset_destroy(ds)
+            rc, ds = create(dd, 1 << 18, FP64 | BF16)
+            before = hip.fake_live()
+            dd.dd_dataset_destroy(None)        # what is left is the data set's
+            sizes.append((held(dd, ds), hip.fake_live()))
+            dd.dd_dataset_destroy(ds)
+            dd.dd_dataset_destroy(None)
+        assert len(set(sizes)) == 1, sizes
+        """)
