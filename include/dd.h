@@ -90,7 +90,8 @@ typedef enum dd_mode {
    * budget it stops after that many leaves (64 points each) and is approximate
    * (never worse than the warm-start point).  An exact call that asks for no
    * statistics finds the same answers by a 16-bit scan where that is sooner (data
-   * sets of 2^13 to 2^24 points; scan_for_walk in project.hip). */
+   * sets of 2^13 to 2^24 points; scan_for_walk in project.hip).  Such a call with
+   * statistics walks, and so does a server's batch. */
   DD_ANN = 3,
   /* Plain FP64 direct-form scan (VALU), the simplest exact kernel. */
   DD_DIRECT_FP64 = 4,

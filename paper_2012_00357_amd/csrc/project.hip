@@ -29,6 +29,11 @@ struct Scratch {
   ScratchArena* arena() const { return fixed ? fixed : a.get(); }
   // bytes left in a caller's block; SIZE_MAX with the dataset's arenas
   size_t room() const { return fixed ? fixed->bytes - off : SIZE_MAX; }
+  // a caller's block: hands back what has been carved since off was `mark`, for
+  // kernels queued behind those that use it
+  void rewind(size_t mark) {
+    if (fixed) off = mark;
+  }
   dd_status open() {
     if (fixed) {
       DD_HIP(hipStreamWaitEvent(st, fixed->done, 0));
@@ -198,12 +203,18 @@ dd_status direct_from(const Dataset& D, const QueryPrep& Q, QueryList L2, int64_
 // runs of queries.
 constexpr size_t kMaskBytes = (size_t)256 << 20;
 
-// Queries of one run (whole mask words) whose masks fit in `room` bytes.
+// Work entries of a run's tiles: launch_plan cuts a tile's groups into parts of a mask
+// word's 32 at least.
+size_t mask_entries(int64_t n_tiles, int words) {
+  return (size_t)n_tiles * std::min(words, kMaskParts);
+}
+// Queries of one run (whole mask words) whose masks and entries fit in `room` bytes.
 int64_t mask_run(int64_t n_tiles, int64_t m, int sub, size_t room) {
-  const size_t word = (size_t)n_tiles * 8;   // of mask and left
-  const int64_t words = (int64_t)(std::min(room, kMaskBytes) / word);
+  const size_t word = (size_t)n_tiles * 8;   // of mask and left, and of a part's entries
+  size_t words = std::min(room / (2 * word), (size_t)kMaskParts);
+  if (words == kMaskParts) words = std::min(room / word - kMaskParts, kMaskBytes / word);
   return std::min<int64_t>(std::min<int64_t>(m, kMaskQueries),
-                           std::max<int64_t>(words, 1) * 32 * sub);
+                           (int64_t)std::max<size_t>(words, 1) * 32 * sub);
 }
 // Words of one of a run's two mask arrays, whose rows plan_kernel reads 16 bytes at a
 // time: both begin at a multiple of four words, whatever the widths of the runs.
@@ -212,7 +223,7 @@ size_t mask_len(int64_t n_tiles, int64_t run, int sub) {
 }
 size_t mask_bytes(int64_t n_tiles, int64_t run, int sub) {
   return aligned(8 * mask_len(n_tiles, run, sub) + 16) +
-         aligned((size_t)n_tiles * kMaskParts * sizeof(uint2));
+         aligned(mask_entries(n_tiles, mask_words(run, sub)) * sizeof(uint2));
 }
 dd_status alloc_masks(Scratch& sc, int64_t n_tiles, int64_t run, int sub, TileMasks& M) {
   const size_t len = mask_len(n_tiles, run, sub);
@@ -223,7 +234,7 @@ dd_status alloc_masks(Scratch& sc, int64_t n_tiles, int64_t run, int sub, TileMa
   M.n_entry = z;
   M.mask = z + 4;
   M.left = M.mask + len;
-  DD_TRY(sc.get(M.entry, (size_t)n_tiles * kMaskParts));
+  DD_TRY(sc.get(M.entry, mask_entries(n_tiles, mask_words(run, sub))));
   M.sub = sub;
   return DD_OK;
 }
@@ -299,19 +310,26 @@ int group_key_bits(int64_t m) {
   while (b < kGroupKeyBits && ((int64_t)1 << b) < m) ++b;
   return b;
 }
-// Scratch of a culled FP64 scan beside the prepared queries, with masks for one
-// word of queries at a time (the least it needs).
-size_t culled_bytes(const Dataset& D, int64_t m) {
-  const size_t n = (size_t)m;
-  return 2 * aligned(n * 12 * 4) + aligned(n * 2) + ((size_t)4 << group_key_bits(m)) +
-         aligned(n * 12 * 8) + 2 * aligned(n * 8) + 3 * aligned(n * 4) + aligned(n * 64) +   // sorted
-         2 * aligned(n * kCulledK * 4) + 2 * aligned(n * 4) + aligned(n * 8) + aligned(n * 4) +
-         mask_bytes(D.boxes.n_tiles, 1, 16) + exact64_bytes(m, 1) + 2 * kAlignSlack;
+// Mask bits of a culled scan's queries, and its tiles.
+int cull_sub(int mode) { return mode == DD_EXACT_FP64 ? 16 : 32; }
+const TileBoxes& cull_boxes(const Dataset& D, int mode) {
+  return mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16 ? D.boxes16 : D.boxes;
 }
-// Scratch of the prepared queries and the counters.
-size_t prepared_bytes(int64_t m) {
+// Scratch that culled_scan carves at least, with masks for one word of queries at a time.
+size_t culled_bytes(const Dataset& D, int mode, int64_t m) {
   const size_t n = (size_t)m;
-  return aligned(n * 12 * 8) + 2 * aligned(n * 8) + 2 * aligned(n * 4) + (64 << 10) + kAlignSlack;
+  return aligned(n * 12 * 8) + aligned(n * 12 * 4) + 2 * aligned(n * 8) + 3 * aligned(n * 4) +   // sorted
+         aligned(n * 16 * 4) + 2 * aligned(n * kCulledK * 4) + aligned(n * 4) +
+         mask_bytes(cull_boxes(D, mode).n_tiles, 1, cull_sub(mode)) + kAlignSlack;
+}
+// Scratch of a whole culled call: the prepared queries, their cells, the counters
+// and the fallback list, beside them the scan or, after it, the fallback of every query.
+size_t culled_call_bytes(const Dataset& D, int mode, int64_t m) {
+  const size_t n = (size_t)m;
+  const size_t after = mode == DD_EXACT_FP64 ? n * kDirectBytes : exact64_bytes(m, 1);
+  return aligned(n * 12 * 8) + aligned(n * 12 * 4) + 2 * aligned(n * 8) + 3 * aligned(n * 4) +
+         aligned(n * 2) + ((size_t)4 << group_key_bits(m)) + (64 << 10) +
+         std::max(culled_bytes(D, mode, m), after + 2 * kAlignSlack);
 }
 // Whether a scan of m queries is culled.  Culling costs about nine small launches
 // (50 us) and leaves few of the pairs of a large data set: at 2^23 points it
@@ -352,10 +370,12 @@ int scan_for_walk(const Dataset& D, int64_t m) {
 // A culled scan in `mode` of m prepared queries (with their coordinates on the
 // principal axes): all of them, sorted by their cells, or those of list L in
 // its order; merge and FP64 rerank.  n_left: the queries the scan leaves (their
-// list overflowed, or the mode's scan does not take them), in fb / fb_count.
+// list overflowed, or the mode's scan does not take them), in fb / fb_count.  Its
+// scratch in a caller's block is free again afterwards, for their fallback.
 dd_status culled_scan(const Dataset& D, int mode, const QueryPrep& Q, QueryList L, int64_t m,
-                      float u32_scale, Outputs out, Scratch& sc, int* d_counters, int* fb_count,
-                      hipStream_t st, int*& fb, int64_t& n_left, Timing* tm) {
+                      float u32_scale, Outputs out, Scratch& sc, int* d_counters, int* fb, int* fb_count,
+                      hipStream_t st, int64_t& n_left, Timing* tm) {
+  const size_t mark = sc.off;
   QueryPrep R;
   int* order = nullptr;
   DD_TRY(alloc_sorted(sc, m, R, order));
@@ -365,13 +385,12 @@ dd_status culled_scan(const Dataset& D, int mode, const QueryPrep& Q, QueryList 
   DD_TRY(sc.get(cb.lb, (size_t)m * cb.K));
   DD_TRY(sc.get(cb.j, (size_t)m * cb.K));
   DD_TRY(sc.get(cb.count, (size_t)m));
-  DD_TRY(sc.get(fb, (size_t)m));
   DD_HIP(hipMemsetAsync(cb.count, 0, sizeof(int) * (size_t)m, st));
   const bool scan16 = mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16;
   if (scan16) DD_TRY(sc.get(R.q16, (size_t)m * 16));
-  const TileBoxes& B = scan16 ? D.boxes16 : D.boxes;
-  const int sub = mode == DD_EXACT_FP64 ? 16 : 32;
-  const size_t keep = kAlignSlack + mask_bytes(B.n_tiles, 0, sub) + exact64_bytes(m, 1);
+  const TileBoxes& B = cull_boxes(D, mode);
+  const int sub = cull_sub(mode);
+  const size_t keep = 1024;   // alignment of masks and entries
   const size_t room = sc.room() == SIZE_MAX ? SIZE_MAX : sc.room() > keep ? sc.room() - keep : 0;
   const int64_t run = mask_run(B.n_tiles, m, sub, room);
   TileMasks M;
@@ -412,6 +431,7 @@ dd_status culled_scan(const Dataset& D, int mode, const QueryPrep& Q, QueryList 
   DD_HIP(hipMemcpyAsync(hw, fb_count, sizeof(int), hipMemcpyDeviceToHost, st));
   DD_HIP(hipStreamSynchronize(st));
   n_left = (int64_t)*hw;
+  sc.rewind(mark);
   return DD_OK;
 }
 
@@ -420,12 +440,15 @@ dd_status culled_scan(const Dataset& D, int mode, const QueryPrep& Q, QueryList 
 // direct scan of what it leaves.  u32_scale: the scale Q.u32 is in.
 dd_status fallback64(const Dataset& D, const QueryPrep& Q, QueryList L, int64_t h, float u32_scale,
                      Outputs out, Scratch& sc, int* d_counters, hipStream_t st) {
-  if (!Q.yq || sc.room() != SIZE_MAX || !cull_pays(D, DD_EXACT_FP64, h, false))
+  if (!Q.yq || !cull_pays(D, DD_EXACT_FP64, h, false) ||
+      (sc.room() != SIZE_MAX &&
+       sc.room() < aligned((size_t)h * sizeof(int)) + culled_bytes(D, DD_EXACT_FP64, h)))
     return exact64(D, Q, L, h, 0, out, sc, d_counters, st, nullptr, nullptr);
   int* fb = nullptr;
+  DD_TRY(sc.get(fb, (size_t)h));
   int64_t left = 0;
-  DD_TRY(culled_scan(D, DD_EXACT_FP64, Q, L, h, u32_scale, out, sc, d_counters, d_counters + 1, st,
-                     fb, left, nullptr));
+  DD_TRY(culled_scan(D, DD_EXACT_FP64, Q, L, h, u32_scale, out, sc, d_counters, fb, d_counters + 1, st,
+                     left, nullptr));
   if (left == 0) return DD_OK;
   return direct_from(D, Q, QueryList{fb, d_counters + 1, left}, left, 0, out, sc, st);
 }
@@ -542,7 +565,7 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
   Scratch sc(D, st, fixed);
   DD_TRY(sc.open());
   const bool cull = cull_pays(D, mode, m, warm_start_idx_dev != nullptr) &&
-                    (!fixed || sc.room() > prepared_bytes(m) + culled_bytes(D, m));
+                    (!fixed || sc.room() >= culled_call_bytes(D, mode, m));
   Timing timing;
   if (opts && opts->stats) DD_TRY(timing.init(st));
   QueryPrep Q;
@@ -587,10 +610,11 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
     DD_TRY(timing.mark(2, st));
   } else if (cull) {
     int* fb = nullptr;
+    DD_TRY(sc.get(fb, (size_t)m));
     int64_t left = 0;
     const float s = scan16 ? D.sc16.s : 1.0f;
     int* fb_count = counters + (mode == DD_EXACT_FP64 ? 1 : 0);
-    DD_TRY(culled_scan(D, mode, Q, all, m, s, out, sc, counters, fb_count, st, fb, left, &timing));
+    DD_TRY(culled_scan(D, mode, Q, all, m, s, out, sc, counters, fb, fb_count, st, left, &timing));
     n_fallback += left;
     if (scan16) n_items_host = -1;   // read with the statistics
     if (left > 0) {

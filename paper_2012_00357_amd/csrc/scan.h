@@ -53,7 +53,7 @@ struct TileMasks {
   size_t zero_bytes = 0;
   uint32_t* mask = nullptr;      // [tiles][words]
   uint32_t* left = nullptr;      // [tiles][words] groups the scan leaves for its extraction
-  uint2* entry = nullptr;        // [kMaskParts * tiles] (launch_plan)
+  uint2* entry = nullptr;        // [min(words, kMaskParts) * tiles] (launch_plan)
   unsigned* n_entry = nullptr;   // entries under mask, entries under left
   int words = 0, sub = 0;
   // statistics, or nullptr: (query, point) pairs of the scan, (group, tile) items

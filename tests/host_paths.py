@@ -122,3 +122,27 @@ def run_scenario(tmp_path, source):
                        text=True, timeout=110)
     assert r.returncode == 0, r.stdout + r.stderr
     return r.stdout
+
+
+class Arena(ctypes.Structure):     # ScratchArena of csrc/dd_internal.h
+    _fields_ = [("block", vp), ("bytes", ctypes.c_size_t), ("done", vp), ("pinned", vp)]
+
+
+def scratch_need(dd, ds, mode, m_max):
+    f = dd._ZN2dd20project_scratch_needERKNS_7DatasetEil
+    f.argtypes, f.restype = [vp, ctypes.c_int, i64], ctypes.c_size_t
+    return f(ds, MODE[mode], m_max)
+
+
+def project_reserved(hip, dd, ds, mode, m, room, warm=vp(4096)):
+    """A projection in a block of `room` bytes, as a server's batches run it."""
+    block = vp()
+    assert hip.hipMalloc(ctypes.byref(block), ctypes.c_size_t(room)) == 0
+    f = dd._ZN2dd16project_reservedERKNS_7DatasetEPKdblPKlPK15dd_project_optsPlPdPNS_12ScratchArenaEP12ihipStream_t
+    f.argtypes = [vp, vp, ctypes.c_bool, i64, vp, vp, vp, vp, vp, vp]
+    pinned = (ctypes.c_uint32 * 64)()
+    arena = Arena(block, room, None, ctypes.cast(pinned, vp))
+    opts = ProjectOpts(MODE[mode], 0, 0, 0, None, 0.0)
+    rc = f(ds, vp(4096), True, m, warm, ctypes.byref(opts), vp(4096), vp(4096), ctypes.byref(arena), None)
+    hip.hipFree(block)
+    return rc

@@ -153,3 +153,47 @@ def test_kept_blocks_are_counted_as_they_are(tmp_path):
             dd.dd_dataset_destroy(None)
         assert len(set(sizes)) == 1, sizes
         """)
+
+
+@pytest.mark.parametrize("mode,points,tile", [
+    ("bf16", 1 << 24, 0), ("bf16", 1 << 26, 0), ("bf16", 1 << 27, 0), ("fp16", 1 << 24, 512), ("bf16", 1 << 22, 128),
+    ("bf16", 1 << 26, 128), ("fp32", 1 << 24, 0), ("fp64", 1 << 24, 0), ("fp64", 1 << 27, 0), ("bf16", 1_000_000, 0)])
+def test_server_batches_cull(tmp_path, mode, points, tile):
+    """The batches of a server, whole ones too, leave out tiles in the scratch it holds,
+    and that holds the fallback of every query of a batch."""
+    pack = {"bf16": "BF16", "fp16": "FP16", "fp32": "FP32", "fp64": "FP64"}[mode]
+    scenario(tmp_path, f"""
+        rc, ds = create(dd, {points}, FP64 | {pack}, {tile})
+        assert rc == 0, dd.dd_last_error()
+        for top in (65536, 40000, 5000):
+            need = scratch_need(dd, ds, "{mode}", top)
+            for m in (top, top - 1, top // 2 + 1, 4096):
+                for left in (0, 1, 700, m):
+                    hip.fake_watch(b"none", 0, None)
+                    hip.fake_word(b"merge_rerank", min(left, m))
+                    rc = project_reserved(hip, dd, ds, "{mode}", m, need)
+                    assert rc == 0, (top, m, left, dd.dd_last_error())
+                    assert hip.fake_launches(b"cull_kernel") > 0, (top, m, left)
+        """)
+
+
+@pytest.mark.parametrize("mode", ["bf16", "fp32", "fp64", "ann"])
+def test_any_block_holds_a_call_or_is_refused_before(tmp_path, mode):
+    """Whatever the block, a culled batch that begins in it also ends in it, with every
+    query left to the fallback."""
+    scenario(tmp_path, f"""
+        rc, ds = create(dd, 1 << 22, FP64 | FP32 | BF16 | ANN, 128)
+        m = 20000
+        need = scratch_need(dd, ds, "{mode}", m)
+        culled = 0
+        for k in range(400):
+            room = need // 4 + k * (need // 200)
+            for left in (0, 700, m):
+                hip.fake_watch(b"none", 0, None)
+                hip.fake_word(b"merge_rerank" if "{mode}" != "ann" else b"walk", left)
+                rc = project_reserved(hip, dd, ds, "{mode}", m, room)
+                n = hip.fake_launches(b"cull_kernel")
+                culled += n > 0
+                assert rc == 0 or (n == 0 and room < need), (room, need, left, dd.dd_last_error())
+        assert culled > 100, culled
+        """)
