@@ -228,8 +228,8 @@ dd_status dd_dataset_destroy(dd_dataset* ds);
 
 /* Number of points, and bytes of device memory the dataset holds: its packs and
    trees plus the projection scratch it keeps between calls (at most 8 idle
-   blocks of at most 1 GiB, released by dd_dataset_destroy).  The K^-1 cache of
-   dd_solve is not counted. */
+   blocks of at most 1 GiB, released by dd_dataset_destroy).  The operators that
+   dd_solve keeps on it are not counted. */
 dd_status dd_dataset_info(const dd_dataset* ds, int64_t* n_points, int64_t* device_bytes);
 
 /* Shape of a dataset's search trees (zeros for a tree it does not hold). */
@@ -450,7 +450,7 @@ typedef struct dd_server_statistics {
   int64_t active, queued;           /* admitted solves now; submitted, not yet admitted */
   int64_t batches, queries;         /* projection batches run; material points projected */
   int64_t peak_active, peak_bytes;  /* most solves admitted at once; most bytes charged at once
-                                       (reserve, admitted solves, K^-1 inverses) */
+                                       (reserve, admitted solves, kept operators) */
   int64_t budget_bytes;             /* the admission budget */
   double proj_p50_ms, proj_p99_ms;  /* per projection: a solve's state ready -> association back */
   double solve_p50_ms, solve_p99_ms;  /* per solve: submit -> result ready */
@@ -467,10 +467,10 @@ typedef struct dd_server_statistics {
  * batch buffers and the scratch of a projection of max_batch states, which the
  * batch projections carve every temporary buffer from, so they allocate
  * nothing), plus the summed footprint of admitted solves (their P_C buffers and
- * states), plus the K^-1 inverses the server forms (from admission of the solve
- * that needs one, and for as long as the dataset's cache keeps it); an inverse
- * is formed on a builder thread while the other solves go on, and a solve whose
- * inverse cannot fit next to it even on an idle server is run by CG (dd_solve's
+ * states), plus the operators (see DD_SOLVE_CG) the server forms (from admission of
+ * the solve that needs one, and for as long as the dataset's cache keeps it); an operator is formed on a builder thread while
+ * the other solves go on, and a solve whose operator cannot be formed next to it
+ * even on an idle server is run by CG (dd_solve's
  * DD_SOLVE_CG trajectory); 0 = half of the free device memory.  opts NULL =
  * BF16 projections, defaults above.  Errors: DD_ERR_ARG, DD_ERR_UNSUPPORTED
  * (mode without its pack), DD_ERR_TOO_LARGE (the reserve alone exceeds the

@@ -181,18 +181,18 @@ inline bool walk_mode(int mode) { return mode == DD_ANN || mode == DD_KMEANS; }
 constexpr int64_t kTreeScanMin = (int64_t)1 << 13, kTreeScanMax = (int64_t)1 << 24;
 constexpr int kAnnMaxLevels = 6;   // 64^6 leaves exceed any N <= 2^31 - 1
 
-// K^-1 of one mesh and Dirichlet pattern (P_C by a dense product), padded to
-// n_pad rows and columns, row-major.
+// The operator of P_C kept for one mesh and Dirichlet pattern: K^-1, padded to n_pad
+// rows and columns, row-major, or the block elimination of its node planes.
 struct DenseInverse {
   int nx = 0, ny = 0, nz = 0;
   double hx = 0, hy = 0, hz = 0;
   std::vector<uint8_t> mask;
   int64_t n = 0, n_pad = 0;
-  bool planes = false;   // inv holds the block elimination of node planes instead
+  bool planes = false;   // inv holds the elimination (dense.hip)
   DevBuf inv;
 };
-constexpr int64_t kDenseMaxDof = 16384;               // meshes up to here use K^-1
-constexpr int64_t kDenseCacheBytes = (int64_t)4 << 30;  // inverses kept per dataset
+constexpr int64_t kDenseMaxDof = 16384;               // meshes up to here always keep one
+constexpr int64_t kDenseCacheBytes = (int64_t)4 << 30;  // operators kept per dataset
 
 // Device scratch of the projection, reused from call to call.  A call takes an
 // idle arena (or makes one), carves its buffers out of the arena's block and
@@ -306,7 +306,7 @@ struct Dataset {
   DevBuf kmt_pos;    // uint32 [leaves*64]: sorted position of each slot (empty: 0xFFFFFFFF)
   DevBuf kmt_slot;   // uint32 [N]: slot of each sorted position
 
-  // inverses of K for dd_solve, most recently used first (see DenseInverse)
+  // operators of dd_solve, most recently used first (see DenseInverse)
   mutable std::mutex cache_mu;
   mutable std::list<std::shared_ptr<DenseInverse>> pc_cache;
   // idle projection scratch arenas (see ScratchArena); arena_bytes counts the

@@ -18,11 +18,11 @@
 // the batch buffers and the scratch of the largest projection batch (every
 // temporary buffer of the batch's projection is carved from it, so the
 // projection allocates nothing and never exceeds it).  A solve is charged its
-// solver buffers while it is admitted.  A mesh that dd_solve would solve through a cached K^-1
-// and whose inverse the dataset does not hold yet is charged that inverse too:
-// the inverse is formed on a builder thread (the solve waits, the others go
-// on) and stays charged to the server while the dataset's cache keeps it.  A
-// solve whose inverse could not fit next to it even on an idle server is run
+// solver buffers while it is admitted.  A mesh that dd_solve would solve through
+// an operator kept on the dataset (K^-1 or the elimination of its node planes) that
+// the dataset does not hold yet is charged that operator too: it is formed on a
+// builder thread (the solve waits, the others go on) and stays charged to the server while the dataset's cache keeps it.  A
+// solve whose operator could not be formed next to it even on an idle server is run
 // by CG instead (the trajectory of dd_solve with DD_SOLVE_CG).
 #include <algorithm>
 #include <atomic>
@@ -65,9 +65,9 @@ struct Job {
   int max_iter = 500;
   double deadline_s = 0.0;
   int64_t footprint = 0;
-  int64_t inv_bytes = 0;       // K^-1 the solve would use (0: solved by CG)
-  bool use_cg = false;         // run by CG: its K^-1 does not fit the budget
-  std::string inv_key;         // mesh and Dirichlet pattern of its K^-1
+  int64_t inv_bytes = 0;       // operator the solve would keep on the dataset (0: solved by CG)
+  bool use_cg = false;         // run by CG: its operator does not fit the budget
+  std::string inv_key;         // mesh and Dirichlet pattern of its operator
   int64_t n_mp = 0, n_dof = 0;
 
   enum Phase { kQueued, kInverse, kCg, kReady, kInBatch, kScalars, kDone };
@@ -121,8 +121,8 @@ struct Server {
   // scheduler-thread state
   std::vector<Job*> active;
   int64_t used = 0;
-  // K^-1 formed ahead of setup: builds in flight (key -> result, bytes) and the
-  // inverses this server formed that the dataset still caches (key -> bytes)
+  // operators formed ahead of setup: builds in flight (key -> result, bytes) and
+  // those this server formed that the dataset still caches (key -> bytes)
   struct Build {
     std::shared_future<std::pair<dd_status, std::string>> done;
     int64_t bytes;
@@ -167,8 +167,9 @@ struct Server {
 // ---------------------------------------------------------------------------
 // scheduler thread
 // ---------------------------------------------------------------------------
-// Bytes of the inverses in flight and of those this server formed that the
-// dataset still caches (dropped from the charge once the cache lets them go).
+// Bytes of the operators in flight and of those this server
+// formed that the dataset still caches (dropped from the charge once the cache lets
+// them go).
 int64_t Server::held_bytes() {
   int64_t b = 0;
   for (const auto& kv : building) b += kv.second.bytes;
@@ -189,8 +190,8 @@ int64_t Server::held_bytes() {
 dd_status Server::admit(Job* j) {
   DD_HIP(hipStreamCreateWithFlags(&j->stream, hipStreamNonBlocking));
   if (j->inv_bytes > 0 && !j->use_cg && !DDSolver::inverse_cached(*D, j->mesh, j->mask.data())) {
-    // form K^-1 on a builder thread (or wait for the build of the same
-    // inverse already in flight); the solve waits in kInverse
+    // form the operator on a builder thread (or wait for the build of the same
+    // one already in flight); the solve waits in kInverse
     if (!building.count(j->inv_key)) {
       const Dataset* ds = D;
       const int dev = device;
@@ -201,7 +202,7 @@ dd_status Server::admit(Job* j) {
         hipStream_t s = nullptr;
         if (hipSetDevice(dev) != hipSuccess ||
             hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
-          r.first = set_error(DD_ERR_DEVICE, "K^-1 builder: no stream");
+          r.first = set_error(DD_ERR_DEVICE, "operator builder: no stream");
         } else {
           r.first = DDSolver::prepare_inverse(*ds, mesh, mask.data(), s);
           (void)hipStreamDestroy(s);
@@ -279,7 +280,7 @@ bool Server::step(Job* j) {
     return true;
   }
   if (j->phase == Job::kInverse) {
-    // the build was swept when it ended; setup() then finds the inverse cached
+    // the build was swept when it ended; setup() then finds the operator cached
     // (or, after a failed build, forms it itself and reports its error)
     if (building.count(j->inv_key)) return false;
     const dd_status st = admit_setup(j);
@@ -424,7 +425,7 @@ void Server::scheduler() {
   (void)hipSetDevice(device);
   for (;;) {
     bool progress = false;
-    // finished K^-1 builds: charged while the dataset caches the inverse
+    // finished builds: charged while the dataset caches the operator
     for (auto it = building.begin(); it != building.end();) {
       if (it->second.done.wait_for(std::chrono::seconds(0)) == std::future_status::ready) {
         if (it->second.done.get().first == DD_OK) formed[it->first] = it->second.bytes;
@@ -457,8 +458,8 @@ void Server::scheduler() {
       }
       while (!queue.empty() && (int)active.size() < max_active) {
         Job* j = queue.front();
-        // the K^-1 this solve would form: charged from admission on; one that
-        // cannot fit next to the solve even on an idle server means CG
+        // the operator this solve would form: charged from admission on; one that
+        // cannot be formed next to the solve even on an idle server means CG
         int64_t extra = 0;
         if (j->inv_bytes > 0 && !j->use_cg && !building.count(j->inv_key) &&
             !DDSolver::inverse_cached(*D, j->mesh, j->mask.data())) {
@@ -737,7 +738,7 @@ extern "C" dd_status dd_server_submit(dd_server* h, const dd_solve_request* r, u
   j->max_iter = r->max_iter > 0 ? r->max_iter : 500;
   j->deadline_s = r->deadline_s;
   j->footprint = DDSolver::footprint_bytes(r->mesh);
-  j->inv_bytes = DDSolver::inverse_bytes(r->mesh);
+  j->inv_bytes = DDSolver::inverse_bytes(r->mesh, r->dirichlet_mask);
   {
     dd_mesh key_mesh;
     std::memset(&key_mesh, 0, sizeof(key_mesh));   // no padding bytes of the caller's struct

@@ -32,11 +32,11 @@ dd_status project_whitened(const Dataset& D, const double* qw_dev, int64_t m,
 
 // Element stiffness Ke = w sum_g B_g^T C B_g (24 x 24).
 void element_stiffness(const FEMesh& M, const double* C, double* Ke);
-// K^-1 for the mesh and Dirichlet pattern, formed on st on first use and cached
-// on the dataset.
+// The operator of P_C for the mesh and Dirichlet pattern (K^-1 or the elimination of
+// the node planes), formed on st on first use and cached on the dataset.
 dd_status dense_inverse_for(const Dataset& ds, const FEMesh& M, const uint8_t* mask,
                             std::shared_ptr<DenseInverse>& out, hipStream_t st);
-// The cached K^-1 for the mesh and Dirichlet pattern, or null.
+// The cached operator for the mesh and Dirichlet pattern, or null.
 std::shared_ptr<DenseInverse> dense_inverse_cached(const Dataset& ds, const FEMesh& M,
                                                    const uint8_t* mask);
 // How P_C is solved for a mesh unless the caller asks for CG, and the device
@@ -75,11 +75,11 @@ class DDSolver {
   // after ev_scal: (d_half, d_full, changed, bad flag); swaps in the new association
   void scalars_end(double sc[3], int* bad);
   static int64_t footprint_bytes(const dd_mesh& mesh);
-  // Device bytes of the K^-1 that setup() uses for the mesh (0: the mesh is
-  // solved by CG), whether the dataset already caches it for the Dirichlet
-  // pattern, and its formation ahead of setup() (a no-op when cached or when
-  // the mesh is solved by CG; synchronises st).
-  static int64_t inverse_bytes(const dd_mesh& mesh);
+  // Device bytes of the operator that setup() keeps on the dataset for the mesh and
+  // Dirichlet pattern (0: solved by CG), whether the dataset already caches it, and
+  // its formation ahead of setup() (a no-op when cached or when the mesh is solved by
+  // CG; synchronises st).
+  static int64_t inverse_bytes(const dd_mesh& mesh, const uint8_t* mask);
   static bool inverse_cached(const Dataset& D, const dd_mesh& mesh, const uint8_t* mask);
   static dd_status prepare_inverse(const Dataset& D, const dd_mesh& mesh, const uint8_t* mask,
                                    hipStream_t st);
@@ -141,7 +141,7 @@ class DDSolver {
   int64_t skipped_total = 0;
   dd_status project_step(int it);   // P_D of the current states into d_idx_new / d_dist
   bool use_graph = true;
-  std::shared_ptr<DenseInverse> dense;   // set: P_C is a product with K^-1
+  std::shared_ptr<DenseInverse> dense;   // set: P_C by an operator kept on the dataset
   hipGraphExec_t cg_graph = nullptr;
   int cg_last_iters[2] = {0, 0};
   double cg_last_res[2] = {0.0, 0.0};

@@ -960,8 +960,10 @@ int64_t DDSolver::footprint_bytes(const dd_mesh& m) {
          8 * (4 + 3 * kScalBlocks) + 64 + 64 * (nb + nbs) + (int64_t)sizeof(CGState);
 }
 
-int64_t DDSolver::inverse_bytes(const dd_mesh& m) {
-  return pc_bytes(m.nx, m.ny, m.nz);
+int64_t DDSolver::inverse_bytes(const dd_mesh& m, const uint8_t* mask) {
+  std::unique_ptr<FEMesh> M(new FEMesh());
+  M->init(m);
+  return use_kept_operator(*M, mask) ? pc_bytes(m.nx, m.ny, m.nz) : 0;
 }
 
 bool DDSolver::inverse_cached(const Dataset& D, const dd_mesh& m, const uint8_t* mask) {

@@ -197,3 +197,26 @@ def test_any_block_holds_a_call_or_is_refused_before(tmp_path, mode):
                 assert rc == 0 or (n == 0 and room < need), (room, need, left, dd.dd_last_error())
         assert culled > 100, culled
         """)
+
+
+@pytest.mark.parametrize("box", [(30, 30, 5), (9, 9, 9), (24, 24, 24)])
+def test_server_charges_what_it_holds(tmp_path, box):
+    """A body free to move beyond the inverse's sizes (16384 unknowns) is solved by CG and
+    charged no operator."""
+    large = 3 * (box[0] + 1) * (box[1] + 1) * (box[2] + 1) > 16384
+    scenario(tmp_path, f"""
+        for clamp in (True, False):
+            rc, ds = create(dd, 1 << 14, FP64 | BF16)
+            dd.dd_dataset_destroy(None)
+            hip.fake_watch(b"none", 0, None)
+            base = hip.fake_live()
+            hip.fake_peak()
+            rc, srv = server(dd, ds, 8 << 30, "bf16", 1024)
+            assert dd.dd_server_wait(srv, submit(dd, srv, *{box}, clamp=clamp), None, 60.0) in (0, 5)
+            s, peak, formed = stats(dd, srv), hip.fake_peak() - base, hip.fake_launches(b"gj_first_kernel")
+            print(clamp, s.reserve_bytes, s.peak_bytes, peak, formed)
+            assert (formed > 0) == (clamp or not {large})
+            assert formed or s.peak_bytes - s.reserve_bytes < 100 << 20     # solver buffers alone
+            dd.dd_server_destroy(srv)
+            dd.dd_dataset_destroy(ds)
+        """)
