@@ -468,7 +468,8 @@ typedef struct dd_server_statistics {
  * batch projections carve every temporary buffer from, so they allocate
  * nothing), plus the summed footprint of admitted solves (their P_C buffers and
  * states), plus the operators (see DD_SOLVE_CG) the server forms (from admission of
- * the solve that needs one, and for as long as the dataset's cache keeps it); an operator is formed on a builder thread while
+ * the solve that needs one, with the workspace while it is formed, and for as long
+ * as the dataset's cache keeps it); an operator is formed on a builder thread while
  * the other solves go on, and a solve whose operator cannot be formed next to it
  * even on an idle server is run by CG (dd_solve's
  * DD_SOLVE_CG trajectory); 0 = half of the free device memory.  opts NULL =

@@ -458,6 +458,22 @@ int64_t pc_bytes(int64_t nx, int64_t ny, int64_t nz) {
   }
 }
 
+// Padded size of the blocks that form_planes inverts.
+static int64_t plane_pad(const PlaneBlocks& B) {
+  return (std::max(B.b, B.bl) + kB - 1) / kB * kB;
+}
+
+int64_t pc_work_bytes(int64_t nx, int64_t ny, int64_t nz) {
+  const PlaneBlocks B = plane_blocks(nx, ny, nz);
+  const int64_t n = (nz + 1) * B.face, w = plane_pad(B);
+  const int64_t in = 8 * 24 * 24 + n;   // element stiffness and mask
+  switch (pc_kind(nx, ny, nz)) {
+    case PCKind::kPlanes: return in + 8 * (2 * w * w + 2 * 27 * B.face + 2 * sweep_len(w));
+    case PCKind::kInverse: return in + 8 * sweep_len((n + kB - 1) / kB * kB);
+    default: return 0;
+  }
+}
+
 namespace {
 
 struct PlaneArgs {
@@ -632,7 +648,7 @@ static dd_status form_planes(const FEMesh& M, const double* Ke, const uint8_t* m
   D.n = n;
   D.planes = true;
   DD_TRY(D.inv.alloc(sizeof(double) * (size_t)(inv_len + plane_h_len(B))));
-  const int64_t bmax = std::max(B.b, B.bl), wmax = (bmax + kB - 1) / kB * kB;
+  const int64_t wmax = plane_pad(B);
   DevBuf work, val, akk, dke, dmask;
   DD_TRY(work.alloc(sizeof(double) * (size_t)(2 * wmax * wmax)));
   DD_TRY(val.alloc(sizeof(double) * (size_t)(2 * 27 * B.face)));

@@ -21,7 +21,8 @@
 // solver buffers while it is admitted.  A mesh that dd_solve would solve through
 // an operator kept on the dataset (K^-1 or the elimination of its node planes) that
 // the dataset does not hold yet is charged that operator too: it is formed on a
-// builder thread (the solve waits, the others go on) and stays charged to the server while the dataset's cache keeps it.  A
+// builder thread (the solve waits, the others go on; its workspace is charged
+// meanwhile) and stays charged to the server while the dataset's cache keeps it.  A
 // solve whose operator could not be formed next to it even on an idle server is run
 // by CG instead (the trajectory of dd_solve with DD_SOLVE_CG).
 #include <algorithm>
@@ -66,6 +67,7 @@ struct Job {
   double deadline_s = 0.0;
   int64_t footprint = 0;
   int64_t inv_bytes = 0;       // operator the solve would keep on the dataset (0: solved by CG)
+  int64_t inv_work = 0;        // workspace of its formation
   bool use_cg = false;         // run by CG: its operator does not fit the budget
   std::string inv_key;         // mesh and Dirichlet pattern of its operator
   int64_t n_mp = 0, n_dof = 0;
@@ -121,11 +123,11 @@ struct Server {
   // scheduler-thread state
   std::vector<Job*> active;
   int64_t used = 0;
-  // operators formed ahead of setup: builds in flight (key -> result, bytes) and
-  // those this server formed that the dataset still caches (key -> bytes)
+  // operators formed ahead of setup: builds in flight (key -> result, bytes kept,
+  // workspace) and those this server formed that the dataset still caches (key -> bytes)
   struct Build {
     std::shared_future<std::pair<dd_status, std::string>> done;
-    int64_t bytes;
+    int64_t bytes, work;
   };
   std::map<std::string, Build> building;
   std::map<std::string, int64_t> formed;
@@ -167,12 +169,12 @@ struct Server {
 // ---------------------------------------------------------------------------
 // scheduler thread
 // ---------------------------------------------------------------------------
-// Bytes of the operators in flight and of those this server
+// Bytes of the operators in flight, with their workspaces, and of those this server
 // formed that the dataset still caches (dropped from the charge once the cache lets
 // them go).
 int64_t Server::held_bytes() {
   int64_t b = 0;
-  for (const auto& kv : building) b += kv.second.bytes;
+  for (const auto& kv : building) b += kv.second.bytes + kv.second.work;
   for (auto it = formed.begin(); it != formed.end();) {
     dd_mesh m;
     std::memcpy(&m, it->first.data(), sizeof(m));
@@ -210,7 +212,7 @@ dd_status Server::admit(Job* j) {
         if (r.first != DD_OK) r.second = dd_last_error();
         return r;
       });
-      building[j->inv_key] = Build{fut.share(), j->inv_bytes};
+      building[j->inv_key] = Build{fut.share(), j->inv_bytes, j->inv_work};
     }
     j->phase = Job::kInverse;
     return DD_OK;
@@ -463,10 +465,10 @@ void Server::scheduler() {
         int64_t extra = 0;
         if (j->inv_bytes > 0 && !j->use_cg && !building.count(j->inv_key) &&
             !DDSolver::inverse_cached(*D, j->mesh, j->mask.data())) {
-          if (reserve + j->footprint + j->inv_bytes > budget)
+          if (reserve + j->footprint + j->inv_bytes + j->inv_work > budget)
             j->use_cg = true;
           else
-            extra = j->inv_bytes;
+            extra = j->inv_bytes + j->inv_work;
         }
         const int64_t held = held_bytes();
         if (reserve + used + held + j->footprint + extra > budget) break;
@@ -738,7 +740,7 @@ extern "C" dd_status dd_server_submit(dd_server* h, const dd_solve_request* r, u
   j->max_iter = r->max_iter > 0 ? r->max_iter : 500;
   j->deadline_s = r->deadline_s;
   j->footprint = DDSolver::footprint_bytes(r->mesh);
-  j->inv_bytes = DDSolver::inverse_bytes(r->mesh, r->dirichlet_mask);
+  j->inv_bytes = DDSolver::inverse_bytes(r->mesh, r->dirichlet_mask, &j->inv_work);
   {
     dd_mesh key_mesh;
     std::memset(&key_mesh, 0, sizeof(key_mesh));   // no padding bytes of the caller's struct

@@ -39,11 +39,12 @@ dd_status dense_inverse_for(const Dataset& ds, const FEMesh& M, const uint8_t* m
 // The cached operator for the mesh and Dirichlet pattern, or null.
 std::shared_ptr<DenseInverse> dense_inverse_cached(const Dataset& ds, const FEMesh& M,
                                                    const uint8_t* mask);
-// How P_C is solved for a mesh unless the caller asks for CG, and the device
-// bytes kept on the dataset for it.
+// How P_C is solved for a mesh unless the caller asks for CG, the device bytes
+// kept on the dataset for it, and those its formation takes beside them.
 enum class PCKind { kInverse, kPlanes, kCG };
 PCKind pc_kind(int64_t nx, int64_t ny, int64_t nz);
 int64_t pc_bytes(int64_t nx, int64_t ny, int64_t nz);
+int64_t pc_work_bytes(int64_t nx, int64_t ny, int64_t nz);
 // x[0..n) = K^-1 b[0..n), x[n..2n) = K^-1 b[n..2n); b is overwritten.
 dd_status dense_apply(const DenseInverse& D, double* b, double* x, hipStream_t st);
 
@@ -76,10 +77,10 @@ class DDSolver {
   void scalars_end(double sc[3], int* bad);
   static int64_t footprint_bytes(const dd_mesh& mesh);
   // Device bytes of the operator that setup() keeps on the dataset for the mesh and
-  // Dirichlet pattern (0: solved by CG), whether the dataset already caches it, and
-  // its formation ahead of setup() (a no-op when cached or when the mesh is solved by
-  // CG; synchronises st).
-  static int64_t inverse_bytes(const dd_mesh& mesh, const uint8_t* mask);
+  // Dirichlet pattern (0: solved by CG) and, in *work, of its formation beside it;
+  // whether the dataset already caches it, and its formation ahead of setup() (a
+  // no-op when cached or when the mesh is solved by CG; synchronises st).
+  static int64_t inverse_bytes(const dd_mesh& mesh, const uint8_t* mask, int64_t* work);
   static bool inverse_cached(const Dataset& D, const dd_mesh& mesh, const uint8_t* mask);
   static dd_status prepare_inverse(const Dataset& D, const dd_mesh& mesh, const uint8_t* mask,
                                    hipStream_t st);

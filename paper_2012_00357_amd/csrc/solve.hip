@@ -960,10 +960,12 @@ int64_t DDSolver::footprint_bytes(const dd_mesh& m) {
          8 * (4 + 3 * kScalBlocks) + 64 + 64 * (nb + nbs) + (int64_t)sizeof(CGState);
 }
 
-int64_t DDSolver::inverse_bytes(const dd_mesh& m, const uint8_t* mask) {
+int64_t DDSolver::inverse_bytes(const dd_mesh& m, const uint8_t* mask, int64_t* work) {
   std::unique_ptr<FEMesh> M(new FEMesh());
   M->init(m);
-  return use_kept_operator(*M, mask) ? pc_bytes(m.nx, m.ny, m.nz) : 0;
+  const bool kept = use_kept_operator(*M, mask);
+  *work = kept ? pc_work_bytes(m.nx, m.ny, m.nz) : 0;
+  return kept ? pc_bytes(m.nx, m.ny, m.nz) : 0;
 }
 
 bool DDSolver::inverse_cached(const Dataset& D, const dd_mesh& m, const uint8_t* mask) {

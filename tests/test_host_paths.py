@@ -201,8 +201,8 @@ def test_any_block_holds_a_call_or_is_refused_before(tmp_path, mode):
 
 @pytest.mark.parametrize("box", [(30, 30, 5), (9, 9, 9), (24, 24, 24)])
 def test_server_charges_what_it_holds(tmp_path, box):
-    """A body free to move beyond the inverse's sizes (16384 unknowns) is solved by CG and
-    charged no operator."""
+    """The charged peak covers what forming an operator takes; a body free to move beyond
+    the inverse's sizes (16384 unknowns) is solved by CG and charged no operator."""
     large = 3 * (box[0] + 1) * (box[1] + 1) * (box[2] + 1) > 16384
     scenario(tmp_path, f"""
         for clamp in (True, False):
@@ -216,6 +216,8 @@ def test_server_charges_what_it_holds(tmp_path, box):
             s, peak, formed = stats(dd, srv), hip.fake_peak() - base, hip.fake_launches(b"gj_first_kernel")
             print(clamp, s.reserve_bytes, s.peak_bytes, peak, formed)
             assert (formed > 0) == (clamp or not {large})
+            fetch = 96 * 8 * {box[0] * box[1] * box[2]}       # strains and stresses on their way to the host
+            assert peak <= s.peak_bytes + fetch + 4096
             assert formed or s.peak_bytes - s.reserve_bytes < 100 << 20     # solver buffers alone
             dd.dd_server_destroy(srv)
             dd.dd_dataset_destroy(ds)
