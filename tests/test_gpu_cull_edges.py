@@ -42,3 +42,34 @@ def test_states_beyond_single_precision(L, mode, flip, far):
         assert torch.equal(idx, ref)
         np.testing.assert_allclose(dist.cpu().numpy(), dref.cpu().numpy(), rtol=1e-14, atol=0)
     ds.close()
+
+
+@pytest.mark.parametrize("mode", ["fp64", "fp32", "bf16", "fp16"])
+def test_overflowing_lists_end_early(L, mode):
+    """States far to one side of the data, whose distances the 16-bit formats cannot tell
+    apart, overflow every list: the direct scan's answers, and the scan takes no longer
+    than a few of ordinary states (a hundred and more where every point is appended)."""
+    import torch
+    n, m = 1 << 19, 2048
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn(n, 12, dtype=torch.float64, device="cuda", generator=g)
+    X[:, 6:] = X[:, :6] + 0.01 * X[:, 6:]
+    X[17], X[n - 5] = X[123], X[123]
+    ds = L.dd_dataset_create(X[:, :6].contiguous(), X[:, 6:].contiguous(), np.eye(6), packs=FP64 | FP32 | BF16 | FP16)
+    pick = torch.randint(0, n, (m,), device="cuda", generator=g)
+    near = (X[pick] + 0.05 * torch.randn(m, 12, dtype=torch.float64, device="cuda", generator=g)).contiguous()
+    side = 0.3 * torch.randn(m, 12, dtype=torch.float64, device="cuda", generator=g)
+    side[:, :6] += 10.0
+    side[:, 6:] -= 10.0
+    ms = {}
+    for name, y in (("near", near), ("side", side)):
+        for _ in range(2):
+            idx, dist, st = L.dd_project(ds, y, mode=mode, stats=True)
+        ms[name] = st["scan_ms"]
+        ref, dref = L.dd_project(ds, y, mode="direct")
+        assert torch.equal(idx, ref) and torch.equal(dist, dref)
+        if mode == "bf16" and name == "side":
+            assert st["overflowed"] == m
+    print(mode, ms)
+    assert ms["side"] < 40 * ms["near"]
+    ds.close()
