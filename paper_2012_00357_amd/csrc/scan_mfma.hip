@@ -268,14 +268,10 @@ __device__ inline void mask_items(const uint32_t* row, int words, uint32_t part,
   end = total * (k + 1) / parts;
 }
 
-// A query whose list has overflowed goes to the fallback whatever else is found, so
-// it takes no more candidates.  (States that the scan's numbers cannot tell the points
+// A query whose list is found full goes to the fallback whatever else is near, so its
+// lane takes no more candidates.  (States that the scan's numbers cannot tell the points
 // apart for, 4096 of them to one side of 2^20 points in BF16: 40 ms of scan with every
-// append queued on its query's count, 0.58 now.)
-__device__ inline bool list_full(const CandBuf& cb, int64_t p) {
-  return __hip_atomic_load(&cb.count[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > cb.K;
-}
-
+// append queued on its query's count, 0.54 now.)
 constexpr int kMaskGroups64 = (int)(kMaskQueries / 16);
 
 // FP64, groups of 16 queries.  !EXTRACT: the tile's minimum lowers the queries'
@@ -343,7 +339,6 @@ __global__ __launch_bounds__(256, 4) void scan64_culled_kernel(
         if (!EXTRACT) {
           tm = fmin(tm, mn);
         } else if (__any((mn + qq) - alpha <= Uq)) {
-          if (v && list_full(cb, p)) Uq = -INFINITY;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int64_t x = t * kTile64 + rb * 16 + kq + 4 * j;
@@ -353,6 +348,8 @@ __global__ __launch_bounds__(256, 4) void scan64_culled_kernel(
               if (at < cb.K) {
                 cb.lb[p * cb.K + at] = f32_down(lb);
                 cb.j[p * cb.K + at] = (uint32_t)x;
+              } else {
+                Uq = -INFINITY;
               }
             }
           }
@@ -660,7 +657,6 @@ __global__ __launch_bounds__(256, 4) void scan32_culled_kernel(
         if (!EXTRACT) {
           tm = mn;
         } else if (__any((mn + o) - a <= Uq)) {
-          if (v && list_full(cb, p)) Uq = -INFINITY;
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int64_t x = t * kTile32 + rb * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
@@ -670,6 +666,8 @@ __global__ __launch_bounds__(256, 4) void scan32_culled_kernel(
               if (at < cb.K) {
                 cb.lb[p * cb.K + at] = lb;
                 cb.j[p * cb.K + at] = (uint32_t)x;
+              } else {
+                Uq = -INFINITY;
               }
             }
           }
@@ -1132,7 +1130,6 @@ __global__ __launch_bounds__(64 * kW16c, 4) void scan16_culled_kernel(
       float tm[2] = {INFINITY, INFINITY};
       auto extract = [&](int g, int rb, const f32x16_t& acc) __attribute__((always_inline)) {
         if (min16(INFINITY, acc) <= T[g]) {
-          if (list_full(cb, p[g])) T[g] = -INFINITY;
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             if (acc[j] <= T[g]) {
@@ -1143,6 +1140,8 @@ __global__ __launch_bounds__(64 * kW16c, 4) void scan16_culled_kernel(
                 if (at < cb.K) {
                   cb.lb[(int64_t)p[g] * cb.K + at] = lb;
                   cb.j[(int64_t)p[g] * cb.K + at] = (uint32_t)x;
+                } else {
+                  T[g] = -INFINITY;
                 }
               }
             }
