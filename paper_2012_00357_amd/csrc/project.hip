@@ -335,18 +335,31 @@ size_t culled_call_bytes(const Dataset& D, int mode, int64_t m) {
 // (50 us) and leaves few of the pairs of a large data set: at 2^23 points it
 // takes 0.11 to 0.83 ms for 8 to 4096 queries in FP64 against 1.2 to 24 ms for
 // the scan of every tile, and 0.11 to 0.43 against 0.32 to 1.5 ms in BF16.  The
-// line lies where both take the same time: at 2^18 points without a warm start
-// (BF16, 8 to 4096 queries: 101 to 166 against 110 to 205 us) and 2^19 with one,
-// which makes the full scan faster (10^6 points: 101 to 187 against 108 to 211
-// us; 2^18: 103 to 165 against 87 to 136 us).  Below that it is a large batch's
-// work that pays: FP64 from 2^27 pairs (2^16 points, 4096 queries: 178 against
-// 426 us; 512 queries: 112 against 111 us), 16 bits from 2^32.
+// line lies where both take the same time on data near a law: at 2^18 points
+// without a warm start (BF16, 8 to 4096 queries: 101 to 166 against 110 to 205 us)
+// and with one, which makes the full scan faster, at 2^19 in FP64 and FP32 (1024
+// queries there: 152 against 318 and 143 against 203 us) and 5 2^17 in 16 bits (2^19
+// points, 8 to 4096 queries: 99 to 167 against 93 to 153 us; 655360: 100 to 167
+// against 104 to 167).  There the full scan's blocks of 1024 queries are cheapest
+// when full: one of them (1024 queries) 130 against 131 us at 655360 points, 160
+// against 148 at 3 2^19, 167 against 162 at 2^21; two (2048) 144 against 136 at
+// 655360, 159 against 153 at 2^20, 177 against 183 at 3 2^19; three (3072) 153
+// against 191 at 655360.  Below the line it is a large batch's work that pays: FP64
+// from 2^27 pairs (2^16 points, 4096 queries: 178 against 426 us; 512 queries: 112
+// against 111 us), 16 bits from 2^32 (2^19 points, 8192 queries: 202 against 219).
+// Where nothing can be left out (states far from the data in all twelve dimensions,
+// data that fill them) the culled scan still takes 0.4 to 1.0 times as long without
+// a warm start; with one up to 1.3 times in 16 bits (2^19 to 2^23 points) and 1.25
+// in FP64 and FP32 (2^17 to 2^19), less than the full scan beyond.
 bool cull_pays(const Dataset& D, int mode, int64_t m, bool warm) {
   if (D.boxes.n_tiles < 1 || mode == DD_DIRECT_FP64 || walk_mode(mode)) return false;
-  if (D.N >= (1 << 19) || (!warm && D.N >= (1 << 18))) return true;
-  const bool scan16 = mode == DD_MIXED_BF16 || mode == DD_MIXED_FP16;
-  return scan16 ? D.N >= (1 << 18) && m * D.N >= ((int64_t)1 << 32)
-                : D.N >= (1 << 16) && m * D.N > ((int64_t)1 << 27);
+  if (!warm && D.N >= (1 << 18)) return true;
+  if (mode != DD_MIXED_BF16 && mode != DD_MIXED_FP16)
+    return D.N >= (1 << 19) || (D.N >= (1 << 16) && m * D.N > ((int64_t)1 << 27));
+  if (D.N < (1 << 18)) return false;
+  if (D.N >= (1 << 21) || m * D.N >= ((int64_t)1 << 32)) return true;
+  if (D.N < 5 * (1 << 17)) return false;
+  return m <= kScan16Queries * 3 / 4 || (m > kScan16Queries && D.N > (1 << 20)) || m > 2 * kScan16Queries;
 }
 
 // The 16-bit scan that finds an exact walk's answers sooner, or 0.  Its tiles are
@@ -564,7 +577,8 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
   const bool scan = !walk_mode(mode) && mode != DD_DIRECT_FP64;
   Scratch sc(D, st, fixed);
   DD_TRY(sc.open());
-  const bool cull = cull_pays(D, mode, m, warm_start_idx_dev != nullptr) &&
+  // (a warm start that is scanned with a bound-seeding pass is as slow as none)
+  const bool cull = cull_pays(D, mode, m, warm_start_idx_dev && !(opts && opts->passes == 2)) &&
                     (!fixed || sc.room() >= culled_call_bytes(D, mode, m));
   Timing timing;
   if (opts && opts->stats) DD_TRY(timing.init(st));

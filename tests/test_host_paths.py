@@ -222,3 +222,30 @@ def test_server_charges_what_it_holds(tmp_path, box):
             dd.dd_server_destroy(srv)
             dd.dd_dataset_destroy(ds)
         """)
+
+
+def test_which_scans_are_culled(tmp_path):
+    """Both sides of the lines that the rule draws, warm and cold, per format."""
+    scenario(tmp_path, """
+        def culled(ds, m, mode, warm, **kw):
+            hip.fake_watch(b"none", 0, None)
+            assert project(dd, ds, m, mode, vp(4096) if warm else None, **kw) == 0, dd.dd_last_error()
+            return hip.fake_launches(b"cull_kernel") > 0
+        want = {            # points: (queries, 16 bits warm, 16 bits cold, FP64 warm, FP64 cold)
+            1 << 16: [(2048, 0, 0, 0, 0), (2049, 0, 0, 1, 1), (65536, 0, 0, 1, 1)],
+            (1 << 18) - 1: [(8, 0, 0, 0, 0), (20000, 0, 0, 1, 1)],
+            1 << 18: [(8, 0, 1, 0, 1), (16383, 0, 1, 1, 1), (16384, 1, 1, 1, 1)],
+            1 << 19: [(8, 0, 1, 1, 1), (8191, 0, 1, 1, 1), (8192, 1, 1, 1, 1)],
+            5 * (1 << 17): [(768, 1, 1, 1, 1), (769, 0, 1, 1, 1), (2048, 0, 1, 1, 1), (2049, 1, 1, 1, 1)],
+            (1 << 20) + 1: [(768, 1, 1, 1, 1), (1024, 0, 1, 1, 1), (1025, 1, 1, 1, 1), (2048, 1, 1, 1, 1)],
+            1 << 21: [(1, 1, 1, 1, 1), (1024, 1, 1, 1, 1)]}
+        for n, rows in want.items():
+            rc, ds = create(dd, n, FP64 | FP32 | BF16 | FP16)
+            assert rc == 0
+            for m, w16, c16, w64, c64 in rows:
+                for mode, w, c in (("bf16", w16, c16), ("fp16", w16, c16), ("fp32", w64, c64), ("fp64", w64, c64)):
+                    assert culled(ds, m, mode, True) == w, (n, m, mode, "warm")
+                    assert culled(ds, m, mode, False) == c, (n, m, mode, "cold")
+                    assert culled(ds, m, mode, True, passes=2) == c, (n, m, mode, "stale warm start")
+            dd.dd_dataset_destroy(ds)
+        """)
