@@ -161,8 +161,8 @@ typedef struct dd_project_stats {
 
 typedef struct dd_project_opts {
   int32_t mode;             /* dd_mode; default DD_EXACT_FP64 */
-  int32_t splits;           /* data splits per query block; 0 = automatic (no effect on a scan
-                               that leaves out tiles) */
+  int32_t splits;           /* > 0: the scan of every tile, its data cut into so many splits per
+                               query block; 0 = automatic (tiles left out where that is sooner) */
   int32_t ann_budget;       /* DD_ANN, DD_KMEANS: max leaves visited per query;
                                0 = unlimited (exact) */
   int32_t passes;           /* 16-bit modes: 1 = marking pass only, 2 = a bound-seeding pass over

@@ -577,8 +577,10 @@ static dd_status project_run(const Dataset& D, int mode, const double* states_de
   const bool scan = !walk_mode(mode) && mode != DD_DIRECT_FP64;
   Scratch sc(D, st, fixed);
   DD_TRY(sc.open());
-  // (a warm start that is scanned with a bound-seeding pass is as slow as none)
-  const bool cull = cull_pays(D, mode, m, warm_start_idx_dev && !(opts && opts->passes == 2)) &&
+  // (a caller who gives the splits asks for the scan of every tile, cut so; a warm
+  // start that is scanned with a bound-seeding pass is as slow as none)
+  const bool cull = splits == 0 &&
+                    cull_pays(D, mode, m, warm_start_idx_dev && !(opts && opts->passes == 2)) &&
                     (!fixed || sc.room() >= culled_call_bytes(D, mode, m));
   Timing timing;
   if (opts && opts->stats) DD_TRY(timing.init(st));

@@ -73,3 +73,20 @@ def test_overflowing_lists_end_early(L, mode):
     print(mode, ms)
     assert ms["side"] < 40 * ms["near"]
     ds.close()
+
+
+@pytest.mark.parametrize("mode", ["fp64", "fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("splits", [1, 7, 64])
+def test_splits_ask_for_every_tile(L, C0, mode, splits):
+    """A caller who gives the splits gets the scan of every tile, with the same answers."""
+    import torch
+    n, m = N0 + 513, 700
+    e, s = ddsynth.data_points(n, 7600)
+    qe, qs, _ = ddsynth.queries(e, s, m, 7601)
+    ds = L.dd_dataset_create(to_dev(e), to_dev(s), C0, packs=FP64 | FP32 | BF16 | FP16)
+    y = to_dev(ddsynth.states(qe, qs))
+    idx, dist, st = L.dd_project(ds, y, mode=mode, splits=splits, stats=True)
+    ref, dref, sr = L.dd_project(ds, y, mode=mode, stats=True)
+    assert torch.equal(idx, ref) and torch.equal(dist, dref)
+    assert st["visited"] == n * m and sr["visited"] < 0.7 * n * 32 * ((m + 31) // 32)
+    ds.close()

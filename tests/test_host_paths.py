@@ -247,5 +247,6 @@ def test_which_scans_are_culled(tmp_path):
                     assert culled(ds, m, mode, True) == w, (n, m, mode, "warm")
                     assert culled(ds, m, mode, False) == c, (n, m, mode, "cold")
                     assert culled(ds, m, mode, True, passes=2) == c, (n, m, mode, "stale warm start")
+                    assert not culled(ds, m, mode, False, splits=8)
             dd.dd_dataset_destroy(ds)
         """)
