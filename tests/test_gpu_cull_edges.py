@@ -90,3 +90,73 @@ def test_splits_ask_for_every_tile(L, C0, mode, splits):
     assert torch.equal(idx, ref) and torch.equal(dist, dref)
     assert st["visited"] == n * m and sr["visited"] < 0.7 * n * 32 * ((m + 31) // 32)
     ds.close()
+
+
+def _law(L, n, seed, C0):
+    """n points near a linear law on the GPU, and states around m of them."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    C = torch.from_numpy(np.ascontiguousarray(C0)).cuda()
+    e = torch.empty(n, 6, dtype=torch.float64, device="cuda")
+    s = torch.empty_like(e)
+    for a in range(0, n, 1 << 23):
+        b = min(n, a + (1 << 23))
+        e[a:b] = 1e-3 * torch.randn(b - a, 6, dtype=torch.float64, device="cuda", generator=g)
+        s[a:b] = e[a:b] @ C
+
+    def states(m):
+        pick = torch.randint(0, n, (m,), device="cuda", generator=g)
+        y = torch.cat([e[pick], s[pick]], 1)
+        return (y * (1.0 + 0.05 * torch.randn(m, 12, dtype=torch.float64, device="cuda", generator=g))).contiguous(), pick
+    return e, s, states
+
+
+def _equal(a, b):
+    import torch
+    assert torch.equal(a[0], b[0])
+    assert np.array_equal(a[1].cpu().numpy(), b[1].cpu().numpy(), equal_nan=True)
+
+
+@pytest.mark.parametrize("mode", ["fp64", "fp32", "bf16", "fp16"])
+def test_batch_beyond_a_mask(L, C0, mode):
+    """A batch of more states than the masks hold at once (65536), the last run of them
+    33: the answers of the scan of every tile, from a fraction of its pairs."""
+    n, m = 1 << 18, 65536 + 33
+    e, s, states = _law(L, n, 81, C0)
+    ds = L.dd_dataset_create(e, s, C0, packs=FP64 | FP32 | BF16 | FP16)
+    y, _ = states(m)
+    y[5, 2] = y[m - 1, 7] = float("nan")
+    idx, dist, st = L.dd_project(ds, y, mode=mode, stats=True)
+    _equal((idx, dist), L.dd_project(ds, y, mode=mode, splits=8))
+    assert 0 < st["visited"] < 0.5 * n * m
+    ds.close()
+
+
+def test_run_shorter_than_a_mask(L, C0):
+    """So many tiles that the masks hold 120 of the batch's 124 words of states at once,
+    an odd number of tiles, a last run of four words."""
+    n, m = (1 << 26) + (1 << 22) + 77, 120 * 512 + 3 * 512 + 9
+    e, s, states = _law(L, n, 82, C0)
+    ds = L.dd_dataset_create(e, s, C0, packs=FP64)
+    y, pick = states(m)
+    del e, s
+    idx, dist, st = L.dd_project(ds, y, mode="fp64", stats=True)
+    full = L.dd_project(ds, y, warm_start_idx=pick, mode="fp64", splits=8)
+    _equal((idx, dist), full)
+    assert 0 < st["visited"] < 0.1 * n * m
+    ds.close()
+
+
+@pytest.mark.parametrize("m", [1, 300, 16390])
+def test_large_kmeans_walk_equals_fp64_scan(L, C0, m):
+    """The k-means walk beyond the scans' sizes, begun with the seed bound or a warm start."""
+    n = (1 << 24) + 4097
+    e, s, states = _law(L, n, 83, C0)
+    ds = L.dd_dataset_create(e, s, C0, packs=FP64 | KMEANS)
+    y, pick = states(m)
+    if m > 1:
+        y[m // 2, 5] = float("nan")
+    ref = L.dd_project(ds, y, mode="fp64")
+    for warm in (None, pick):
+        _equal(L.dd_project(ds, y, warm_start_idx=warm, mode="kmeans"), ref)
+    ds.close()
