@@ -422,8 +422,8 @@ static PlaneBlocks plane_blocks(int64_t nx, int64_t ny, int64_t nz) {
 
 // Bytes that K^-1 must be larger by, per block, for the chain's launches to pay.
 // Measured per DD iteration, cubes of n elements a side, FP64 scan of 2000 points,
-// inverse / planes: n = 8 0.128 / 0.146 ms, 11 0.198 / 0.209 (15 MB a block), 12
-// 0.254 / 0.224 (23 MB), 14 0.397 / 0.310, 16 0.693 / 0.392; beyond the inverse's
+// inverse / planes: n = 8 0.127 / 0.149 ms, 11 0.190 / 0.208 (15 MB a block), 12
+// 0.253 / 0.246 (23 MB), 14 0.396 / 0.272, 16 0.693 / 0.365; beyond the inverse's
 // sizes CG / planes: 18 6.2 / 0.51, 20 7.8 / 0.73, 24 12.9 / 1.29, 27 16.9 / 2.06.
 constexpr int64_t kPlaneStepBytes = (int64_t)18 << 20;
 
