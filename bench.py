@@ -491,7 +491,7 @@ def main():
                     help="solves per Poisson run of the serving leg (N=2^26); 0 = skip")
     ap.add_argument("--serve-modes", default="ann",
                     help="projection modes of the serving leg, comma separated (bf16 serves "
-                         "about 0.7 solves/s of this mix: 200 solves take minutes per rate)")
+                         "about 27 solves/s of this mix, ann 15)")
     ap.add_argument("--paper-seeds", type=int, default=3,
                     help="random starts per data-set size in the paper-example leg; 0 = skip")
     ap.add_argument("--paper-only", action="store_true",
