@@ -354,6 +354,14 @@ __global__ __launch_bounds__(256, 6) void ann_walk_kernel(AnnArgs A) {
     yq[k] = A.yq[12 * q + k];
   }
   const float qnorm = (float)sqrt(A.qn2[q]);
+  // squares past the FP32 range bound nothing (2^60 and more, NaN): the fallback's
+  if (__builtin_bit_cast(uint32_t, qnorm + A.xmax) >= 0x5D800000u) {
+    if (lane == 0) {
+      A.fb_list[atomicAdd(A.fb_count, 1)] = (int)q;
+      if (TOP2) A.dist2[q] = -1.0;
+    }
+    return;
+  }
   const float ebase = kEps20 * qnorm;
   const float slack = kEps22 * (qnorm + A.xmax) + 1e-30f;
   // U: pruning bound (the smallest upper bound seen; with TOP2 the second
